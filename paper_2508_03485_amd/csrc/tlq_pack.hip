@@ -1,6 +1,6 @@
 // Twin-Log Quantization of a weight matrix: calibrate (search-based clipping), encode, build the
 // per-channel int8 level table and pack (Method, "Twin-Log Quantization for Weights").  Offline step:
-// one workgroup per output channel, fp64 throughout, written for clarity rather than speed.
+// one workgroup per output channel, fp64 throughout.
 #include "lrq_internal.h"
 
 namespace lrq {
@@ -29,17 +29,6 @@ __device__ __forceinline__ double wave_mind(double v) {
     return v;
 }
 
-// Sum of the workgroup's NT per-thread values in ascending thread order, one fp64 addition after the other (the order
-// the search objective is defined in); red must hold NT doubles.  Every thread returns the same bits.
-__device__ __forceinline__ double block_sum_ascending(double v, double* red) {
-    red[threadIdx.x] = v;
-    __syncthreads();
-    double r = 0.0;
-    for (int i = 0; i < NT; ++i) r = r + red[i];
-    __syncthreads();
-    return r;
-}
-
 __device__ __forceinline__ double block_sum(double v, double* red) {
     v = wave_sum(v);
     if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = v;
@@ -53,53 +42,177 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 
 __device__ __forceinline__ double clampd(double v, double lo, double hi) { return fmin(fmax(v, lo), hi); }
 
-// Grid search of one clip factor for one sign (Eq. hyperparameters clip); all threads return the
-// same (s, z, factor).  sgn = +1 scans the positive weights, -1 the negative ones.
-// ggrid / ngamma: optional grid of the lower clip factor (extension: s = (c W_max - g W_min) / intervals,
-// z = round(g W_min / s)), scanned inside the loop over c; ngamma = 0 is the paper's formula (g = 1).
-// The objective of a candidate is summed in a fixed order: thread j adds the terms of k = j, j + NT, j + 2 NT, ...
-// one after the other, then the NT partial sums are added in ascending j - so which of two close candidates is the
-// smaller one does not depend on the reduction tree.
-__device__ void search_side(const float* __restrict__ w, const double* __restrict__ ell, int K, double sgn,
-                            bool has, double wmax, double wmin, const float* __restrict__ grid, int ngrid,
-                            const float* __restrict__ ggrid, int ngamma,
-                            double nint, double qlo, double qhi, double* red, double& s_out, double& z_out,
-                            float& c_out, float& g_out, double& err_out) {
-    double best_err = INFINITY, best_s = 1.0, best_z = has ? rint(wmin) : 0.0;
-    float best_c = 1.0f, best_g = 1.0f;
+// ---- grid search of the clip factors (Eq. hyperparameters clip), both signs at once ------------------------------------
+// A candidate is one value of the clip factor (and, in the extension with a lower clip, one value of gamma):
+// s = (c W_max - g W_min) / intervals, z = round(g W_min / s); its objective per sign is sum (W_f - W)^2 over the weights of
+// that sign.  The sum has a fixed order: thread j adds the terms of k = j, j + NT, j + 2 NT, ... one after the other, then
+// the NT partial sums are added in ascending j - so which of two close candidates is the smaller one does not depend on a
+// reduction tree.
+// What bounds the search: fp64 vector work, about twenty instructions per weight and candidate.  It is arranged so that little
+// else is left:
+//   * a weight belongs to one sign, so one pass over the weights serves both searches (no idle lanes in a pass per sign);
+//   * a candidate has at most eight levels per sign, so exp2 runs once per level (into an LDS table), not once per weight;
+//   * the quotient W' / s is a multiplication by 1 / s: with |W' / s| <= 2^20 the product is within 2^-31 of the quotient,
+//     which settles the rounding unless it lies within 1e-7 of a half-integer - only then is the division itself taken;
+//   * NC candidates go together: their ordered sums, 256 dependent additions each, run side by side in 2 NC lanes
+//     instead of one after the other in every lane;
+//   * a thread's weights and their logarithms stay in registers (K <= 6144), longer rows keep the logarithms in LDS.
+// Measured at 4608 x 1152 with 21 candidates per sign: 1490 us with a pass per sign, an exp2 and a division per weight and
+// candidate and one ordered sum after the other; 177 us in this form
+// (about 65 us of them the logarithms, the encoding and the packing, 5 us each candidate).
+constexpr int PSTRIDE = NT + 1;          // one double of padding: the lanes that sum in parallel read distinct banks
+constexpr double kMagic = 6755399441055744.0;   // 1.5 * 2^52: adding it rounds to an integer, ties to even
+
+struct Candidate {
+    double s, inv, z;
+    int zlow;                            // z + lowest level index of the sign
+    int mode;                            // 0: skipped, 1: 1 / s settles the rounding (see above), 2: always divide
+};
+
+// NC candidates per pass: 8 (NC * 2 * 257 doubles of partial sums are 33 KB: four workgroups per CU), 4 where a row of
+// logarithms leaves no room for more.
+template <int NC>
+struct __attribute__((aligned(16))) SearchLds {
+    double part[NC][2][PSTRIDE];
+    double level[NC][2][8];
+    Candidate cand[NC][2];
+    double err[NC][2];
+    double best_err[2], best_s[2], best_z[2];
+    float best_c[2], best_g[2];
+};
+
+__device__ __forceinline__ double log2_abs(double w) { return w != 0.0 ? log2(fabs(w)) : 0.0; }
+__device__ __forceinline__ double level_index(double ell, double s, double z, double qlo, double qhi) {
+    return clampd(rint(ell / s) - z, qlo, qhi);
+}
+
+// Elements k = base + e NT + t of the row, e < NE: REGS: the row fits NT * NE elements and el / wv hold it all along; otherwise
+// they are read from ell (LDS) and w for every pass.
+template <int NE, bool REGS, int NC>
+__device__ void search_clip(const float* __restrict__ w, const double* __restrict__ ell, double (&el)[NE], float (&wv)[NE], int K,
+                            const bool (&has)[2], const double (&wmax)[2], const double (&wmin)[2],
+                            const float* __restrict__ agrid, int na, const float* __restrict__ bgrid, int nb,
+                            const float* __restrict__ ggrid, int ngamma, int half, SearchLds<NC>& S) {
+    const int t = threadIdx.x;
     const int ng = ngamma > 0 ? ngamma : 1;
-    for (int ci = 0; ci < ngrid; ++ci)
-    for (int gi = 0; gi < ng; ++gi) {
-        const float c32 = grid[ci];
-        const float g32 = ngamma > 0 ? ggrid[gi] : 1.0f;
-        const double T = (double)c32 * wmax;
-        const double B = (double)g32 * wmin;
-        if (!(has && T > B)) continue;                       // uniform over the workgroup
-        const double s = (T - B) / nint;
-        const double z = rint(B / s);
-        double err = 0.0;
-        for (int k = threadIdx.x; k < K; k += NT) {
-            const double wk = (double)w[k];
-            if (wk * sgn > 0.0) {
-                const double qv = clampd(rint(ell[k] / s) - z, qlo, qhi);
-                const double d = exp2(s * (qv + z)) - fabs(wk);
-                err = err + d * d;
+    const int total = (na > nb ? na : nb) * ng;
+    if (t < 2) {
+        S.best_err[t] = INFINITY;
+        S.best_s[t] = 1.0;
+        S.best_z[t] = has[t] ? rint(wmin[t]) : 0.0;
+        S.best_c[t] = 1.0f;
+        S.best_g[t] = 1.0f;
+    }
+    for (int c0 = 0; c0 < total; c0 += NC) {
+        const int nc = total - c0 < NC ? total - c0 : NC;
+        if (t < NC * 2) {
+            const int j = t / 2, side = t % 2, ci = (c0 + j) / ng, gi = (c0 + j) % ng;
+            Candidate c = {1.0, 1.0, 0.0, 0, 0};
+            if (j < nc && ci < (side ? nb : na) && has[side]) {
+                const float c32 = side ? bgrid[ci] : agrid[ci], g32 = ngamma > 0 ? ggrid[gi] : 1.0f;
+                const double T = (double)c32 * wmax[side], B = (double)g32 * wmin[side];
+                if (T > B) {
+                    c.s = (T - B) / (double)(side ? half : half - 1);
+                    c.z = rint(B / c.s);
+                    c.inv = 1.0 / c.s;
+                    c.mode = fmax(fmax(fabs(wmax[side]), fabs(wmin[side])) * c.inv, fabs(c.z)) <= 1048576.0 ? 1 : 2;
+                    c.zlow = c.mode == 1 ? (int)c.z + side : 0;
+                }
+            }
+            S.cand[j][side] = c;
+        }
+        __syncthreads();
+        if (t < NC * 16) {
+            const int j = t / 16, side = (t / 8) % 2, i = t % 8;
+            const Candidate c = S.cand[j][side];
+            if (i < half && c.mode) S.level[j][side][i] = exp2(c.s * ((double)(i + side) + c.z));
+        }
+        __syncthreads();
+        for (int base = 0; base < K; base += NT * NE) {
+            if constexpr (!REGS) {
+#pragma unroll
+                for (int e = 0; e < NE; ++e) {
+                    const int k = base + e * NT + t;
+                    wv[e] = k < K ? w[k] : 0.0f;
+                    el[e] = k < K ? ell[k] : 0.0;
+                }
+            }
+            for (int j = 0; j < nc; ++j) {
+                const Candidate cp = S.cand[j][0], cn = S.cand[j][1];
+                double ep = base ? S.part[j][0][t] : 0.0, en = base ? S.part[j][1][t] : 0.0;
+                const double ep0 = ep, en0 = en;
+                bool unsettled = cp.mode == 2 || cn.mode == 2;
+                // what is derived from a weight (sign, double) is derived again for every candidate, not kept in registers
+#pragma unroll
+                for (int e = 0; e < NE; ++e) asm volatile("" : "+v"(wv[e]));
+#pragma unroll
+                for (int e = 0; e < NE; ++e) {
+                    const bool neg = wv[e] < 0.0f;
+                    const double y = el[e] * (neg ? cn.inv : cp.inv);
+                    const double m = y + kMagic;
+                    unsettled |= !(fabs(y - (m - kMagic)) < 0.4999999);
+                    const int i = min(max(__double2loint(m) - (neg ? cn.zlow : cp.zlow), 0), half - 1);
+                    const double d = S.level[j][neg ? 1 : 0][i] - fabs((double)wv[e]);
+                    const double d2 = d * d;
+                    ep = ep + (wv[e] > 0.0f ? d2 : 0.0);          // + 0.0 leaves the other sign's sum as it is
+                    en = en + (neg ? d2 : 0.0);
+                    if (e % 3 == 2) __builtin_amdgcn_sched_barrier(0);   // three in flight
+                }
+                if (unsettled) {                                  // rare: this thread's terms again, with the quotient itself
+                    ep = ep0;
+                    en = en0;
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) {
+                        const double wk = (double)wv[e];
+                        if (wk != 0.0) {
+                            const bool neg = wk < 0.0;
+                            const double s = neg ? cn.s : cp.s, z = neg ? cn.z : cp.z, lo = neg ? 1.0 : 0.0;
+                            const double d = exp2(s * (level_index(el[e], s, z, lo, lo + (double)(half - 1)) + z)) - fabs(wk);
+                            if (neg) en = en + d * d; else ep = ep + d * d;
+                        }
+                        __builtin_amdgcn_sched_barrier(0);        // one element after the other: few registers
+                    }
+                }
+                S.part[j][0][t] = ep;
+                S.part[j][1][t] = en;
             }
         }
-        err = block_sum_ascending(err, red);
-        if (err < best_err) {
-            best_err = err;
-            best_s = s;
-            best_z = z;
-            best_c = c32;
-            best_g = g32;
+        __syncthreads();
+        if (t < 2 * nc) {
+            const double* p = S.part[t / 2][t % 2];
+            // eight values are fetched while the eight before them are added: the chain then waits for its additions only
+            double cur[8], nxt[8], r = 0.0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) cur[i] = p[i];
+#pragma unroll 16
+            for (int b = 8; b <= NT; b += 8) {
+                const int at = b < NT ? b : 0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) nxt[i] = p[at + i];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) r = r + cur[i];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) cur[i] = nxt[i];
+            }
+            S.err[t / 2][t % 2] = S.cand[t / 2][t % 2].mode ? r : INFINITY;
         }
+        __syncthreads();
+        if (t < 2) {                                          // first minimum wins, candidates in grid order
+            for (int j = 0; j < nc; ++j) {
+                const double e = S.err[j][t];
+                if (S.cand[j][t].mode && e < S.best_err[t]) {
+                    S.best_err[t] = e;
+                    S.best_s[t] = S.cand[j][t].s;
+                    S.best_z[t] = S.cand[j][t].z;
+                    S.best_c[t] = (t ? bgrid : agrid)[(c0 + j) / ng];
+                    S.best_g[t] = ngamma > 0 ? ggrid[(c0 + j) % ng] : 1.0f;
+                }
+            }
+        }
+        __syncthreads();
     }
-    s_out = best_s;
-    z_out = best_z;
-    c_out = best_c;
-    g_out = best_g;
-    err_out = best_err;
 }
 
 // Round-to-nearest-even bf16 of a double.  The detour over fp32 could round twice only when the fp32 value lands
@@ -129,7 +242,8 @@ __device__ __forceinline__ uint8_t f64_to_e4m3_rne(double x) {
     return (uint8_t)(sgn | ((unsigned)(e + 7) << 3) | ((unsigned)n - 8u));
 }
 
-__global__ __launch_bounds__(NT) void tlq_quantize_pack_kernel(
+template <int NE, bool REGS, int NC>
+__global__ __launch_bounds__(NT, !REGS || NE > 12 ? 2 : (NE > 6 ? 3 : 4)) void tlq_quantize_pack_kernel(
     const float* __restrict__ W, int N, int K, int bits, int I, const float* __restrict__ agrid, int na,
     const float* __restrict__ bgrid, int nb, uint8_t* __restrict__ codes_out, double* __restrict__ s_pos,
     double* __restrict__ s_neg, int32_t* __restrict__ z_pos, int32_t* __restrict__ z_neg,
@@ -137,22 +251,39 @@ __global__ __launch_bounds__(NT) void tlq_quantize_pack_kernel(
     uint8_t* __restrict__ gemm_codes, int32_t* __restrict__ colsum, const float* __restrict__ ggrid, int ngamma,
     float* __restrict__ gamma_pos, float* __restrict__ gamma_neg, uint16_t* __restrict__ levels,
     double* __restrict__ err_pos, double* __restrict__ err_neg, uint8_t* __restrict__ lut_fp8, float* __restrict__ wscale_fp8) {
-    extern __shared__ double sm[];
-    double* ell = sm;                                   // K doubles: log2|w|
-    double* red = sm + K;                               // NT doubles of reduction scratch
-    int8_t* code = reinterpret_cast<int8_t*>(red + NT); // K signed codes
+    // LDS: search state (its partial sums double as reduction scratch outside the search), then the row: its logarithms, each
+    // of which later gives its low byte to the code (REGS: codes only)
+    extern __shared__ __attribute__((aligned(16))) unsigned char sm[];
+    SearchLds<NC>& S = *reinterpret_cast<SearchLds<NC>*>(sm);
+    double* red = &S.part[0][0][0];
+    double* ell = reinterpret_cast<double*>(sm + sizeof(SearchLds<NC>));
+    int8_t* code = reinterpret_cast<int8_t*>(ell);
+    constexpr int CS = REGS ? 1 : 8;                    // bytes from one code to the next
     const int n = blockIdx.x, t = threadIdx.x;
     const float* w = W + (size_t)n * K;
     const int half = 1 << (bits - 1), nlev = 1 << bits;
 
     // W' = log2|W| and the per-sign extrema over the masked positions
     double pmax = -INFINITY, pmin = INFINITY, nmax = -INFINITY, nmin = INFINITY;
-    for (int k = t; k < K; k += NT) {
-        const double wk = (double)w[k];
-        const double l = wk != 0.0 ? log2(fabs(wk)) : 0.0;
-        ell[k] = l;
+    double el[NE];
+    float wv[NE];
+    auto logarithm = [&](float wk32) {
+        const double wk = (double)wk32;
+        const double l = log2_abs(wk);
         if (wk > 0.0) { pmax = fmax(pmax, l); pmin = fmin(pmin, l); }
         if (wk < 0.0) { nmax = fmax(nmax, l); nmin = fmin(nmin, l); }
+        return l;
+    };
+    if constexpr (REGS) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) wv[e] = e * NT + t < K ? w[e * NT + t] : 0.0f;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            el[e] = logarithm(wv[e]);
+            __builtin_amdgcn_sched_barrier(0);           // one element after the other: few registers
+        }
+    } else {
+        for (int k = t; k < K; k += NT) ell[k] = logarithm(w[k]);
     }
     pmax = wave_maxd(pmax); pmin = wave_mind(pmin); nmax = wave_maxd(nmax); nmin = wave_mind(nmin);
     Red4* r4 = reinterpret_cast<Red4*>(red);
@@ -167,12 +298,11 @@ __global__ __launch_bounds__(NT) void tlq_quantize_pack_kernel(
     if (!has_p) pmax = pmin = 0.0;
     if (!has_n) nmax = nmin = 0.0;
 
-    double sp, zp, sn, zn, ep, en;
-    float al, be, gp, gn;
-    search_side(w, ell, K, 1.0, has_p, pmax, pmin, agrid, na, ggrid, ngamma, (double)(half - 1), 0.0, (double)(half - 1),
-                red, sp, zp, al, gp, ep);
-    search_side(w, ell, K, -1.0, has_n, nmax, nmin, bgrid, nb, ggrid, ngamma, (double)half, 1.0, (double)half, red, sn, zn,
-                be, gn, en);
+    const bool has[2] = {has_p, has_n};
+    const double wmax[2] = {pmax, nmax}, wmin[2] = {pmin, nmin};
+    search_clip<NE, REGS, NC>(w, ell, el, wv, K, has, wmax, wmin, agrid, na, bgrid, nb, ggrid, ngamma, half, S);
+    const double sp = S.best_s[0], zp = S.best_z[0], ep = S.best_err[0], sn = S.best_s[1], zn = S.best_z[1], en = S.best_err[1];
+    const float al = S.best_c[0], be = S.best_c[1], gp = S.best_g[0], gn = S.best_g[1];
 
     if (t == 0) {
         s_pos[n] = sp; s_neg[n] = sn; z_pos[n] = (int32_t)zp; z_neg[n] = (int32_t)zn;
@@ -235,19 +365,27 @@ __global__ __launch_bounds__(NT) void tlq_quantize_pack_kernel(
     }
 
     // codes (Eq. log-based quantizer); the negative twin is clamped to [1, 2^(b-1)]
-    for (int k = t; k < K; k += NT) {
-        const double wk = (double)w[k];
-        int c = 0;
-        if (wk > 0.0) c = (int)clampd(rint(ell[k] / sp) - zp, 0.0, (double)(half - 1));
-        else if (wk < 0.0) c = -(int)clampd(rint(ell[k] / sn) - zn, 1.0, (double)half);
-        code[k] = (int8_t)c;
+    auto encode = [&](int k, double l, float wk) {
+        const bool neg = wk < 0.0f;
+        const double lo = neg ? 1.0 : 0.0;
+        const int c = (int)level_index(l, neg ? sn : sp, neg ? zn : zp, lo, lo + (double)(half - 1));
+        code[k * CS] = (int8_t)(wk == 0.0f ? 0 : (neg ? -c : c));
+    };
+    if constexpr (REGS) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            if (e * NT + t < K) encode(e * NT + t, el[e], wv[e]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        for (int k = t; k < K; k += NT) encode(k, ell[k], w[k]);
     }
     __syncthreads();
 
     const unsigned mask = (unsigned)nlev - 1u;
     {   // sum of the channel's decoded levels (exact in fp64: |sum| <= 127 K)
         double part = 0.0;
-        for (int k = t; k < K; k += NT) part += (double)lutv[(unsigned)code[k] & mask];
+        for (int k = t; k < K; k += NT) part += (double)lutv[(unsigned)code[k * CS] & mask];
         const double tot = block_sum(part, red);
         if (t == 0) colsum[n] = (int32_t)tot;
     }
@@ -257,7 +395,7 @@ __global__ __launch_bounds__(NT) void tlq_quantize_pack_kernel(
         for (int g = t; g < K / 8; g += NT) {
             unsigned canon = 0;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) canon |= ((unsigned)code[g * 8 + i] & mask) << (4 * i);
+            for (int i = 0; i < 8; ++i) canon |= ((unsigned)code[(g * 8 + i) * CS] & mask) << (4 * i);
             dst[g] = canon;
         }
     } else {
@@ -266,7 +404,7 @@ __global__ __launch_bounds__(NT) void tlq_quantize_pack_kernel(
         for (int g = t; g < K / 8; g += NT) {
             unsigned v24 = 0;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v24 |= ((unsigned)code[g * 8 + i] & mask) << (3 * i);
+            for (int i = 0; i < 8; ++i) v24 |= ((unsigned)code[(g * 8 + i) * CS] & mask) << (3 * i);
             dst[g * 3 + 0] = (uint8_t)(v24 & 255u);
             dst[g * 3 + 1] = (uint8_t)((v24 >> 8) & 255u);
             dst[g * 3 + 2] = (uint8_t)(v24 >> 16);
@@ -278,7 +416,7 @@ __global__ __launch_bounds__(NT) void tlq_quantize_pack_kernel(
         unsigned tiled = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            tiled |= (((unsigned)code[g * 8 + j] & mask) | (((unsigned)code[g * 8 + 4 + j] & mask) << 4)) << (8 * j);
+            tiled |= (((unsigned)code[(g * 8 + j) * CS] & mask) | (((unsigned)code[(g * 8 + 4 + j) * CS] & mask) << 4)) << (8 * j);
         // slot (n % 16, 16-k group kq) of the unit; the channel's half of its 32-tile picks the slot's 8-byte half
         const int kb = g / 8, r = g % 8, kq = r / 2, d = r % 2;
         const size_t unit = (size_t)(n / kGemmTileN) * (K / kGemmBlockK) + kb;
@@ -293,15 +431,29 @@ hipError_t launch_tlq_quantize_pack(hipStream_t st, const float* W, int N, int K
                                     const float* alpha_grid, int n_alpha, const float* beta_grid, int n_beta,
                                     const lrq_tlq_weight& out, const float* gamma_grid, int n_gamma, float* gamma_pos,
                                     float* gamma_neg) {
-    const size_t lds = (size_t)K * sizeof(double) + NT * sizeof(double) + (size_t)K;
-    {
-        const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(tlq_quantize_pack_kernel), 158 * 1024);
-        if (e != hipSuccess) return e;
+    // Weights per thread: the smallest count that holds the row (K = 1152 fills 4.5 of 5); above 6144 the row goes through the
+    // registers in passes of 16.
+#define LRQ_GO(NE, REGS, NC)                                                                                                  \
+    {                                                                                                                         \
+        const size_t lds = sizeof(SearchLds<NC>) + (size_t)K * (REGS ? 1 : sizeof(double));                                   \
+        const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(tlq_quantize_pack_kernel<NE, REGS, NC>), 158 * 1024); \
+        if (e != hipSuccess) return e;                                                                                        \
+        hipLaunchKernelGGL((tlq_quantize_pack_kernel<NE, REGS, NC>), dim3(N), dim3(NT), lds, st, W, N, K, bits, I, alpha_grid, \
+                           n_alpha, beta_grid, n_beta, out.codes, out.s_pos, out.s_neg, out.z_pos, out.z_neg, out.alpha,      \
+                           out.beta, out.lut, out.wscale, out.gemm_codes, out.colsum, gamma_grid, n_gamma, gamma_pos,         \
+                           gamma_neg, out.levels, out.err_pos, out.err_neg, out.lut_fp8, out.wscale_fp8);                     \
     }
-    hipLaunchKernelGGL(tlq_quantize_pack_kernel, dim3(N), dim3(NT), lds, st, W, N, K, bits, I, alpha_grid, n_alpha,
-                       beta_grid, n_beta, out.codes, out.s_pos, out.s_neg, out.z_pos, out.z_neg, out.alpha, out.beta,
-                       out.lut, out.wscale, out.gemm_codes, out.colsum, gamma_grid, n_gamma, gamma_pos, gamma_neg, out.levels,
-                       out.err_pos, out.err_neg, out.lut_fp8, out.wscale_fp8);
+    const int ne = (K + NT - 1) / NT;
+    if (ne <= 3) LRQ_GO(3, true, 8)
+    else if (ne <= 5) LRQ_GO(5, true, 8)
+    else if (ne <= 6) LRQ_GO(6, true, 8)
+    else if (ne <= 9) LRQ_GO(9, true, 8)
+    else if (ne <= 12) LRQ_GO(12, true, 8)
+    else if (ne <= 18) LRQ_GO(18, true, 8)
+    else if (ne <= 24) LRQ_GO(24, true, 8)
+    else if (K <= 12288) LRQ_GO(16, false, 8)
+    else LRQ_GO(16, false, 4)
+#undef LRQ_GO
     return hipGetLastError();
 }
 

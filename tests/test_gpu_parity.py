@@ -452,6 +452,35 @@ def test_tlq_lower_clip_bit_exact(lrq, N, K, bits):
     assert torch_equal(w0.codes, w1.codes) and torch_equal(w0.lut, w1.lut) and torch_equal(w0.s_pos, w1.s_pos)
 
 
+@pytest.mark.parametrize("K,bits", [(768, 4), (1344, 3), (1536, 4), (2304, 4), (3072, 3), (4608, 4), (6144, 4), (6208, 3), (12288, 3),
+                                    (16384, 4)])
+def test_tlq_search_every_row_length(lrq, K, bits):
+    """Every register count of the search kernel, the first row length that goes through LDS and the longest one; grids
+    of different lengths that are no multiple of a pass of candidates; rounding decisions at and near the tie."""
+    print(f"case tlq rows K={K} b={bits}", flush=True)
+    W = synth.make_weights(6, K, (941, K, bits))
+    # magnitudes 2^0 .. 2^-14: with the factor 1 the quotients log2|w| / s are half-integers for every odd exponent (s = 2 at
+    # 4 bits for the positive twin), i.e. exact ties
+    W[1] = np.exp2(-(np.arange(K) % 15)).astype(np.float32) * np.where(np.arange(K) % 2, -1.0, 1.0)
+    _check_weight(lrq, W, bits, 7, GRID[:9], GRID[:12])
+
+
+def test_tlq_search_with_quotients_past_the_reciprocal_range(lrq):
+    """Two neighbouring fp32 magnitudes per sign: s is about 2e-8 and log2|w| / s about 3e8, where the search divides instead of
+    multiplying by 1 / s.  s itself is the difference of two nearly equal logarithms from two math libraries, so only what
+    does not depend on its last digits is compared: the smaller magnitude takes its twin's lowest code, the larger one the highest."""
+    K = 512
+    lo = np.float32(0.01)
+    hi = np.nextafter(lo, np.float32(1))
+    W = np.where(np.arange(K) % 3 == 0, lo, hi)[None].repeat(3, 0).astype(np.float32)
+    W[:, 1::2] *= -1
+    one = np.array([1.0], np.float32)
+    w = lrq.tlq_quantize_pack(to_dev(W), 4, 7, to_dev(one), to_dev(one))
+    want = np.where(W > 0, np.where(W == hi, 7, 0), np.where(W == -hi, -8, -1)).astype(np.int8)
+    assert np.array_equal(oracle.tlq_encode(W, oracle.tlq_calibrate(W, 4, one, one)), want)
+    assert np.array_equal(w.codes.cpu().numpy(), oracle.pack_codes(want, 4))
+
+
 @pytest.mark.parametrize("N,K,bits", [(70, 192, 4), (48, 128, 3), (33, 64, 4)])
 def test_gemm_code_tiling_matches_its_description(lrq, N, K, bits):
     """The GEMM's private copy of the weight codes: units of (32 channels x 64 k) stored [channel tile][K block], 64 slots
