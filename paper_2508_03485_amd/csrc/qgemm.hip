@@ -19,7 +19,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 constexpr int WAVES = 4;
 constexpr int BK = kGemmBlockK;     // 64
 constexpr int PLANE_PAD = 32;          // padding of a plane (swept 0 / 16 / 32 / 48: 32 leaves the fewest bank conflicts)
-constexpr int AF_DIST = 2;             // A fragments are read this many row tiles (four MFMAs each) ahead of their use (swept 2 - 4: no difference)
+constexpr int AF_DIST = 2;             // A fragments are read this many row tiles (one pair) ahead of their use
 constexpr int PLANE = 32 * 16 + PLANE_PAD;     // bytes of one (row tile, 16-byte k chunk) plane in LDS, padded
 constexpr int EPI_ROW = 64 * 2 + 16;   // bytes of one staged output row of a wave (up to 64 bf16 / 32 fp32) + pad
 constexpr int EPI_WAVE = 32 * EPI_ROW; // one 32-row slab per wave
@@ -86,6 +86,11 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
 }
 
+// fp32(a + zero * colsum).  The sum can exceed 32 bits but is a whole number below 2^53 (|zero| <= 2^31, |colsum| <= 127 K), so
+// fp64 holds it exactly and the conversion rounds it once, as it would a 64-bit integer; that takes three instructions where the
+// 64-bit multiply and conversion take about twenty (2333 x 1152 -> 1091: 2 us of a 15 us launch).
+__device__ __forceinline__ float zp_sum(int a, double zero, double colsum) { return (float)fma(zero, colsum, (double)a); }
+
 // One K block of the main loop.  The A tiles rotate through three LDS buffers: block kb multiplies from `cur`
 // (tile kb), stages tile kb+2 (held in aS, which is then reloaded with tile kb+4) into `st`, and - because tile kb+1
 // in `nx` has been complete since the previous barrier - reads the first A fragments of block kb+1 before its own
@@ -136,24 +141,32 @@ __device__ __forceinline__ void kblock(unsigned char* smem, int cur, int st, int
     constexpr int DIST = AF_DIST;                   // A fragments are read this many row tiles ahead
 #pragma unroll
     for (int p = 0; p < DIST; ++p) af[p] = afp[p];
+    // Two row tiles at a time, their matrix instructions in an order that changes one operand per instruction: the matrix pipe
+    // is limited by the power its operands' toggling draws (35100 x 12288 -> 3072, us: weight operand changing with every
+    // instruction 1207, back and forth over the column tiles 1196, this order 1187 - 1193).
+    static_assert(AF_DIST == 2 && RT % 2 == 0, "row tiles are walked in pairs, one pair read ahead");
 #pragma unroll
-    for (int p = 0; p < RT; ++p) {
+    for (int p = 0; p < RT; p += 2) {
         if (p == RT - 2) {          // next block's first fragments, early enough to land before the closing barrier
 #pragma unroll
             for (int pp = 0; pp < DIST; ++pp)
                 afp[pp] = *reinterpret_cast<const v4i*>(&smem[nx + (pp / 2) * 4 * PLANE + (pp % 2) * 256 + rd_off]);
-        }
-        if (p + DIST < RT)
-            af[p + DIST] = *reinterpret_cast<const v4i*>(&Acur[((p + DIST) / 2) * 4 * PLANE + ((p + DIST) % 2) * 256 + rd_off]);
+        } else {
 #pragma unroll
-        for (int d = 0; d < DPB; ++d) {
+            for (int pp = 0; pp < DIST; ++pp)
+                af[p + DIST + pp] = *reinterpret_cast<const v4i*>(&Acur[((p + DIST) / 2) * 4 * PLANE + pp * 256 + rd_off]);
+        }
+#pragma unroll
+        for (int d = 0; d < 2 * DPB; ++d) {
             const int dd = p * DPB + d, ct = dd / 4;
             if (dd < CT * 4) bdNxt[ct][dd % 4] = (int)decode_dword<BITS>(bRaw[ct / 2], L[ct], ct % 2, dd % 4, C);
         }
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-            acc[p][ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[p], bdCur[ct], acc[p][ct], 0, 0, 0);
-        if (p == RT - 1) {
+        for (int c = 0; c < 2 * CT; ++c) {
+            const int ct = c / 2, i = p + ((c + 1) / 2) % 2;
+            acc[i][ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bdCur[ct], af[i], acc[i][ct], 0, 0, 0);
+        }
+        if (p == RT - 2) {
 #pragma unroll
             for (int j = 0; j < NTW; ++j) bRaw[j] = load_braw<BITS>(bptr[j] + (size_t)kbn * UNIT);
         }
@@ -163,9 +176,9 @@ __device__ __forceinline__ void kblock(unsigned char* smem, int cur, int st, int
 }
 
 // BM rows x (4 waves x NTW x 32) columns per workgroup; RT = BM / 16 row tiles and 2 NTW column tiles of 16 per wave.  Shapes in use
-// (launch_qgemm picks): 128 x 256 (NTW = 2, 128 accumulator registers per lane, two workgroups per CU), 128 x 128
-// (NTW = 1, 64 accumulator registers, three per CU) and 64 x 128 for a few tokens (256-row shapes - half the decode
-// work per MFMA - measured no faster, or slower, on every workload).  ZP: zero-point form (epilogue term).
+// (launch_qgemm picks): 128 x 256 (NTW = 2, 128 accumulator registers per lane, two workgroups per CU), 160 x 128, 128 x 128
+// (NTW = 1, 64 accumulator registers, three per CU) and 64 x 128 (256-row shapes - half the decode work per MFMA - measured
+// no faster, or slower, on every workload).  ZP: zero-point form (epilogue term).
 template <int BITS, int BM, int NTW, bool ZP, bool A4P = false>
 __global__ __launch_bounds__(256, BM * NTW <= 128 ? 3 : (BM * NTW <= 256 ? 2 : 1)) void qgemm_kernel(
     const int8_t* __restrict__ q, const float* __restrict__ scale, int M, int K, int N,
@@ -177,12 +190,14 @@ __global__ __launch_bounds__(256, BM * NTW <= 128 ? 3 : (BM * NTW <= 256 ? 2 : 1
     constexpr int WN = 32 * NTW, BN = WAVES * WN;
     constexpr int ABUF = (BM / 32) * 4 * PLANE;
     constexpr int ACHUNKS = A4P ? BM * 2 : BM * 4;                 // 16-byte chunks of the A tile in global memory
-    constexpr int ALOADS = ACHUNKS >= 256 ? ACHUNKS / 256 : 1;      // per thread (fewer chunks than threads: some are fetched twice)
+    constexpr int ALOADS = (ACHUNKS + 255) / 256;                  // per thread (not a multiple of the threads: some are fetched twice)
     constexpr int ABK = A4P ? BK / 2 : BK;
     constexpr int LDS_BYTES = (3 * ABUF > WAVES * EPI_WAVE) ? 3 * ABUF : WAVES * EPI_WAVE;
     __shared__ __attribute__((aligned(16))) unsigned char smem[LDS_BYTES];
     __shared__ __attribute__((aligned(16))) float sc[BM];
-    __shared__ __attribute__((aligned(16))) int zr[BM];          // per-token zero-points (zero-point form only)
+    __shared__ __attribute__((aligned(16))) int zr[ZP ? BM : 4];      // per-token zero-points (zero-point form only)
+    __shared__ __attribute__((aligned(16))) float wsc[BN], bs[BN];    // scale and bias of the tile's channels
+    __shared__ __attribute__((aligned(16))) int csum[ZP ? BN : 4];    // their level sums (zero-point form only)
 
     // XCD-aware tile order.  Consecutive workgroup ids go round-robin over the 8 XCDs (each with its own L2), so
     // XCD x is handed a contiguous range of a linear tile order; that order walks 8-row-tile groups n-fastest
@@ -245,7 +260,13 @@ __global__ __launch_bounds__(256, BM * NTW <= 128 ? 3 : (BM * NTW <= 256 ? 2 : 1
     if (t < BM) {
         const int r = m0 + t;
         sc[t] = r < M ? scale[r] : 0.0f;
-        zr[t] = (ZP && r < M) ? (zero ? zero[r] : const_zero) : 0;
+        if constexpr (ZP) zr[t] = r < M ? (zero ? zero[r] : const_zero) : 0;
+    }
+    if (t < BN) {
+        const int n = n0 + t < N ? n0 + t : N - 1;
+        wsc[t] = wscale[n];
+        bs[t] = bias ? bias[n] : 0.0f;
+        if constexpr (ZP) csum[t] = colsum[n];
     }
 
     v4i acc[RT][CT];
@@ -319,34 +340,32 @@ __global__ __launch_bounds__(256, BM * NTW <= 128 ? 3 : (BM * NTW <= 256 ? 2 : 1
     if (kb < KB)                // odd number of K blocks
         kblock<BITS, RT, NTW, ALOADS, A4P>(smem, o0, o2, o1, aO, bO, kb, KB, aptr, aoff, bptr, L, C, bdA, bdB, acc, rd_off, afp);
 
-    // ---- epilogue: rescale in fp32.  Lane holds column (lane % 16) and rows 4 (lane / 16) + (0..3) of every 16 x 16
-    // accumulator tile.
-    float wsc[CT], bs[CT];
-    int csum[CT];
+    // ---- epilogue: rescale in fp32.  The weights are the first operand of the matrix instructions, so a lane holds token
+    // lane % 16 and the four neighbouring channels 4 (lane / 16) + (0..3) of every 16 x 16 accumulator tile: they go to
+    // LDS in one 8-byte (bf16) or 16-byte (fp32) store.
+    // y of accumulator tile (i, ct); the zero-point form adds zero_t * colsum_n to the integer sum
+    const int lc = 4 * (lane / 16);
+    float wq[CT][4], bq[CT][4];
+    double cq[CT][4];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-        int n = n0 + wv * WN + ct * 16 + lane % 16;
-        if (n >= N) n = N - 1;
-        wsc[ct] = wscale[n];
-        bs[ct] = bias ? bias[n] : 0.0f;
-        csum[ct] = ZP ? colsum[n] : 0;
-    }
-    // y of accumulator register x of tile (i, ct); the zero-point form adds zero_t * colsum_n to the integer sum
-    // (64-bit: the product can exceed 32 bits)
-    auto rescale4 = [&](int i, int ct, float (&y)[4]) {
-        const int lr0 = i * 16 + 4 * (lane / 16);
-        const float4 s4 = *reinterpret_cast<const float4*>(&sc[lr0]);
-        const float sv[4] = {s4.x, s4.y, s4.z, s4.w};
-        int zv[4] = {0, 0, 0, 0};
+        const float4 w4 = *reinterpret_cast<const float4*>(&wsc[wv * WN + ct * 16 + lc]);
+        const float4 b4 = *reinterpret_cast<const float4*>(&bs[wv * WN + ct * 16 + lc]);
+        wq[ct][0] = w4.x; wq[ct][1] = w4.y; wq[ct][2] = w4.z; wq[ct][3] = w4.w;
+        bq[ct][0] = b4.x; bq[ct][1] = b4.y; bq[ct][2] = b4.z; bq[ct][3] = b4.w;
         if constexpr (ZP) {
-            const int4 z4 = *reinterpret_cast<const int4*>(&zr[lr0]);
-            zv[0] = z4.x; zv[1] = z4.y; zv[2] = z4.z; zv[3] = z4.w;
+            const int4 c4 = *reinterpret_cast<const int4*>(&csum[wv * WN + ct * 16 + lc]);
+            cq[ct][0] = c4.x; cq[ct][1] = c4.y; cq[ct][2] = c4.z; cq[ct][3] = c4.w;
         }
+    }
+    auto rescale4 = [&](int i, int ct, float (&y)[4]) {
+        const float sv = sc[i * 16 + lane % 16];
+        const double zv = ZP ? (double)zr[i * 16 + lane % 16] : 0.0;
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
             const int a = acc[i][ct][x];
-            const float tot = ZP ? (float)((long long)a + (long long)zv[x] * (long long)csum[ct]) : (float)a;
-            y[x] = (tot * sv[x]) * wsc[ct] + bs[ct];
+            const float tot = ZP ? zp_sum(a, zv, cq[ct][x]) : (float)a;
+            y[x] = (tot * sv) * wq[ct][x] + bq[ct][x];
         }
     };
     const int ncol0 = n0 + wv * WN;                 // first column of this wave
@@ -365,29 +384,27 @@ __global__ __launch_bounds__(256, BM * NTW <= 128 ? 3 : (BM * NTW <= 256 ? 2 : 1
                 for (int ct = 0; ct < CT; ++ct) {
                     float y[4];
                     rescale4(2 * i2 + h, ct, y);
-                    const unsigned d[2] = {pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
-#pragma unroll
-                    for (int x = 0; x < 4; ++x)
-                        *reinterpret_cast<uint16_t*>(&slab[(16 * h + 4 * (lane / 16) + x) * EPI_ROW + (ct * 16 + lane % 16) * 2]) =
-                            (uint16_t)(d[x / 2] >> (16 * (x % 2)));
+                    *reinterpret_cast<uint2*>(&slab[(16 * h + lane % 16) * EPI_ROW + (ct * 16 + lc) * 2]) =
+                        make_uint2(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]));
                 }
             wave_sync();
-            // 32 rows x (WN * 2) bytes: WN / 8 lanes per row, 16 bytes per lane
-            constexpr int LPR = WN / 8, RPP = 64 / LPR;
+            if (vec) {
+                // 32 rows x (WN * 2) bytes: WN / 8 lanes per row, 16 bytes per lane
+                constexpr int LPR = WN / 8, RPP = 64 / LPR;
 #pragma unroll
-            for (int p = 0; p < 32 / RPP; ++p) {
-                const int lr = p * RPP + lane / LPR, cb = (lane % LPR) * 8;   // 8 bf16 per lane
-                const uint4 v = *reinterpret_cast<const uint4*>(&slab[lr * EPI_ROW + cb * 2]);
-                const int row = m0 + i2 * 32 + lr, col = ncol0 + cb;
-                if (row < M) {
-                    if (vec && col + 8 <= N) {
-                        *reinterpret_cast<uint4*>(&Yh[(size_t)row * N + col]) = v;
-                    } else {
-                        const unsigned e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                        for (int x = 0; x < 8; ++x)
-                            if (col + x < N) Yh[(size_t)row * N + col + x] = (uint16_t)(e[x / 2] >> (16 * (x % 2)));
-                    }
+                for (int p = 0; p < 32 / RPP; ++p) {
+                    const int lr = p * RPP + lane / LPR, cb = (lane % LPR) * 8;   // 8 bf16 per lane
+                    const uint4 v = *reinterpret_cast<const uint4*>(&slab[lr * EPI_ROW + cb * 2]);
+                    const int row = m0 + i2 * 32 + lr, col = ncol0 + cb;
+                    if (row < M && col < N) *reinterpret_cast<uint4*>(&Yh[(size_t)row * N + col]) = v;
+                }
+            } else {
+                // rows of any alignment: neighbouring lanes store neighbouring elements
+                const int cl = lane % WN, col = ncol0 + cl;
+#pragma unroll 8
+                for (int p = 0; p < WN / 2; ++p) {
+                    const int lr = p * (64 / WN) + lane / WN, row = m0 + i2 * 32 + lr;
+                    if (row < M && col < N) Yh[(size_t)row * N + col] = *reinterpret_cast<const uint16_t*>(&slab[lr * EPI_ROW + cl * 2]);
                 }
             }
             wave_sync();
@@ -406,30 +423,167 @@ __global__ __launch_bounds__(256, BM * NTW <= 128 ? 3 : (BM * NTW <= 256 ? 2 : 1
                     for (int c = 0; c < 2; ++c) {
                         float y[4];
                         rescale4(2 * i2 + h, 2 * j + c, y);
-#pragma unroll
-                        for (int x = 0; x < 4; ++x)
-                            *reinterpret_cast<float*>(&slab[(16 * h + 4 * (lane / 16) + x) * EPI_ROW + (c * 16 + lane % 16) * 4]) = y[x];
+                        *reinterpret_cast<float4*>(&slab[(16 * h + lane % 16) * EPI_ROW + (c * 16 + lc) * 4]) =
+                            make_float4(y[0], y[1], y[2], y[3]);
                     }
                 wave_sync();
+                if (vec) {
 #pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    const int lr = p * 8 + lane / 8, cb = (lane % 8) * 4;    // 4 floats per lane
-                    const uint4 v = *reinterpret_cast<const uint4*>(&slab[lr * EPI_ROW + cb * 4]);
-                    const int row = m0 + i2 * 32 + lr, col = ncol0 + j * 32 + cb;
-                    if (row < M) {
-                        if (vec && col + 4 <= N) {
-                            *reinterpret_cast<uint4*>(&Yf[(size_t)row * N + col]) = v;
-                        } else {
-                            const unsigned e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                            for (int x = 0; x < 4; ++x)
-                                if (col + x < N) Yf[(size_t)row * N + col + x] = __uint_as_float(e[x]);
-                        }
+                    for (int p = 0; p < 4; ++p) {
+                        const int lr = p * 8 + lane / 8, cb = (lane % 8) * 4;    // 4 floats per lane
+                        const uint4 v = *reinterpret_cast<const uint4*>(&slab[lr * EPI_ROW + cb * 4]);
+                        const int row = m0 + i2 * 32 + lr, col = ncol0 + j * 32 + cb;
+                        if (row < M && col < N) *reinterpret_cast<uint4*>(&Yf[(size_t)row * N + col]) = v;
+                    }
+                } else {
+                    const int cl = lane % 32, col = ncol0 + j * 32 + cl;
+#pragma unroll 8
+                    for (int p = 0; p < 16; ++p) {
+                        const int lr = p * 2 + lane / 32, row = m0 + i2 * 32 + lr;
+                        if (row < M && col < N) Yf[(size_t)row * N + col] = *reinterpret_cast<const float*>(&slab[lr * EPI_ROW + cl * 4]);
                     }
                 }
                 wave_sync();
             }
     }
+}
+
+// Small inputs.  A 128-row tile makes so few workgroups of them that most of the chip idles while each walks all of K in
+// sequence (256 x 1152 -> 1152: 18 workgroups on 256 CUs).  Here a workgroup owns 16 RT rows x 32 channels and its SW waves split
+// K between them (wave w takes the K blocks w, w + SW, ...): no LDS and no barrier in the loop, both operands come straight
+// from L2 as matrix operands, the loads of UB blocks in flight at a time.  The partial sums are integers, so their order does
+// not matter; they meet in LDS once at the end.
+constexpr int SW = 8;
+template <int BITS, int RT, bool ZP, bool A4P>
+__global__ __launch_bounds__(64 * SW) void qgemm_small_kernel(
+    const int8_t* __restrict__ q, const float* __restrict__ scale, int M, int K, int N,
+    const uint8_t* __restrict__ gcodes, const int8_t* __restrict__ lut, const float* __restrict__ wscale,
+    const float* __restrict__ bias, int out_fp32, void* __restrict__ Y, int tiles_n,
+    const int32_t* __restrict__ zero, const int32_t* __restrict__ colsum, int const_zero) {
+    static_assert(!A4P || ZP, "the packed form needs the zero-point term of the epilogue");
+    constexpr int UNIT = 64 * 16, UB = RT <= 2 ? 3 : 2;
+    __shared__ __attribute__((aligned(16))) v4i part[SW][2 * RT][64];
+    const int t = threadIdx.x, lane = t % 64, wv = t / 64;
+    const int tn = blockIdx.x % tiles_n, m0 = (blockIdx.x / tiles_n) * (16 * RT);
+    const int KB = K / BK;
+    unsigned L[2][4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        int n = tn * 32 + h * 16 + lane % 16;
+        if (n >= N) n = N - 1;
+        const uint4 lv = *reinterpret_cast<const uint4*>(lut + (size_t)n * 16);
+        L[h][0] = lv.x; L[h][1] = lv.y; L[h][2] = lv.z; L[h][3] = lv.w;
+    }
+    const uint8_t* bptr = gcodes + (size_t)tn * KB * UNIT + (size_t)lane * (UNIT / 64);
+    const int8_t* aptr[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        int r = m0 + i * 16 + lane % 16;
+        if (r >= M) r = M - 1;
+        aptr[i] = A4P ? q + (size_t)r * (K / 2) + (lane / 16) * 8 : q + (size_t)r * K + (lane / 16) * 16;
+    }
+    unsigned C = 0x03020100u;
+    asm volatile("" : "+v"(C));
+    v4i acc[RT][2];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) acc[i][h] = v4i{0, 0, 0, 0};
+    for (int kb0 = wv; kb0 < KB; kb0 += SW * UB) {
+        BRaw<BITS> b[UB];
+        v4i a[UB][RT];
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+            const int kb = kb0 + u * SW < KB ? kb0 + u * SW : kb0;         // past the end: loaded again, not used
+            b[u] = load_braw<BITS>(bptr + (size_t)kb * UNIT);
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                if constexpr (A4P) {
+                    const uint2 w = *reinterpret_cast<const uint2*>(aptr[i] + (size_t)kb * (BK / 2));
+                    a[u][i] = v4i{(int)(w.x & 0x0f0f0f0fu), (int)((w.x >> 4) & 0x0f0f0f0fu), (int)(w.y & 0x0f0f0f0fu),
+                                  (int)((w.y >> 4) & 0x0f0f0f0fu)};
+                } else {
+                    a[u][i] = *reinterpret_cast<const v4i*>(aptr[i] + (size_t)kb * BK);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+            if (kb0 + u * SW < KB) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    v4i bd;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) bd[g] = (int)decode_dword<BITS>(b[u], L[h], h, g, C);
+#pragma unroll
+                    for (int i = 0; i < RT; ++i)
+                        acc[i][h] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bd, a[u][i], acc[i][h], 0, 0, 0);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) part[wv][2 * i + h][lane] = acc[i][h];
+    __syncthreads();
+    // one thread per (accumulator tile, lane): token lane % 16, four neighbouring channels
+    const bool vec = N % 4 == 0;
+    for (int o = t; o < 2 * RT * 64; o += 64 * SW) {
+        const int tile = o / 64, l = o % 64;
+        const int row = m0 + (tile / 2) * 16 + l % 16, n = tn * 32 + (tile % 2) * 16 + 4 * (l / 16);
+        if (row >= M || n >= N) continue;
+        v4i s = part[0][tile][l];
+#pragma unroll
+        for (int w = 1; w < SW; ++w) s += part[w][tile][l];
+        const float sv = scale[row];
+        const double zv = ZP ? (double)(zero ? zero[row] : const_zero) : 0.0;
+        float y[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int nx = n + x < N ? n + x : N - 1;
+            const float tot = ZP ? zp_sum(s[x], zv, (double)colsum[nx]) : (float)s[x];
+            y[x] = (tot * sv) * wscale[nx] + (bias ? bias[nx] : 0.0f);
+        }
+        if (!out_fp32) {
+            uint16_t* dst = reinterpret_cast<uint16_t*>(Y) + (size_t)row * N + n;
+            const unsigned d[2] = {pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
+            if (vec) {
+                *reinterpret_cast<uint2*>(dst) = make_uint2(d[0], d[1]);
+            } else {
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    if (n + x < N) dst[x] = (uint16_t)(d[x / 2] >> (16 * (x % 2)));
+            }
+        } else {
+            float* dst = reinterpret_cast<float*>(Y) + (size_t)row * N + n;
+            if (vec) {
+                *reinterpret_cast<float4*>(dst) = make_float4(y[0], y[1], y[2], y[3]);
+            } else {
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    if (n + x < N) dst[x] = y[x];
+            }
+        }
+    }
+}
+
+template <int BITS, int RT>
+hipError_t launch_small(hipStream_t st, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
+                        const lrq_tlq_weight& w, const float* bias, int fp32, void* Y, bool packed4) {
+    const int tiles_n = (w.N + 31) / 32;
+    const dim3 grid(((M + 16 * RT - 1) / (16 * RT)) * tiles_n), block(64 * SW);
+    const int32_t* none = nullptr;
+    if (packed4)
+        hipLaunchKernelGGL((qgemm_small_kernel<BITS, RT, true, true>), grid, block, 0, st, q, scale, M, K, w.N, w.gemm_codes, w.lut,
+                           w.wscale, bias, fp32, Y, tiles_n, none, w.colsum, -8);
+    else if (zero)
+        hipLaunchKernelGGL((qgemm_small_kernel<BITS, RT, true, false>), grid, block, 0, st, q, scale, M, K, w.N, w.gemm_codes, w.lut,
+                           w.wscale, bias, fp32, Y, tiles_n, zero, w.colsum, 0);
+    else
+        hipLaunchKernelGGL((qgemm_small_kernel<BITS, RT, false, false>), grid, block, 0, st, q, scale, M, K, w.N, w.gemm_codes, w.lut,
+                           w.wscale, bias, fp32, Y, tiles_n, none, w.colsum, 0);
+    return hipGetLastError();
 }
 
 template <int BITS, int BM, int NTW>
@@ -456,20 +610,47 @@ hipError_t launch_qgemm(hipStream_t st, const int8_t* q, const float* scale, con
                         const lrq_tlq_weight& w, const float* bias, int out_dtype, void* Y, bool packed4) {
     if (packed4 && zero) return hipErrorInvalidValue;
     const int fp32 = out_dtype == LRQ_OUT_FP32;
-    // Tile shape.  128 x 256 (two workgroups per CU) is the fastest on long K loops; 128 x 128 (three per CU)
-    // hides the prologue / epilogue of short K loops better and wastes less on N that is not a multiple of 256;
-    // 64 x 128 serves inputs of a few tokens (conditioning vectors), where taller tiles multiply padding.
-    const bool narrow = K <= 2048 || (w.N % 256 != 0 && w.N <= 2048);
-    if (M <= 64) {
-        if (w.bits == 4) return launch<4, 64, 1>(st, q, scale, zero, M, K, w, bias, fp32, Y, packed4);
-        return launch<3, 64, 1>(st, q, scale, zero, M, K, w, bias, fp32, Y, packed4);
+#define LRQ_SHAPE(F, ...) (w.bits == 4 ? F<4, __VA_ARGS__>(st, q, scale, zero, M, K, w, bias, fp32, Y, packed4)   \
+                                       : F<3, __VA_ARGS__>(st, q, scale, zero, M, K, w, bias, fp32, Y, packed4))
+    // Small products.  Up to this many outputs, K split over the waves of a workgroup is faster than tiles that walk all of K in
+    // sequence (M x K -> N, us, split against the best tile: 512 x 1152 -> 1152 7.0 / 7.5, 64 x 3072 -> 9216 12.0 / 14.5, 256 x 3072 ->
+    // 3072 12.2 / 14.6, 16 x 3072 -> 12288 6.2 / 14.2; beyond it the operands are fetched too often: 1024 x 1152 -> 1152 10.1 / 7.7).
+    // Rows per workgroup (1, 2 or 4 sixteens): few while workgroups are what the chip lacks, more once there is one or two per
+    // CU, so that the weights are fetched and decoded less often (us with 1 / 2 / 4: 64 x 1152 -> 1152 3.4 / 4.1 / 4.8, 256 x 1152 ->
+    // 1152 5.3 / 5.7 / 4.8; 64 x 12288 -> 3072 16.6 / 15.4 / 24.9).  Up to 24 K blocks a wave has a single batch of loads, and the
+    // taller tiles pay sooner.
+    if ((long)M * w.N <= 768 * 1024) {
+        const long tn = (w.N + 31) / 32;
+        const bool single = K <= 24 * BK;
+        if (M <= 16 || (M + 15) / 16 * tn <= (single ? 256 : 512)) return LRQ_SHAPE(launch_small, 1);
+        if ((M + 31) / 32 * tn <= (single ? 256 : 768)) return LRQ_SHAPE(launch_small, 2);
+        return LRQ_SHAPE(launch_small, 4);
     }
-    if (narrow) {
-        if (w.bits == 4) return launch<4, 128, 1>(st, q, scale, zero, M, K, w, bias, fp32, Y, packed4);
-        return launch<3, 128, 1>(st, q, scale, zero, M, K, w, bias, fp32, Y, packed4);
+    // Tile shape.  A CU's tiles run one after the other or share it at the same total rate, so the time follows from the tiles of the
+    // fullest CU: ceil(tiles / 256) x (K blocks + about four for prologue and epilogue) x the shape's time per K block (measured
+    // with one tile per CU and with many, us: 128 x 256 0.47 - 0.49, 160 x 128 0.37, 128 x 128 0.28 - 0.32, 64 x 128 0.17 - 0.24).
+    // Output rows that are not 16-byte aligned leave element by element, which costs most where no other tile hides it.  The
+    // tall shapes decode less per matrix instruction, the small ones leave less of the chip idle in the last round: 8192 x 4608 ->
+    // 1152 takes 56 us with 160 rows (468 tiles) and 61 with 128 (576), 1000 x 3072 -> 3072 takes 20 us with 128 x 128 and 29 with
+    // 128 x 256, 2333 x 1152 -> 1091 in fp32 10.2 us with 64 rows and 13.0 with 128.
+    const struct { int bm, ntw; float us; } shapes[] = {{128, 2, 0.48f}, {160, 1, 0.37f}, {128, 1, 0.29f}, {64, 1, 0.175f}};
+    const bool aligned = w.N % (fp32 ? 4 : 8) == 0;
+    int best = 0;
+    float best_us = 0.0f;
+    for (int i = 0; i < 4; ++i) {
+        const long bn = WAVES * 32 * shapes[i].ntw;
+        const long tiles = (long)((M + shapes[i].bm - 1) / shapes[i].bm) * ((w.N + bn - 1) / bn);
+        const int blocks = K / BK + 4 + (aligned ? 0 : shapes[i].bm * shapes[i].ntw / 8);
+        const float us = (float)((tiles + 255) / 256) * (float)blocks * shapes[i].us;
+        if (i == 0 || us < best_us) { best = i; best_us = us; }
     }
-    if (w.bits == 4) return launch<4, 128, 2>(st, q, scale, zero, M, K, w, bias, fp32, Y, packed4);
-    return launch<3, 128, 2>(st, q, scale, zero, M, K, w, bias, fp32, Y, packed4);
+    switch (best) {
+        case 0: return LRQ_SHAPE(launch, 128, 2);
+        case 1: return LRQ_SHAPE(launch, 160, 1);
+        case 2: return LRQ_SHAPE(launch, 128, 1);
+        default: return LRQ_SHAPE(launch, 64, 1);
+    }
+#undef LRQ_SHAPE
 }
 
 }  // namespace lrq

@@ -564,6 +564,45 @@ def test_qgemm_against_oracle(lrq, M, N, K, w_bits, a_bits):
         assert np.array_equal(acc.astype(np.float64), ref_acc)
 
 
+@pytest.mark.parametrize("M,N,K,w_bits,form", [
+    (5, 70, 64, 3, "symmetric"),          # split K: 16-row tiles, fewer K blocks than waves, cut channel tile, odd pairs
+    (17, 33, 1600, 4, "zero_point"),      # 25 blocks: a second batch that only one wave has
+    (150, 1151, 576, 4, "packed"),        # 32-row tiles, N odd
+    (290, 1030, 640, 3, "zero_point"),    # 64-row tiles, cut row tile
+    (770, 1090, 128, 4, "symmetric"),     # just above the split-K range: 64 x 128 tiles, rows of Y not 16-byte aligned
+    (6300, 133, 192, 4, "packed"),        # 128 or 64 rows, three blocks, cut channel tile
+    (8192, 1152, 320, 4, "symmetric"),    # 160 x 128 tiles, cut row tile
+    (8190, 1149, 64, 3, "zero_point"),    # one K block, ragged both ways
+    (4607, 3064, 128, 4, "symmetric"),    # 128 x 256 tiles, cut both ways
+])
+def test_qgemm_tile_shapes(lrq, M, N, K, w_bits, form):
+    """Every shape of the GEMM's dispatch and its edges.  Scales of one make the fp32 outputs the integer sums themselves,
+    which are below 2^24 here except for the zero-point form's, rounded once."""
+    import torch
+    print(f"case qgemm shapes M={M} N={N} K={K} W{w_bits} {form}", flush=True)
+    rng = synth.rng_for(909, M, N, K)
+    gd = to_dev(np.array([1.0, 1.5], np.float32))
+    w = lrq.tlq_quantize_pack(to_dev(synth.make_weights(N, K, (909, N, K))), w_bits, 7, gd, gd)
+    lut = w.lut.cpu().numpy().astype(np.int64)
+    codes = oracle.unpack_codes(w.codes.cpu().numpy(), w_bits, K).astype(np.int64) & (2 ** w_bits - 1)
+    wv = np.take_along_axis(lut, codes, axis=1).astype(np.float64)
+    lim = 7 if form == "packed" else 127
+    q = rng.integers(-lim, lim + 1, size=(M, K)).astype(np.int8)
+    ref = q.astype(np.float64) @ wv.T
+    zero = None
+    if form == "zero_point":
+        zero = rng.integers(-2 ** 31, 2 ** 31, size=M).astype(np.int32)
+        ref += zero.astype(np.float64)[:, None] * wv.sum(axis=1)[None, :]      # below 2^53: exact
+    w.wscale.fill_(1.0)
+    ones = torch.ones(M, device="cuda")
+    for dt in (torch.float32, torch.bfloat16):
+        if form == "packed":
+            y = lrq.qgemm_packed4(to_dev(oracle.pack_act_codes4(q)), ones, w, out_dtype=dt)
+        else:
+            y = lrq.qgemm(to_dev(q), ones, w, out_dtype=dt, zero=None if zero is None else to_dev(zero))
+        assert torch.equal(y.cpu(), torch.from_numpy(ref).to(torch.float32).to(dt))
+
+
 @pytest.mark.parametrize("M,N,K,w_bits,a_bits,I", [
     (256, 1152, 1152, 4, 8, 7),   # config 1
     (300, 352, 1152, 4, 8, 7),    # ragged M, N not a multiple of the workgroup tile
