@@ -782,83 +782,278 @@ __global__ __launch_bounds__(256, 2) void blockdiag_rotate_mfma_f64_kernel(const
         }
 }
 
-// out[row, j] = in[row, perm[j]] for fp64 rows: the row is staged in LDS so that global reads and writes are both
-// contiguous.  Indices are clamped into [0, K) (a malformed perm gives wrong values, never an out-of-range access).
-__global__ __launch_bounds__(256) void permute_rows_f64_kernel(const double* __restrict__ in, const int32_t* __restrict__ perm,
-                                                                int M, int K, double* __restrict__ out) {
-    extern __shared__ __attribute__((aligned(16))) double prow[];
-    const int t = threadIdx.x;
-    for (int row = blockIdx.x; row < M; row += gridDim.x) {
-        const double2* src = reinterpret_cast<const double2*>(in + (size_t)row * K);
-        for (int c = t; c < K / 2; c += 256) reinterpret_cast<double2*>(prow)[c] = src[c];
-        __syncthreads();
-        double2* dst = reinterpret_cast<double2*>(out + (size_t)row * K);
-        for (int c = t; c < K / 2; c += 256) {
-            const int2 pi = reinterpret_cast<const int2*>(perm)[c];
-            const int i0 = min(max(pi.x, 0), K - 1), i1 = min(max(pi.y, 0), K - 1);
-            dst[c] = make_double2(prow[i0], prow[i1]);
+// The two block-diagonal products of the structured rotation on the fp64 matrix cores, 64 x 128 output tiles:
+// dst[:, block g] = left[:, block g] . R_g with R bf16 [K/B, B, B].
+// GATHER = false: left = bf16 x (times the fp32 pre-scale): every product is exact in fp64, so the matrix instruction's fused
+//   multiply-adds (v_mfma_f64_16x16x4_f64 takes its four k in ascending order) give the plain ascending-k sum.
+// GATHER = true: left[:, j] = z[:, perm[j]] with fp64 z.  The definition rounds every product and every sum separately.  A product
+//   with a bf16 value is exact, and the fused form the same, when z has at most 45 significant bits, i.e. when the last 8 bits of
+//   its significand are zero.  The z of ordinary activations have 25 to 40 bits (they are sums of 16-bit products of similar
+//   exponents; 6 in 100000 have more than 45), so a wave looks at the z of every matrix step (16 rows x 4 k).  For the rows with
+//   one that does not pass, products rounded on their own are added through matrix instructions with an identity operand, so
+//   that the accumulators have one layout: 16 times the step's time.
+//   The first product leaves the number of such z of each of its tiles in wide (K / 128 ints at the head of the row tile's q
+//   rows, which the quantizer overwrites later); row tiles with more than one in 1024 are left to
+//   blockdiag_rotate_seq_f64_kernel, which computes all of them with separate roundings (there a pre-scale ends up: its fp32
+//   factors fill the significands).
+//   The channels are gathered straight from z (indices clamped into [0, K): a malformed perm gives wrong values, never an
+//   out-of-range access); the column tiles of a row tile run on one XCD, whose L2 serves the 16 values of a line that
+//   different column tiles need.
+// Bound by fp64 matrix issue (46 us per product at 4608 x 3072, B = 128) and the passes over z, 24 us each: 76 us for the first
+// product (85 with 128 x 128 tiles, too few for the chip), 126 + 5 us for the second (154 on the vector units after a
+// permutation pass of 38).
+// LDS rows: 34 doubles (left) and 288 bytes (R), which put the 32 lanes of a fragment read on distinct banks.
+__device__ __forceinline__ bool tile_is_wide(const int8_t* wide, int row0, int K) {      // the same answer in every lane
+    const int* c = reinterpret_cast<const int*>(wide + (size_t)row0 * K);
+    int n = 0;
+    for (int i = threadIdx.x % kWave; i < K / 128; i += kWave) n += c[i];
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) n += __shfl_xor(n, o, kWave);
+    return n > K / 16;                               // 64 K / 1024
+}
+
+template <bool GATHER>
+__global__ __launch_bounds__(256, 3) void blockdiag_stage_kernel(const void* __restrict__ src, const int32_t* __restrict__ perm,
+                                                                 const uint16_t* __restrict__ R, int M, int K, int B,
+                                                                 double* __restrict__ dst, const float* __restrict__ ps, int tiles_m,
+                                                                 int8_t* __restrict__ wide) {
+    constexpr int KS = 32, TM = 64, TN = 128;
+    constexpr int LS = KS + 2, RS = 288;            // row strides: doubles, bytes
+    __shared__ __attribute__((aligned(16))) double Ls[2][TM * LS];
+    __shared__ __attribute__((aligned(16))) unsigned char Rs[2][KS * RS];
+    const int t = threadIdx.x, lane = t % 64, wv = t / 64;
+    const int wm = wv / 2, wn = wv % 2;
+    // workgroup ids are dealt round-robin to the 8 XCDs: XCD x takes the row tiles x, x + 8, ...
+    const int tiles_n = K / TN, seq = blockIdx.x / 8;
+    const int tm = seq / tiles_n * 8 + blockIdx.x % 8;
+    if (tm >= tiles_m) return;
+    const int row0 = tm * TM, col0 = seq % tiles_n * TN;
+    if (GATHER && tile_is_wide(wide, row0, K)) return;
+    const int g = col0 / B, kbase = g * B, cb = col0 - kbase;
+    v4d acc[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+    const int lr = t / 4, lk = (t % 4) * 8;         // left tile: 8 values per thread
+    const int rk = t / 16, rc = (t % 16) * 8;       // R tile: rows rk and rk + 16, 8 bf16 each
+    const size_t lrow = (size_t)(row0 + lr < M ? row0 + lr : M - 1) * K;
+    const uint16_t* rsrc = R + (size_t)g * B * B + (size_t)rk * B + cb + rc;
+    double ln[8];                                   // the stage in flight
+    uint4 xn, rn0, rn1;
+    int4 pn0 = {0, 0, 0, 0}, pn1 = {0, 0, 0, 0};    // indices of the stage after it
+    auto load_perm = [&](int k0) {
+        if constexpr (GATHER) {
+            const int4* p = reinterpret_cast<const int4*>(perm + kbase + lk + k0);
+            pn0 = p[0];
+            pn1 = p[1];
         }
+    };
+    auto load = [&](int k0) {
+        if constexpr (GATHER) {
+            const double* z = static_cast<const double*>(src) + lrow;
+            const int pi[8] = {pn0.x, pn0.y, pn0.z, pn0.w, pn1.x, pn1.y, pn1.z, pn1.w};
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ln[i] = z[min(max(pi[i], 0), K - 1)];
+        } else {
+            xn = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src) + lrow + kbase + lk + k0);
+        }
+        rn0 = *reinterpret_cast<const uint4*>(rsrc + (size_t)k0 * B);
+        rn1 = *reinterpret_cast<const uint4*>(rsrc + (size_t)(k0 + 16) * B);
+    };
+    auto stage = [&](int buf, int k0) {
+        if constexpr (!GATHER) {
+            const unsigned w[4] = {xn.x, xn.y, xn.z, xn.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                ln[2 * i] = (double)__uint_as_float(w[i] << 16);
+                ln[2 * i + 1] = (double)__uint_as_float(w[i] & 0xffff0000u);
+            }
+            if (ps) prescale8(ps + kbase + lk + k0, ln);
+        }
+        double2* ld = reinterpret_cast<double2*>(&Ls[buf][lr * LS + lk]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ld[i] = make_double2(ln[2 * i], ln[2 * i + 1]);
+        *reinterpret_cast<uint4*>(&Rs[buf][rk * RS + rc * 2]) = rn0;
+        *reinterpret_cast<uint4*>(&Rs[buf][(rk + 16) * RS + rc * 2]) = rn1;
+    };
+    load_perm(0);
+    load(0);
+    load_perm(KS);                                  // B >= 128: there is a second stage
+    stage(0, 0);
+    __syncthreads();
+    int cur = 0;
+    for (int k0 = 0; k0 < B; k0 += KS, cur ^= 1) {
+        const bool more = k0 + KS < B;
+        if (more) {
+            load(k0 + KS);
+            if (k0 + 2 * KS < B) load_perm(k0 + 2 * KS);
+        }
+        const double* la = &Ls[cur][(wm * 32 + lane % 16) * LS + lane / 16];
+        const unsigned char* rb = &Rs[cur][(lane / 16) * RS + (wn * 64 + lane % 16) * 2];
+#pragma unroll 2
+        for (int ks = 0; ks < KS / 4; ++ks) {
+            double a[2], b[4];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) a[i] = la[i * 16 * LS + ks * 4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                b[j] = (double)__uint_as_float((unsigned)*reinterpret_cast<const uint16_t*>(rb + ks * 4 * RS + j * 32) << 16);
+            unsigned long long low[2] = {0, 0};
+            if constexpr (GATHER) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) low[i] = __ballot((__double2loint(a[i]) & 0xff) != 0);
+                if (low[0] | low[1]) {
+                    // rows to redo: some z does not pass, all are finite (a row with an infinite one ends infinite either way)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        unsigned long long inf = __ballot((__double2hiint(a[i]) & 0x7ff00000) == 0x7ff00000);
+                        low[i] |= low[i] >> 32; low[i] |= low[i] >> 16;
+                        inf |= inf >> 32; inf |= inf >> 16;
+                        low[i] &= ~inf & 0xffffull;
+                        if ((low[i] >> (lane % 16)) & 1) a[i] = 0.0;
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+            if constexpr (GATHER) {
+                if (low[0] | low[1]) {
+#pragma unroll 1
+                    for (int kk = ks * 4; kk < ks * 4 + 4; ++kk) {
+                        double z[2];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+                            z[i] = (low[i] >> (lane % 16)) & 1 ? Ls[cur][(wm * 32 + i * 16 + lane % 16) * LS + kk] : 0.0;
+#pragma unroll 1
+                        for (int s = 0; s < 4; ++s) {      // output columns 4 s + [0, 4) of every column tile
+                            const int c = 4 * s + lane / 16;
+                            const double one = lane % 16 == c ? 1.0 : 0.0;
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                const double r = (double)__uint_as_float((unsigned)*reinterpret_cast<const uint16_t*>(
+                                                                             &Rs[cur][kk * RS + (wn * 64 + j * 16 + c) * 2]) << 16);
+#pragma unroll
+                                for (int i = 0; i < 2; ++i)
+                                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(__dmul_rn(z[i], r), one, acc[i][j], 0, 0, 0);
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        if (more) stage(cur ^ 1, k0 + KS);          // its last readers passed the barrier that closed the previous stage
         __syncthreads();
+    }
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = row0 + wm * 32 + i * 16 + 4 * r + lane / 16;
+            if (row < M) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double u = acc[i][j][r];
+                    dst[(size_t)row * K + col0 + wn * 64 + j * 16 + lane % 16] = u;
+                    if (!GATHER) n += (__double2loint(u) & 0xff) != 0;
+                }
+            }
+        }
+    if constexpr (!GATHER) {
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) n += __shfl_xor(n, o, kWave);
+        int* sum = reinterpret_cast<int*>(Rs[0]);    // the last stage's barrier is behind every reader
+        if (lane == 0) sum[wv] = n;
+        __syncthreads();
+        if (t == 0) reinterpret_cast<int*>(wide + (size_t)row0 * K)[col0 / TN] = sum[0] + sum[1] + sum[2] + sum[3];
     }
 }
 
-// Second stage of the structured rotation: dst[:, block g] = src[:, block g] . R_g for fp64 src and bf16 R
-// [K/B, B, B].  A product of an fp64 value and a bf16 value is not exact in fp64, so here multiply and add round
-// separately, term by term in ascending k - the plain sum the definition states - and the fused multiply-adds of the
-// matrix cores cannot be used.  64 x 64 output tile per workgroup, 4 x 4 outputs per thread, 16 k per LDS stage.
+// The second product with separate roundings throughout, for the row tiles that blockdiag_stage_kernel<true> leaves (wide, see
+// there; nullptr: all of them): bound by fp64 vector issue.  64 x 128 output tile per workgroup, 8 x 4 outputs per thread
+// (96 bytes from LDS per 64 operations; with 4 x 4 outputs LDS takes as long as the arithmetic), 16 k per stage in two LDS
+// buffers, the next stage in flight, channels gathered as above: 172 us at 4608 x 3072, B = 128.
+constexpr int SC = 128;  // output columns of one workgroup
 __global__ __launch_bounds__(256) void blockdiag_rotate_seq_f64_kernel(const double* __restrict__ src,
+                                                                        const int32_t* __restrict__ perm,
                                                                         const uint16_t* __restrict__ R, int M, int K, int B,
-                                                                        double* __restrict__ dst) {
-    __shared__ double Xs[DK][DT + 1];
-    __shared__ double Rs[DK][DT];
+                                                                        double* __restrict__ dst, int tiles_m,
+                                                                        const int8_t* __restrict__ wide) {
+    __shared__ __attribute__((aligned(16))) double Xs[2][DK][DT + 2];
+    __shared__ __attribute__((aligned(16))) double Rs[2][DK][SC];
     const int t = threadIdx.x;
-    const int row0 = blockIdx.y * DT, col0 = blockIdx.x * DT;
+    const int tiles_n = K / SC, seq = blockIdx.x / 8;
+    const int tm = seq / tiles_n * 8 + blockIdx.x % 8;
+    if (tm >= tiles_m) return;
+    const int row0 = tm * DT, col0 = seq % tiles_n * SC;
+    if (wide && !tile_is_wide(wide, row0, K)) return;
     const int g = col0 / B, kbase = g * B, cb = col0 - kbase;
-    const int ty = t / 16, tx = t % 16;
-    double acc[4][4];
+    const int ty = t / 32, tx = t % 32;          // rows 8 ty + [0, 8), columns 2 tx + {0, 1} and 64 + 2 tx + {0, 1}
+    double acc[8][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
     const int xr = t / 4, xk = (t % 4) * 4;      // src tile: 64 rows x 16 k, 4 doubles per thread
-    const int rk = t / 16, rc = (t % 16) * 4;    // R tile: 16 k x 64 cols, 4 bf16 per thread
-    int xrow = row0 + xr;
-    if (xrow >= M) xrow = M - 1;
-    const uint16_t* Rg = R + (size_t)g * B * B;
-    for (int k0 = 0; k0 < B; k0 += DK) {
-        const double2 x0 = *reinterpret_cast<const double2*>(src + (size_t)xrow * K + kbase + k0 + xk);
-        const double2 x1 = *reinterpret_cast<const double2*>(src + (size_t)xrow * K + kbase + k0 + xk + 2);
-        const uint2 ra = *reinterpret_cast<const uint2*>(Rg + (size_t)(k0 + rk) * B + cb + rc);
-        Xs[xk + 0][xr] = x0.x;
-        Xs[xk + 1][xr] = x0.y;
-        Xs[xk + 2][xr] = x1.x;
-        Xs[xk + 3][xr] = x1.y;
-        Rs[rk][rc + 0] = (double)__uint_as_float(ra.x << 16);
-        Rs[rk][rc + 1] = (double)__uint_as_float(ra.x & 0xffff0000u);
-        Rs[rk][rc + 2] = (double)__uint_as_float(ra.y << 16);
-        Rs[rk][rc + 3] = (double)__uint_as_float(ra.y & 0xffff0000u);
-        __syncthreads();
+    const int rk = t / 16, rc = (t % 16) * 8;    // R tile: 16 k x 128 cols, 8 bf16 per thread
+    const int xrow = row0 + xr < M ? row0 + xr : M - 1;
+    const double* xsrc = src + (size_t)xrow * K;
+    const int32_t* pk = perm + kbase + xk;
+    const uint16_t* rsrc = R + (size_t)g * B * B + (size_t)rk * B + cb + rc;
+    auto clampk = [&](int k) { return min(max(k, 0), K - 1); };
+    double xn[4];
+    uint4 rn;
+    auto load = [&](int k0) {
+        const int4 p = *reinterpret_cast<const int4*>(pk + k0);
+        xn[0] = xsrc[clampk(p.x)]; xn[1] = xsrc[clampk(p.y)]; xn[2] = xsrc[clampk(p.z)]; xn[3] = xsrc[clampk(p.w)];
+        rn = *reinterpret_cast<const uint4*>(rsrc + (size_t)k0 * B);
+    };
+    auto store = [&](int buf) {
 #pragma unroll
+        for (int i = 0; i < 4; ++i) Xs[buf][xk + i][xr] = xn[i];
+        const unsigned w[4] = {rn.x, rn.y, rn.z, rn.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<double2*>(&Rs[buf][rk][rc + 2 * i]) =
+                make_double2((double)__uint_as_float(w[i] << 16), (double)__uint_as_float(w[i] & 0xffff0000u));
+    };
+    load(0);
+    store(0);
+    __syncthreads();
+    int cur = 0;
+    for (int k0 = 0; k0 < B; k0 += DK, cur ^= 1) {
+        const bool more = k0 + DK < B;
+        if (more) load(k0 + DK);
+#pragma unroll 4
         for (int kk = 0; kk < DK; ++kk) {
-            double a[4], b[4];
+            double a[8], b[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = Xs[kk][ty * 4 + i];
+            for (int i = 0; i < 4; ++i) {
+                const double2 v = *reinterpret_cast<const double2*>(&Xs[cur][kk][ty * 8 + 2 * i]);
+                a[2 * i] = v.x; a[2 * i + 1] = v.y;
+            }
+            const double2 b0 = *reinterpret_cast<const double2*>(&Rs[cur][kk][2 * tx]);
+            const double2 b1 = *reinterpret_cast<const double2*>(&Rs[cur][kk][64 + 2 * tx]);
+            b[0] = b0.x; b[1] = b0.y; b[2] = b1.x; b[3] = b1.y;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Rs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 8; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc[i][j] = __dadd_rn(acc[i][j], __dmul_rn(a[i], b[j]));
         }
+        if (more) store(cur ^ 1);                // its last readers passed the barrier that closed the previous stage
         __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = row0 + ty * 4 + i;
+    for (int i = 0; i < 8; ++i) {
+        const int r = row0 + ty * 8 + i;
         if (r < M) {
-            double* o = dst + (size_t)r * K + col0 + tx * 4;
+            double* o = dst + (size_t)r * K + col0 + 2 * tx;
             *reinterpret_cast<double2*>(o) = make_double2(acc[i][0], acc[i][1]);
-            *reinterpret_cast<double2*>(o + 2) = make_double2(acc[i][2], acc[i][3]);
+            *reinterpret_cast<double2*>(o + 64) = make_double2(acc[i][2], acc[i][3]);
         }
     }
 }
@@ -1135,25 +1330,27 @@ hipError_t launch_dense_rotate_quant(hipStream_t st, const uint16_t* X, const ui
     return hipGetLastError();
 }
 
-// Structured outlier-aware rotation u = ((x . R1) . P) . R2, fp64 throughout: block-diagonal product on the fp64
-// matrix cores into Z (U's storage; its products are exact, so the fused accumulation is the plain sum), row
-// permutation into Zp, second block-diagonal product with separately rounded multiply and add back into U, then the
-// per-token quantizer.
+// Structured outlier-aware rotation u = ((x . R1) . P) . R2, fp64 throughout: the first block-diagonal product into Zp, the
+// second one on the permuted channels into U, then the per-token quantizer.
 hipError_t launch_blockperm_rotate_quant(hipStream_t st, const uint16_t* X, int M, int K, int B, const uint16_t* R1,
                                          const int32_t* perm, const uint16_t* R2, int act_bits, double* U, double* Zp,
                                          int8_t* q, float* scale, int32_t* zero, const float* prescale) {
-    double* Z = U;
-    const dim3 grid(K / MT_, (M + MT_ - 1) / MT_);
-    hipLaunchKernelGGL((blockdiag_rotate_mfma_f64_kernel<MT_>), grid, dim3(256), 0, st, X, R1, M, K, B, Z, prescale, 0);
+    static_assert(DT == 64 && SC == 128, "both kernels of the second product walk the same tiles");
+    const int tiles_m = (M + DT - 1) / DT;
+    const dim3 grid((tiles_m + 7) / 8 * 8 * (K / SC)), block(256);
+    const int32_t* none = nullptr;
+    hipLaunchKernelGGL(blockdiag_stage_kernel<false>, grid, block, 0, st, static_cast<const void*>(X), none, R1, M, K, B, Zp, prescale,
+                       tiles_m, q);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = allow_large_lds(reinterpret_cast<const void*>(permute_rows_f64_kernel), 158 * 1024);
-    if (e != hipSuccess) return e;
-    const int pgrid = M < 4096 ? M : 4096;
-    hipLaunchKernelGGL(permute_rows_f64_kernel, dim3(pgrid), dim3(256), (size_t)K * sizeof(double), st, Z, perm, M, K, Zp);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(blockdiag_rotate_seq_f64_kernel, dim3(K / DT, (M + DT - 1) / DT), dim3(256), 0, st, Zp, R2, M, K, B, U);
+    if (!prescale) {
+        hipLaunchKernelGGL(blockdiag_stage_kernel<true>, grid, block, 0, st, static_cast<const void*>(Zp), perm, R2, M, K, B, U,
+                           static_cast<const float*>(nullptr), tiles_m, q);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(blockdiag_rotate_seq_f64_kernel, grid, block, 0, st, Zp, perm, R2, M, K, B, U, tiles_m,
+                       static_cast<const int8_t*>(prescale ? nullptr : q));
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const QuantSpec qs = make_spec(act_bits, 1, zero);

@@ -304,6 +304,31 @@ def test_blockperm_rotate_quant_bit_exact(lrq, M, K, B, a_bits, asym):
     assert np.array_equal(u, u_ref)
 
 
+@pytest.mark.parametrize("M,K,B,spread", [(200, 384, 128, 4), (130, 512, 256, 7), (129, 256, 128, 12), (70, 256, 128, 40)])
+def test_blockperm_significands_of_every_width(lrq, M, K, B, spread):
+    """Exponents spread over 2^+-spread make z = x.R1 use up to all 53 bits of its significand: the second product then mixes
+    fused and separately rounded steps (small spreads) or takes separate roundings for whole row tiles (large ones)."""
+    print(f"case blockperm widths M={M} K={K} B={B} spread={spread}", flush=True)
+    rng = synth.rng_for(910, M, K, spread)
+    x = rng.standard_normal((M, K))
+    x[: M // 2] *= np.exp2(rng.integers(-spread, spread + 1, size=(M // 2, K)))
+    x[M // 2:, :: 17] *= np.exp2(float(spread))
+    X = synth.f32_to_bf16_bits(x.astype(np.float32))
+    bp, rot = _blockperm_inputs(lrq, K, B, M)
+    z = oracle.rotate_blockperm(oracle.bf16_bits_to_f64(X), oracle.bf16_bits_to_f64(bp[0]), np.arange(K),
+                                np.broadcast_to(np.eye(B), (K // B, B, B)))
+    share = float(((z.view(np.uint64) & np.uint64(0xff)) != 0).mean())
+    print(f"share of z with more than 45 bits: {share:.2e}", flush=True)
+    import torch
+    ws = torch.zeros(lrq.ars_workspace_bytes(M, K, rot, 8), dtype=torch.uint8, device="cuda")
+    q, s = lrq.ars_rotate_quant(bf16_to_dev(X), rot, 8, workspace=ws)
+    u = ws[:M * K * 8].view(torch.float64).view(M, K).cpu().numpy()
+    assert np.array_equal(u, oracle.rotate_blockperm(oracle.bf16_bits_to_f64(X), oracle.bf16_bits_to_f64(bp[0]), bp[1],
+                                                     oracle.bf16_bits_to_f64(bp[2])))
+    q_ref, s_ref = oracle.ars_rotate_quant(X, 8, "blockperm", blockperm=bp)
+    assert np.array_equal(q.cpu().numpy(), q_ref) and np.array_equal(s.cpu().numpy(), s_ref)
+
+
 def test_blockperm_qlinear_against_oracle(lrq):
     import torch
     M, K, N, B = 150, 1152, 320, 128
