@@ -617,12 +617,15 @@ __device__ __forceinline__ Pieces load_pieces(const unsigned char* const (&xp)[8
 }
 
 // All 64 lanes must call this together (lanes without an element pass any valid row / col and ignore the result).
-// K % 64 == 0.  lds: this wave's 2 * XE_BUF bytes.
+// K % 64 == 0.  lds: this wave's 2 * XE_BUF bytes (XE_BUF with XDIRECT).
 // XDIRECT: every lane reads its own x row itself, 16 bytes at a time, and only the R columns go through LDS - for waves whose
 // neighbouring lanes share rows (the list of undecided elements keeps a row's entries together, about nine to a row at
 // config 4): lanes with the same address are served by one request, so the cooperative fetch buys nothing for x there
 // and its trip through LDS is half of the kernel's LDS traffic.
-template <bool XDIRECT>
+// AHEAD (1 or 2; 2 needs K % 128 == 0): batches of 64 k in flight.  Two where few waves run (the amax candidates: 65.8 -> 63.9 us
+// at 35100 x 3072), one where many do and registers decide how many (the undecided elements, three waves per SIMD instead of
+// two: 270 -> 257 us).  Either way a wave spends about 50 cycles on a k, most of it converting two operands to fp64.
+template <bool XDIRECT, int AHEAD>
 __device__ __forceinline__ double exact_element_wave(const uint16_t* X, const uint16_t* Rt, int K, int row, int col,
                                                      unsigned char* lds) {
     const int lane = threadIdx.x % kWave;
@@ -637,13 +640,12 @@ __device__ __forceinline__ double exact_element_wave(const uint16_t* X, const ui
         rp[q] = reinterpret_cast<const unsigned char*>(Rt + (size_t)ec * K) + (lane % 8) * 16;
     }
     unsigned char* xs = lds;
-    unsigned char* rs = lds + XE_BUF;
+    unsigned char* rs = XDIRECT ? lds : lds + XE_BUF;
     const int wr = (lane / 8) * XE_ROW + (lane % 8) * 16;        // + 8 q rows for load q
     const int rd = lane * XE_ROW;
     const int nb = K / 64;
     double u = 0.0;
-    Pieces nxt = load_pieces(xp, rp, 0);
-    for (int b = 0; b < nb; ++b) {
+    auto batch = [&](Pieces& nxt, int b) {
         // stage batch b (the previous batch was read into registers before this point)
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
@@ -656,7 +658,7 @@ __device__ __forceinline__ double exact_element_wave(const uint16_t* X, const ui
             for (int i = 0; i < 8; ++i) xv[i] = nxt.x[i];
         }
         wave_lds_sync();
-        nxt = load_pieces(xp, rp, (size_t)(b + 1 < nb ? b + 1 : b) * 128);     // past the end: a harmless re-read
+        nxt = load_pieces(xp, rp, (size_t)(b + AHEAD < nb ? b + AHEAD : b) * 128);     // past the end: a harmless re-read
         asm volatile("" ::: "memory");                   // keeps these loads ahead of the arithmetic below
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -673,6 +675,16 @@ __device__ __forceinline__ double exact_element_wave(const uint16_t* X, const ui
                 u = fma((double)bf16_hi(xv[i][d]), (double)bf16_hi(rv[i][d]), u);
             }
         __builtin_amdgcn_sched_barrier(0);
+    };
+    Pieces p0 = load_pieces(xp, rp, 0);
+    if constexpr (AHEAD == 1) {
+        for (int b = 0; b < nb; ++b) batch(p0, b);
+    } else {
+        Pieces p1 = load_pieces(xp, rp, 128);
+        for (int b = 0; b < nb; b += 2) {
+            batch(p0, b);
+            batch(p1, b + 1);
+        }
     }
     return u;
 }
@@ -696,7 +708,7 @@ __global__ __launch_bounds__(256) void dense_exact_amax_kernel(const uint16_t* X
         col = have ? (int)cidx[((size_t)row * 2 + side) * CAPC + slot] : 0;
     }
     if (__ballot(have) == 0ull) return;                  // nothing in this wave
-    const double u = exact_element_wave<false>(X, Rt, K, row, col, stage + (threadIdx.x / kWave) * 2 * XE_BUF);
+    const double u = exact_element_wave<false, 2>(X, Rt, K, row, col, stage + (threadIdx.x / kWave) * 2 * XE_BUF);
     if (have) {
         if constexpr (ASYM) atomicMax(&amax_bits[2 * (size_t)row + side], okey(side == 0 ? u : -u));
         else atomicMax(&amax_bits[2 * (size_t)row], (unsigned long long)__double_as_longlong(fabs(u)));
@@ -761,57 +773,82 @@ __global__ __launch_bounds__(256) void dense_quant_flag_kernel(const float* __re
     }
 }
 
-// ---- exclusive prefix sum of the per-row counts, offs[0 .. M] (one workgroup of 1024 threads; 16384 counts per pass
-// through LDS so that global reads and writes are coalesced; a thread sums its 16 counts, the sums are scanned inside
-// each wave with lane shifts and the 16 wave totals by every thread itself: three barriers per pass)
+// ---- exclusive prefix sum of the per-row counts, offs[0 .. M] (one workgroup of 1024 threads, bound by the latency of its
+// passes; 16384 counts per pass, 16 neighbouring ones per thread in registers, the next pass's in flight; the threads'
+// sums are scanned inside each wave with lane shifts and the 16 wave totals by every thread itself: one barrier per pass)
+__device__ __forceinline__ void load_counts16(const int* cnt, int at, int M, int (&v)[16]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        int4 d = {0, 0, 0, 0};
+        if (at + 4 * i + 4 <= M) {
+            d = *reinterpret_cast<const int4*>(cnt + at + 4 * i);
+        } else {
+            if (at + 4 * i < M) d.x = cnt[at + 4 * i];
+            if (at + 4 * i + 1 < M) d.y = cnt[at + 4 * i + 1];
+            if (at + 4 * i + 2 < M) d.z = cnt[at + 4 * i + 2];
+        }
+        v[4 * i] = d.x; v[4 * i + 1] = d.y; v[4 * i + 2] = d.z; v[4 * i + 3] = d.w;
+    }
+}
+
 __global__ __launch_bounds__(1024) void dense_scan_counts_kernel(const int* __restrict__ cnt, int M, int* __restrict__ offs) {
-    __shared__ int buf[16384];
-    __shared__ int wave_total[16];
+    __shared__ int wave_total[2][16];
     const int t = threadIdx.x, lane = t % kWave, wv = t / kWave;
-    int carry = 0;
-    for (int base = 0; base < M; base += 16384) {
-        for (int i = t; i < 16384; i += 1024) buf[i] = base + i < M ? cnt[base + i] : 0;
-        __syncthreads();
+    int carry = 0, par = 0, v[16], nxt[16];
+    load_counts16(cnt, t * 16, M, nxt);
+    for (int base = 0; base < M; base += 16384, par ^= 1) {
         int s = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s += buf[t * 16 + i];
+        for (int i = 0; i < 16; ++i) {
+            v[i] = nxt[i];
+            s += v[i];
+        }
+        const int at = base + t * 16;
+        if (base + 16384 < M) load_counts16(cnt, at + 16384, M, nxt);
         int incl = s;                                   // inclusive scan of s over the wave
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
-            const int v = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += v;
+            const int u = __shfl_up(incl, o, kWave);
+            if (lane >= o) incl += u;
         }
-        if (lane == kWave - 1) wave_total[wv] = incl;
+        if (lane == kWave - 1) wave_total[par][wv] = incl;
         __syncthreads();
         int before = 0, all = 0;                        // totals of the waves before this one, and of all 16
 #pragma unroll
         for (int w = 0; w < 16; ++w) {
-            const int v = wave_total[w];
-            if (w < wv) before += v;
-            all += v;
+            const int u = wave_total[par][w];
+            if (w < wv) before += u;
+            all += u;
         }
         int run = carry + before + incl - s;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int c = buf[t * 16 + i];
-            buf[t * 16 + i] = run;
+            const int c = v[i];
+            v[i] = run;
             run += c;
         }
         carry += all;
-        __syncthreads();
-        for (int i = t; i < 16384; i += 1024)
-            if (base + i < M) offs[base + i] = buf[i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (at + 4 * i + 4 <= M) {
+                *reinterpret_cast<int4*>(offs + at + 4 * i) = make_int4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+            } else {
+#pragma unroll
+                for (int x = 0; x < 3; ++x)
+                    if (at + 4 * i + x < M) offs[at + 4 * i + x] = v[4 * i + x];
+            }
+        }
     }
     if (t == 0) offs[M] = carry;
 }
 
 // ---- undecided elements: exact value, exact code.  Thread i takes list entry i (row found by bisection of offs).
 template <bool ASYM>
-__global__ __launch_bounds__(256) void dense_exact_codes_kernel(const uint16_t* X, const uint16_t* Rt, int M, int K, double qmax,
+__global__ __launch_bounds__(256, 3) void dense_exact_codes_kernel(const uint16_t* X, const uint16_t* Rt, int M, int K, double qmax,
                                                                 const int* __restrict__ offs, const uint16_t* __restrict__ fidx,
                                                                 int capf, const unsigned long long* __restrict__ amax_bits,
                                                                 int8_t* __restrict__ q) {
-    __shared__ __attribute__((aligned(16))) unsigned char stage[4 * 2 * XE_BUF];
+    __shared__ __attribute__((aligned(16))) unsigned char stage[4 * XE_BUF];
     const int total = offs[M];
     const int lane = threadIdx.x % kWave;
     for (int base = blockIdx.x * 256 + (threadIdx.x - lane); base < total; base += gridDim.x * 256) {     // wave-uniform
@@ -827,7 +864,7 @@ __global__ __launch_bounds__(256) void dense_exact_codes_kernel(const uint16_t* 
             row = lo;
             col = (int)fidx[(size_t)row * capf + (i - offs[row])];
         }
-        const double u = exact_element_wave<true>(X, Rt, K, row, col, stage + (threadIdx.x / kWave) * 2 * XE_BUF);
+        const double u = exact_element_wave<true, 1>(X, Rt, K, row, col, stage + (threadIdx.x / kWave) * XE_BUF);
         if (have) {
             const RowQuant rq = row_quant<ASYM>(amax_bits[2 * (size_t)row], amax_bits[2 * (size_t)row + 1], qmax);
             q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
@@ -835,51 +872,57 @@ __global__ __launch_bounds__(256) void dense_exact_codes_kernel(const uint16_t* 
     }
 }
 
-// ---- rows recomputed as a whole (one workgroup per row, rows with mode == 0 leave at once): every column's chain,
-// twice - once for the maximum (zero-point form: maximum and minimum), once for the codes - with the row of x in LDS; R
+// ---- rows recomputed as a whole (a workgroup looks at RPW rows, usually to find that none is marked; one row each took twice
+// as long over it): every column's chain, twice - once for the maximum (zero-point form: maximum and minimum), once for the codes - with the row of x in LDS; R
 // is read row by row, coalesced.
+constexpr int RPW = 8;
 template <bool ASYM>
 __global__ __launch_bounds__(256) void dense_exact_rows_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ R,
-                                                               int K, double qmax, const int* __restrict__ mode,
+                                                               int M, int K, double qmax, const int* __restrict__ mode,
                                                                int8_t* __restrict__ q, float* __restrict__ scale,
                                                                int32_t* __restrict__ zero) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const int row = blockIdx.x, t = threadIdx.x;
-    if (!mode[row]) return;
-    uint16_t* xr = reinterpret_cast<uint16_t*>(lds_raw);
-    double* red = reinterpret_cast<double*>(lds_raw + (((size_t)K * 2 + 15) & ~(size_t)15));
-    for (int k = t; k < K; k += 256) xr[k] = X[(size_t)row * K + k];
-    __syncthreads();
-    RowQuant rq = {};
-    for (int pass = 0; pass < 2; ++pass) {
-        double mx = ASYM ? -INFINITY : 0.0, mn = -INFINITY;      // mn: maximum of -u
-        for (int col = t; col < K; col += 256) {
-            const uint16_t* r = R + col;
-            double u = 0.0;
-            for (int k = 0; k < K; ++k)
-                u = fma((double)__uint_as_float((unsigned)xr[k] << 16), (double)__uint_as_float((unsigned)r[(size_t)k * K] << 16), u);
+    const int t = threadIdx.x, first = blockIdx.x * RPW;
+    const bool marked = t % kWave < RPW && first + t % kWave < M && mode[first + t % kWave] != 0;
+    unsigned long long todo = __ballot(marked);          // the same in every wave
+    for (; todo; todo &= todo - 1) {
+        const int row = first + __ffsll((long long)todo) - 1;
+        __syncthreads();                                     // the previous row's x and maxima have been read
+        uint16_t* xr = reinterpret_cast<uint16_t*>(lds_raw);
+        double* red = reinterpret_cast<double*>(lds_raw + (((size_t)K * 2 + 15) & ~(size_t)15));
+        for (int k = t; k < K; k += 256) xr[k] = X[(size_t)row * K + k];
+        __syncthreads();
+        RowQuant rq = {};
+        for (int pass = 0; pass < 2; ++pass) {
+            double mx = ASYM ? -INFINITY : 0.0, mn = -INFINITY;      // mn: maximum of -u
+            for (int col = t; col < K; col += 256) {
+                const uint16_t* r = R + col;
+                double u = 0.0;
+                for (int k = 0; k < K; ++k)
+                    u = fma((double)__uint_as_float((unsigned)xr[k] << 16), (double)__uint_as_float((unsigned)r[(size_t)k * K] << 16), u);
+                if (pass == 0) {
+                    mx = fmax(mx, ASYM ? u : fabs(u));
+                    if (ASYM) mn = fmax(mn, -u);
+                } else {
+                    q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
+                }
+            }
             if (pass == 0) {
-                mx = fmax(mx, ASYM ? u : fabs(u));
-                if (ASYM) mn = fmax(mn, -u);
-            } else {
-                q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
-            }
-        }
-        if (pass == 0) {
 #pragma unroll
-            for (int o = kWave / 2; o > 0; o >>= 1) {
-                mx = fmax(mx, __shfl_xor(mx, o, kWave));
-                if (ASYM) mn = fmax(mn, __shfl_xor(mn, o, kWave));
-            }
-            if (t % kWave == 0) { red[t / kWave] = mx; red[4 + t / kWave] = mn; }
-            __syncthreads();
-            const double vmax = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-            const double nmin = fmax(fmax(red[4], red[5]), fmax(red[6], red[7]));
-            rq = ASYM ? row_quant<true>(okey(vmax), okey(nmin), qmax)
-                      : row_quant<false>((unsigned long long)__double_as_longlong(vmax), 0ull, qmax);
-            if (t == 0) {
-                scale[row] = rq.scale;
-                if (ASYM) zero[row] = rq.izero;
+                for (int o = kWave / 2; o > 0; o >>= 1) {
+                    mx = fmax(mx, __shfl_xor(mx, o, kWave));
+                    if (ASYM) mn = fmax(mn, __shfl_xor(mn, o, kWave));
+                }
+                if (t % kWave == 0) { red[t / kWave] = mx; red[4 + t / kWave] = mn; }
+                __syncthreads();
+                const double vmax = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+                const double nmin = fmax(fmax(red[4], red[5]), fmax(red[6], red[7]));
+                rq = ASYM ? row_quant<true>(okey(vmax), okey(nmin), qmax)
+                          : row_quant<false>((unsigned long long)__double_as_longlong(vmax), 0ull, qmax);
+                if (t == 0) {
+                    scale[row] = rq.scale;
+                    if (ASYM) zero[row] = rq.izero;
+                }
             }
         }
     }
@@ -990,7 +1033,8 @@ hipError_t launch_dense_fast(hipStream_t st, const uint16_t* X, const uint16_t* 
     hipLaunchKernelGGL(dense_scan_counts_kernel, dim3(1), dim3(1024), 0, st, fcount, M, foffs);
     hipLaunchKernelGGL(dense_exact_codes_kernel<ASYM>, dim3(2048), dim3(256), 0, st, X, Rt, M, K, qmax, foffs, fidx, L.capf, amax, q);
     const size_t rows_lds = (((size_t)K * 2 + 15) & ~(size_t)15) + 8 * sizeof(double);
-    hipLaunchKernelGGL(dense_exact_rows_kernel<ASYM>, dim3(M), dim3(256), rows_lds, st, X, R, K, qmax, mode, q, scale, zero);
+    hipLaunchKernelGGL(dense_exact_rows_kernel<ASYM>, dim3((M + RPW - 1) / RPW), dim3(256), rows_lds, st, X, R, M, K, qmax, mode,
+                       q, scale, zero);
     return hipGetLastError();
 }
 }  // namespace
