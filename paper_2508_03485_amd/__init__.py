@@ -145,9 +145,19 @@ def _check(status: int, where: str) -> None:
         raise LrqError(status, where)
 
 
+_current = None     # torch's functions (raw stream of a device, current device)
+
+
 def _stream() -> int:
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+    """Handle of the current stream of the current device, without the Stream object that torch.cuda.current_stream()
+    builds around it on every call (a tenth of a small layer's host time)."""
+    global _current
+    if _current is None:
+        import torch
+        torch.cuda.current_stream()         # initialises the device
+        _current = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+    raw_stream, device = _current
+    return raw_stream(device())
 
 
 def _ptr(t) -> Optional[int]:
@@ -424,7 +434,11 @@ def ars_dense_diagnostics(workspace, M: int, K: int):
 
 def _out_code(dtype) -> int:
     import torch
-    return {torch.bfloat16: LRQ_OUT_BF16, torch.float32: LRQ_OUT_FP32}[dtype]
+    if dtype is torch.bfloat16:
+        return LRQ_OUT_BF16
+    if dtype is torch.float32:
+        return LRQ_OUT_FP32
+    raise KeyError(dtype)
 
 
 def qlinear(X, rot: Rotation, act_bits: int, w: TLQWeight, bias=None, out_dtype=None, out=None, workspace=None,
@@ -438,14 +452,15 @@ def qlinear(X, rot: Rotation, act_bits: int, w: TLQWeight, bias=None, out_dtype=
     out_dtype = out_dtype or (out.dtype if out is not None else torch.bfloat16)
     if out is None:
         out = torch.empty((M, w.N), dtype=out_dtype, device=X.device)
-    r, cs = rot.c_struct(), w.c_struct()
-    size_fn = lib().lrq_workspace_bytes_asym if asym else lib().lrq_workspace_bytes
+    L, r, cs = lib(), ctypes.byref(rot.c_struct()), ctypes.byref(w.c_struct())
     if workspace is None:
-        workspace = torch.empty(size_fn(M, w.N, K, ctypes.byref(r), act_bits), dtype=torch.uint8, device=X.device)
-    name = "lrq_qlinear_asym" if asym else ("lrq_qlinear_levels" if levels else "lrq_qlinear")
-    st = getattr(lib(), name)(_stream(), _ptr(X), M, K, ctypes.byref(r), act_bits, ctypes.byref(cs), _ptr(bias),
-                              _out_code(out_dtype), _ptr(out), _ptr(workspace), workspace.numel())
-    _check(st, name)
+        size_fn = L.lrq_workspace_bytes_asym if asym else L.lrq_workspace_bytes
+        workspace = torch.empty(size_fn(M, w.N, K, r, act_bits), dtype=torch.uint8, device=X.device)
+    call = L.lrq_qlinear_asym if asym else (L.lrq_qlinear_levels if levels else L.lrq_qlinear)
+    st = call(_stream(), X.data_ptr(), M, K, r, act_bits, cs, None if bias is None else bias.data_ptr(), _out_code(out_dtype),
+              out.data_ptr(), workspace.data_ptr(), workspace.numel())
+    if st != LRQ_OK:
+        _check(st, call.__name__)
     return out
 
 
