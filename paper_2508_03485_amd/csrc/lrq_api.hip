@@ -113,7 +113,7 @@ ArsWs ars_layout(int M, int K, const lrq_rotation* rot) {
             if (fast > l.total) l.total = fast;
         }
     }
-    if (rot && rot->kind == LRQ_ROT_BLOCKPERM) {       // U doubles (first Z = x.R1, finally u), then Zp doubles
+    if (rot && rot->kind == LRQ_ROT_BLOCKPERM) {       // U doubles (u), then Zp doubles (Z = x.R1)
         l.zp_off = round256((size_t)M * K * sizeof(double));
         l.total = l.zp_off + round256((size_t)M * K * sizeof(double));
     }
