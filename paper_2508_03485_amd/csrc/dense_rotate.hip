@@ -624,7 +624,8 @@ __device__ __forceinline__ Pieces load_pieces(const unsigned char* const (&xp)[8
 // and its trip through LDS is half of the kernel's LDS traffic.
 // AHEAD (1 or 2; 2 needs K % 128 == 0): batches of 64 k in flight.  Two where few waves run (the amax candidates: 65.8 -> 63.9 us
 // at 35100 x 3072), one where many do and registers decide how many (the undecided elements, three waves per SIMD instead of
-// two: 270 -> 257 us).  Either way a wave spends about 50 cycles on a k, most of it converting two operands to fp64.
+// two: 270 -> 257 us).  Either way a wave spends about 50 cycles on a k; products formed in fp32
+// (exact in range, one conversion per term instead of two) measured the same, so the conversions are not what it waits for.
 template <bool XDIRECT, int AHEAD>
 __device__ __forceinline__ double exact_element_wave(const uint16_t* X, const uint16_t* Rt, int K, int row, int col,
                                                      unsigned char* lds) {
