@@ -164,8 +164,8 @@ __device__ void search_clip(const float* __restrict__ w, const double* __restric
 #pragma unroll
                     for (int e = 0; e < NE; ++e) {
                         const double wk = (double)wv[e];
-                        if (wk != 0.0) {
-                            const bool neg = wk < 0.0;
+                        const bool neg = wk < 0.0;
+                        if (neg || wk > 0.0) {                    // a NaN weight belongs to neither sign
                             const double s = neg ? cn.s : cp.s, z = neg ? cn.z : cp.z, lo = neg ? 1.0 : 0.0;
                             const double d = exp2(s * (level_index(el[e], s, z, lo, lo + (double)(half - 1)) + z)) - fabs(wk);
                             if (neg) en = en + d * d; else ep = ep + d * d;

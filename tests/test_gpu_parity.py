@@ -490,6 +490,21 @@ def test_tlq_search_every_row_length(lrq, K, bits):
     _check_weight(lrq, W, bits, 7, GRID[:9], GRID[:12])
 
 
+@pytest.mark.parametrize("K,bits", [(768, 4), (6208, 3)])
+def test_tlq_weights_that_are_not_finite(lrq, K, bits):
+    """A NaN weight belongs to neither sign: it stays out of the extrema and of both objectives, takes code 0 and leaves the rest of
+    its channel as it was.  An infinite one makes every candidate of its sign NaN: the channel keeps the factor one there.
+    A row that stays in registers and one that goes through LDS."""
+    print(f"case tlq non-finite K={K} b={bits}", flush=True)
+    W = synth.make_weights(5, K, (942, K, bits))
+    W[0, [3, 200, K - 1]] = np.nan
+    W[1, : K // 2] = np.nan
+    W[2, 5], W[2, 6] = np.inf, np.nan
+    W[3, 7], W[3, 8] = -np.inf, -np.nan
+    with np.errstate(all="ignore"):
+        _check_weight(lrq, W, bits, 7, GRID[:9], GRID[:12])
+
+
 def test_tlq_search_with_quotients_past_the_reciprocal_range(lrq):
     """Two neighbouring fp32 magnitudes per sign: s is about 2e-8 and log2|w| / s about 3e8, where the search divides instead of
     multiplying by 1 / s.  s itself is the difference of two nearly equal logarithms from two math libraries, so only what
