@@ -782,65 +782,59 @@ __global__ __launch_bounds__(256, 2) void blockdiag_rotate_mfma_f64_kernel(const
         }
 }
 
-// The two block-diagonal products of the structured rotation on the fp64 matrix cores, 64 x 128 output tiles:
-// dst[:, block g] = left[:, block g] . R_g with R bf16 [K/B, B, B].
-// GATHER = false: left = bf16 x (times the fp32 pre-scale): every product is exact in fp64, so the matrix instruction's fused
-//   multiply-adds (v_mfma_f64_16x16x4_f64 takes its four k in ascending order) give the plain ascending-k sum.
-// GATHER = true: left[:, j] = z[:, perm[j]] with fp64 z.  The definition rounds every product and every sum separately.  A product
-//   with a bf16 value is exact, and the fused form the same, when z has at most 45 significant bits, i.e. when the last 8 bits of
-//   its significand are zero.  The z of ordinary activations have 25 to 40 bits (they are sums of 16-bit products of similar
-//   exponents; 6 in 100000 have more than 45), so a wave looks at the z of every matrix step (16 rows x 4 k).  For the rows with
-//   one that does not pass, products rounded on their own are added through matrix instructions with an identity operand, so
-//   that the accumulators have one layout: 16 times the step's time.
-//   The first product leaves the number of such z of each of its tiles in wide (K / 128 ints at the head of the row tile's q
-//   rows, which the quantizer overwrites later); row tiles with more than one in 1024 are left to
-//   blockdiag_rotate_seq_f64_kernel, which computes all of them with separate roundings (there a pre-scale ends up: its fp32
-//   factors fill the significands).
+// The two block-diagonal products of the structured rotation, dst[:, block g] = left[:, block g] . R_g with R bf16 [K/B, B, B],
+// in tiles of 64 rows x TN columns.
+// First product (GATHER = false): left = bf16 x (times the fp32 pre-scale): every product is exact in fp64, so the matrix
+//   instruction's fused multiply-adds (v_mfma_f64_16x16x4_f64 takes its four k in ascending order) give the plain ascending-k sum.
+// Second product (GATHER = true): left[:, j] = z[:, perm[j]] with fp64 z.  The definition rounds every product and every sum
+//   separately.  A product with a bf16 value is exact, and the fused form the same, when z has at most 45 significant bits, i.e. when
+//   the last 8 bits of its significand are zero.  The z of ordinary activations have 25 to 40 bits (they are sums of 16-bit
+//   products of similar exponents; at B = 128 one in 100000 has more than 45), so a wave looks at the z of every matrix step (16
+//   rows x 4 k).  For the rows with one that does not pass, products rounded on their own are added through matrix
+//   instructions with an identity operand, so that the accumulators have one layout: 16 times the step's time.
+//   The first product marks the channels of a row tile that hold such a z (a byte each, at the head of the tile's q rows, which
+//   the quantizer overwrites later).  A workgroup counts the steps its own channels would redo and takes the separately rounded
+//   form on the vector units (blockdiag_seq_tile) where they are more than one in kRedoShare; there also goes everything with a
+//   pre-scale, whose fp32 factors fill the significands.
 //   The channels are gathered straight from z (indices clamped into [0, K): a malformed perm gives wrong values, never an
-//   out-of-range access); the column tiles of a row tile run on one XCD, whose L2 serves the 16 values of a line that
-//   different column tiles need.
-// Bound by fp64 matrix issue (46 us per product at 4608 x 3072, B = 128) and the passes over z, 24 us each: 76 us for the first
-// product (85 with 128 x 128 tiles, too few for the chip), 126 + 5 us for the second (154 on the vector units after a
-// permutation pass of 38).
-// LDS rows: 34 doubles (left) and 288 bytes (R), which put the 32 lanes of a fragment read on distinct banks.
-__device__ __forceinline__ bool tile_is_wide(const int8_t* wide, int row0, int K) {      // the same answer in every lane
-    const int* c = reinterpret_cast<const int*>(wide + (size_t)row0 * K);
-    int n = 0;
-    for (int i = threadIdx.x % kWave; i < K / 128; i += kWave) n += c[i];
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) n += __shfl_xor(n, o, kWave);
-    return n > K / 16;                               // 64 K / 1024
+//   out-of-range access).
+// LDS rows: 34 doubles (left) and 2 TN + 32 bytes (R), which put the 32 lanes of a fragment read on distinct banks.
+constexpr int BT = 64;                              // rows of a tile
+constexpr int BKS = 32, BLS = BKS + 2;              // k per stage of the matrix form, doubles per LDS row of its left tile
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+template <int TN>
+constexpr int kBlockLds = 2 * BT * BLS * 8 + 2 * BKS * (2 * TN + 32);
+
+// Tiles in row-major order, a contiguous range to each of the 8 XCDs (workgroup ids are dealt to them round-robin): the column
+// tiles of a row tile share an L2, which serves the 16 values of a line that different column tiles need, and a few tiles
+// spread over all XCDs.  Grid: tiles rounded up to a multiple of 8; -1: no tile.
+__device__ __forceinline__ int xcd_tile(int tiles) {
+    const int id = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    return id < tiles ? id : -1;
 }
 
-template <bool GATHER>
-__global__ __launch_bounds__(256, 3) void blockdiag_stage_kernel(const void* __restrict__ src, const int32_t* __restrict__ perm,
-                                                                 const uint16_t* __restrict__ R, int M, int K, int B,
-                                                                 double* __restrict__ dst, const float* __restrict__ ps, int tiles_m,
-                                                                 int8_t* __restrict__ wide) {
-    constexpr int KS = 32, TM = 64, TN = 128;
-    constexpr int LS = KS + 2, RS = 288;            // row strides: doubles, bytes
-    __shared__ __attribute__((aligned(16))) double Ls[2][TM * LS];
-    __shared__ __attribute__((aligned(16))) unsigned char Rs[2][KS * RS];
+template <bool GATHER, int TN>
+__device__ __forceinline__ void blockdiag_mfma_tile(const void* __restrict__ src, const int32_t* __restrict__ perm,
+                                                    const uint16_t* __restrict__ R, int M, int K, int B, double* __restrict__ dst,
+                                                    const float* __restrict__ ps, int row0, int col0, unsigned char* smem,
+                                                    uint8_t* __restrict__ marks) {
+    constexpr int RS = 2 * TN + 32, NJ = TN / 32, RV = TN / 64;
+    double* Ls = reinterpret_cast<double*>(smem);                   // [2][BT * BLS]
+    unsigned char* Rs = smem + 2 * BT * BLS * 8;                    // [2][BKS * RS]
     const int t = threadIdx.x, lane = t % 64, wv = t / 64;
-    const int wm = wv / 2, wn = wv % 2;
-    // workgroup ids are dealt round-robin to the 8 XCDs: XCD x takes the row tiles x, x + 8, ...
-    const int tiles_n = K / TN, seq = blockIdx.x / 8;
-    const int tm = seq / tiles_n * 8 + blockIdx.x % 8;
-    if (tm >= tiles_m) return;
-    const int row0 = tm * TM, col0 = seq % tiles_n * TN;
-    if (GATHER && tile_is_wide(wide, row0, K)) return;
+    const int wm = wv / 2, wn = wv % 2;                             // a wave owns 32 rows x TN / 2 columns
     const int g = col0 / B, kbase = g * B, cb = col0 - kbase;
-    v4d acc[2][4];
+    v4d acc[2][NJ];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+        for (int j = 0; j < NJ; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
     const int lr = t / 4, lk = (t % 4) * 8;         // left tile: 8 values per thread
-    const int rk = t / 16, rc = (t % 16) * 8;       // R tile: rows rk and rk + 16, 8 bf16 each
+    const int rk = t / (TN / 8), rc = (t % (TN / 8)) * 8;     // R tile: 8 bf16 of rows rk, rk + 32 / RV, ...
     const size_t lrow = (size_t)(row0 + lr < M ? row0 + lr : M - 1) * K;
     const uint16_t* rsrc = R + (size_t)g * B * B + (size_t)rk * B + cb + rc;
     double ln[8];                                   // the stage in flight
-    uint4 xn, rn0, rn1;
+    v4u xn, rn[RV];
     int4 pn0 = {0, 0, 0, 0}, pn1 = {0, 0, 0, 0};    // indices of the stage after it
     auto load_perm = [&](int k0) {
         if constexpr (GATHER) {
@@ -856,14 +850,14 @@ __global__ __launch_bounds__(256, 3) void blockdiag_stage_kernel(const void* __r
 #pragma unroll
             for (int i = 0; i < 8; ++i) ln[i] = z[min(max(pi[i], 0), K - 1)];
         } else {
-            xn = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src) + lrow + kbase + lk + k0);
+            xn = *reinterpret_cast<const v4u*>(static_cast<const uint16_t*>(src) + lrow + kbase + lk + k0);
         }
-        rn0 = *reinterpret_cast<const uint4*>(rsrc + (size_t)k0 * B);
-        rn1 = *reinterpret_cast<const uint4*>(rsrc + (size_t)(k0 + 16) * B);
+#pragma unroll
+        for (int v = 0; v < RV; ++v) rn[v] = *reinterpret_cast<const v4u*>(rsrc + (size_t)(k0 + v * (BKS / RV)) * B);
     };
     auto stage = [&](int buf, int k0) {
         if constexpr (!GATHER) {
-            const unsigned w[4] = {xn.x, xn.y, xn.z, xn.w};
+            const unsigned w[4] = {xn[0], xn[1], xn[2], xn[3]};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 ln[2 * i] = (double)__uint_as_float(w[i] << 16);
@@ -871,33 +865,33 @@ __global__ __launch_bounds__(256, 3) void blockdiag_stage_kernel(const void* __r
             }
             if (ps) prescale8(ps + kbase + lk + k0, ln);
         }
-        double2* ld = reinterpret_cast<double2*>(&Ls[buf][lr * LS + lk]);
+        double2* ld = reinterpret_cast<double2*>(&Ls[buf * BT * BLS + lr * BLS + lk]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) ld[i] = make_double2(ln[2 * i], ln[2 * i + 1]);
-        *reinterpret_cast<uint4*>(&Rs[buf][rk * RS + rc * 2]) = rn0;
-        *reinterpret_cast<uint4*>(&Rs[buf][(rk + 16) * RS + rc * 2]) = rn1;
+#pragma unroll
+        for (int v = 0; v < RV; ++v) *reinterpret_cast<v4u*>(&Rs[buf * BKS * RS + (rk + v * (BKS / RV)) * RS + rc * 2]) = rn[v];
     };
     load_perm(0);
     load(0);
-    load_perm(KS);                                  // B >= 128: there is a second stage
+    load_perm(BKS);                                 // B >= 128: there is a second stage
     stage(0, 0);
     __syncthreads();
     int cur = 0;
-    for (int k0 = 0; k0 < B; k0 += KS, cur ^= 1) {
-        const bool more = k0 + KS < B;
+    for (int k0 = 0; k0 < B; k0 += BKS, cur ^= 1) {
+        const bool more = k0 + BKS < B;
         if (more) {
-            load(k0 + KS);
-            if (k0 + 2 * KS < B) load_perm(k0 + 2 * KS);
+            load(k0 + BKS);
+            if (k0 + 2 * BKS < B) load_perm(k0 + 2 * BKS);
         }
-        const double* la = &Ls[cur][(wm * 32 + lane % 16) * LS + lane / 16];
-        const unsigned char* rb = &Rs[cur][(lane / 16) * RS + (wn * 64 + lane % 16) * 2];
+        const double* la = &Ls[cur * BT * BLS + (wm * 32 + lane % 16) * BLS + lane / 16];
+        const unsigned char* rb = &Rs[cur * BKS * RS + (lane / 16) * RS + (wn * (TN / 2) + lane % 16) * 2];
 #pragma unroll 2
-        for (int ks = 0; ks < KS / 4; ++ks) {
-            double a[2], b[4];
+        for (int ks = 0; ks < BKS / 4; ++ks) {
+            double a[2], b[NJ];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = la[i * 16 * LS + ks * 4];
+            for (int i = 0; i < 2; ++i) a[i] = la[i * 16 * BLS + ks * 4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < NJ; ++j)
                 b[j] = (double)__uint_as_float((unsigned)*reinterpret_cast<const uint16_t*>(rb + ks * 4 * RS + j * 32) << 16);
             unsigned long long low[2] = {0, 0};
             if constexpr (GATHER) {
@@ -918,7 +912,7 @@ __global__ __launch_bounds__(256, 3) void blockdiag_stage_kernel(const void* __r
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < NJ; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
             if constexpr (GATHER) {
                 if (low[0] | low[1]) {
@@ -927,15 +921,15 @@ __global__ __launch_bounds__(256, 3) void blockdiag_stage_kernel(const void* __r
                         double z[2];
 #pragma unroll
                         for (int i = 0; i < 2; ++i)
-                            z[i] = (low[i] >> (lane % 16)) & 1 ? Ls[cur][(wm * 32 + i * 16 + lane % 16) * LS + kk] : 0.0;
+                            z[i] = (low[i] >> (lane % 16)) & 1 ? Ls[cur * BT * BLS + (wm * 32 + i * 16 + lane % 16) * BLS + kk] : 0.0;
 #pragma unroll 1
                         for (int s = 0; s < 4; ++s) {      // output columns 4 s + [0, 4) of every column tile
                             const int c = 4 * s + lane / 16;
                             const double one = lane % 16 == c ? 1.0 : 0.0;
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) {
+                            for (int j = 0; j < NJ; ++j) {
                                 const double r = (double)__uint_as_float((unsigned)*reinterpret_cast<const uint16_t*>(
-                                                                             &Rs[cur][kk * RS + (wn * 64 + j * 16 + c) * 2]) << 16);
+                                                     &Rs[cur * BKS * RS + kk * RS + (wn * (TN / 2) + j * 16 + c) * 2]) << 16);
 #pragma unroll
                                 for (int i = 0; i < 2; ++i)
                                     acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(__dmul_rn(z[i], r), one, acc[i][j], 0, 0, 0);
@@ -945,10 +939,10 @@ __global__ __launch_bounds__(256, 3) void blockdiag_stage_kernel(const void* __r
                 }
             }
         }
-        if (more) stage(cur ^ 1, k0 + KS);          // its last readers passed the barrier that closed the previous stage
+        if (more) stage(cur ^ 1, k0 + BKS);         // its last readers passed the barrier that closed the previous stage
         __syncthreads();
     }
-    int n = 0;
+    bool wide[NJ] = {};
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -956,70 +950,72 @@ __global__ __launch_bounds__(256, 3) void blockdiag_stage_kernel(const void* __r
             const int row = row0 + wm * 32 + i * 16 + 4 * r + lane / 16;
             if (row < M) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < NJ; ++j) {
                     const double u = acc[i][j][r];
-                    dst[(size_t)row * K + col0 + wn * 64 + j * 16 + lane % 16] = u;
-                    if (!GATHER) n += (__double2loint(u) & 0xff) != 0;
+                    dst[(size_t)row * K + col0 + wn * (TN / 2) + j * 16 + lane % 16] = u;
+                    if (!GATHER) wide[j] |= (__double2loint(u) & 0xff) != 0;
                 }
             }
         }
     if constexpr (!GATHER) {
+        if (marks) {
+            uint8_t* of = Rs;                       // [2][TN]: per half of the rows; the last stage's barrier is behind every reader
 #pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1) n += __shfl_xor(n, o, kWave);
-        int* sum = reinterpret_cast<int*>(Rs[0]);    // the last stage's barrier is behind every reader
-        if (lane == 0) sum[wv] = n;
-        __syncthreads();
-        if (t == 0) reinterpret_cast<int*>(wide + (size_t)row0 * K)[col0 / TN] = sum[0] + sum[1] + sum[2] + sum[3];
+            for (int j = 0; j < NJ; ++j) {
+                unsigned long long m = __ballot(wide[j]);
+                m |= m >> 32; m |= m >> 16;
+                if (lane < 16) of[wm * TN + wn * (TN / 2) + j * 16 + lane] = (uint8_t)((m >> lane) & 1);
+            }
+            __syncthreads();
+            if (t < TN) marks[(size_t)row0 * K + col0 + t] = of[t] | of[TN + t];
+        }
     }
 }
 
-// The second product with separate roundings throughout, for the row tiles that blockdiag_stage_kernel<true> leaves (wide, see
-// there; nullptr: all of them): bound by fp64 vector issue.  64 x 128 output tile per workgroup, 8 x 4 outputs per thread
-// (96 bytes from LDS per 64 operations; with 4 x 4 outputs LDS takes as long as the arithmetic), 16 k per stage in two LDS
-// buffers, the next stage in flight, channels gathered as above: 172 us at 4608 x 3072, B = 128.
-constexpr int SC = 128;  // output columns of one workgroup
-__global__ __launch_bounds__(256) void blockdiag_rotate_seq_f64_kernel(const double* __restrict__ src,
-                                                                        const int32_t* __restrict__ perm,
-                                                                        const uint16_t* __restrict__ R, int M, int K, int B,
-                                                                        double* __restrict__ dst, int tiles_m,
-                                                                        const int8_t* __restrict__ wide) {
-    __shared__ __attribute__((aligned(16))) double Xs[2][DK][DT + 2];
-    __shared__ __attribute__((aligned(16))) double Rs[2][DK][SC];
+// The second product's tile with separate roundings throughout, on the fp64 vector units.  TN / 16 x 4 outputs per thread, 16 k per
+// stage in two LDS buffers, the next stage in flight, channels gathered as above.
+template <int TN>
+__device__ __forceinline__ void blockdiag_seq_tile(const double* __restrict__ src, const int32_t* __restrict__ perm,
+                                                   const uint16_t* __restrict__ R, int M, int K, int B, double* __restrict__ dst,
+                                                   int row0, int col0, unsigned char* smem) {
+    constexpr int RPT = TN / 16, TX = TN / 4, E = TN / 16, XS = BT + 2;
+    static_assert(2 * DK * (XS + TN) * 8 <= kBlockLds<TN>, "both forms use one LDS allocation");
+    double* Xs = reinterpret_cast<double*>(smem);                   // [2][DK][XS]
+    double* Rs = Xs + 2 * DK * XS;                                  // [2][DK][TN]
     const int t = threadIdx.x;
-    const int tiles_n = K / SC, seq = blockIdx.x / 8;
-    const int tm = seq / tiles_n * 8 + blockIdx.x % 8;
-    if (tm >= tiles_m) return;
-    const int row0 = tm * DT, col0 = seq % tiles_n * SC;
-    if (wide && !tile_is_wide(wide, row0, K)) return;
     const int g = col0 / B, kbase = g * B, cb = col0 - kbase;
-    const int ty = t / 32, tx = t % 32;          // rows 8 ty + [0, 8), columns 2 tx + {0, 1} and 64 + 2 tx + {0, 1}
-    double acc[8][4];
+    const int ty = t / TX, tx = t % TX;          // rows RPT ty + [0, RPT), columns 2 tx + {0, 1} and TN / 2 + 2 tx + {0, 1}
+    double acc[RPT][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < RPT; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
     const int xr = t / 4, xk = (t % 4) * 4;      // src tile: 64 rows x 16 k, 4 doubles per thread
-    const int rk = t / 16, rc = (t % 16) * 8;    // R tile: 16 k x 128 cols, 8 bf16 per thread
+    const int rk = t / 16, rc = (t % 16) * E;    // R tile: 16 k x TN columns, E bf16 per thread
     const int xrow = row0 + xr < M ? row0 + xr : M - 1;
     const double* xsrc = src + (size_t)xrow * K;
     const int32_t* pk = perm + kbase + xk;
     const uint16_t* rsrc = R + (size_t)g * B * B + (size_t)rk * B + cb + rc;
     auto clampk = [&](int k) { return min(max(k, 0), K - 1); };
     double xn[4];
-    uint4 rn;
+    unsigned rn[E / 2];
     auto load = [&](int k0) {
         const int4 p = *reinterpret_cast<const int4*>(pk + k0);
         xn[0] = xsrc[clampk(p.x)]; xn[1] = xsrc[clampk(p.y)]; xn[2] = xsrc[clampk(p.z)]; xn[3] = xsrc[clampk(p.w)];
-        rn = *reinterpret_cast<const uint4*>(rsrc + (size_t)k0 * B);
+        const uint2* r = reinterpret_cast<const uint2*>(rsrc + (size_t)k0 * B);
+#pragma unroll
+        for (int i = 0; i < E / 4; ++i) {
+            const uint2 v = r[i];
+            rn[2 * i] = v.x; rn[2 * i + 1] = v.y;
+        }
     };
     auto store = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) Xs[buf][xk + i][xr] = xn[i];
-        const unsigned w[4] = {rn.x, rn.y, rn.z, rn.w};
+        for (int i = 0; i < 4; ++i) Xs[(buf * DK + xk + i) * XS + xr] = xn[i];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            *reinterpret_cast<double2*>(&Rs[buf][rk][rc + 2 * i]) =
-                make_double2((double)__uint_as_float(w[i] << 16), (double)__uint_as_float(w[i] & 0xffff0000u));
+        for (int i = 0; i < E / 2; ++i)
+            *reinterpret_cast<double2*>(&Rs[(buf * DK + rk) * TN + rc + 2 * i]) =
+                make_double2((double)__uint_as_float(rn[i] << 16), (double)__uint_as_float(rn[i] & 0xffff0000u));
     };
     load(0);
     store(0);
@@ -1030,17 +1026,17 @@ __global__ __launch_bounds__(256) void blockdiag_rotate_seq_f64_kernel(const dou
         if (more) load(k0 + DK);
 #pragma unroll 4
         for (int kk = 0; kk < DK; ++kk) {
-            double a[8], b[4];
+            double a[RPT], b[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const double2 v = *reinterpret_cast<const double2*>(&Xs[cur][kk][ty * 8 + 2 * i]);
+            for (int i = 0; i < RPT / 2; ++i) {
+                const double2 v = *reinterpret_cast<const double2*>(&Xs[(cur * DK + kk) * XS + ty * RPT + 2 * i]);
                 a[2 * i] = v.x; a[2 * i + 1] = v.y;
             }
-            const double2 b0 = *reinterpret_cast<const double2*>(&Rs[cur][kk][2 * tx]);
-            const double2 b1 = *reinterpret_cast<const double2*>(&Rs[cur][kk][64 + 2 * tx]);
+            const double2 b0 = *reinterpret_cast<const double2*>(&Rs[(cur * DK + kk) * TN + 2 * tx]);
+            const double2 b1 = *reinterpret_cast<const double2*>(&Rs[(cur * DK + kk) * TN + TN / 2 + 2 * tx]);
             b[0] = b0.x; b[1] = b0.y; b[2] = b1.x; b[3] = b1.y;
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < RPT; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc[i][j] = __dadd_rn(acc[i][j], __dmul_rn(a[i], b[j]));
         }
@@ -1048,14 +1044,59 @@ __global__ __launch_bounds__(256) void blockdiag_rotate_seq_f64_kernel(const dou
         __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int r = row0 + ty * 8 + i;
+    for (int i = 0; i < RPT; ++i) {
+        const int r = row0 + ty * RPT + i;
         if (r < M) {
             double* o = dst + (size_t)r * K + col0 + 2 * tx;
             *reinterpret_cast<double2*>(o) = make_double2(acc[i][0], acc[i][1]);
-            *reinterpret_cast<double2*>(o + 64) = make_double2(acc[i][2], acc[i][3]);
+            *reinterpret_cast<double2*>(o + TN / 2) = make_double2(acc[i][2], acc[i][3]);
         }
     }
+}
+
+constexpr int BTN = 128;                            // columns of the first product's tiles
+__global__ __launch_bounds__(256, 3) void blockdiag_first_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ R, int M,
+                                                                 int K, int B, double* __restrict__ Z, const float* __restrict__ ps,
+                                                                 int tiles, uint8_t* __restrict__ marks) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[kBlockLds<BTN>];
+    const int id = xcd_tile(tiles);
+    if (id < 0) return;
+    blockdiag_mfma_tile<false, BTN>(X, nullptr, R, M, K, B, Z, ps, id / (K / BTN) * BT, id % (K / BTN) * BTN, smem, marks);
+}
+
+// marks == nullptr: separate roundings everywhere.
+// Bound by fp64 matrix issue (46 us at 4608 x 3072, B = 128) or vector issue and the gathered reads of z.  Both forms in one
+// kernel, chosen tile by tile, so that the few tiles of either form run beside the others and not after them.
+// kRedoShare: whole rotation at 4608 x 3072, B = 128, us: 220 with nothing redone, 253 with separate roundings everywhere; with 0.9, 3.8 and
+// 9 % of the steps holding a wide z 228 / 248 / 259 with a share of 12, 226 / 247 / 256 with 24, 237 / 251 / 252 with 48.  At B = 512 (a
+// tile has four times the steps): 695 / 755 / 807 us with 12, 723 / 751 / 783 with 24, 746 / 792 / 797 with 48 at 2, 3.5 and 7.5 %.
+constexpr int kRedoShare = 16;
+template <int TN>
+__global__ __launch_bounds__(256, 3) void blockdiag_second_kernel(const double* __restrict__ Z, const int32_t* __restrict__ perm,
+                                                                  const uint16_t* __restrict__ R, int M, int K, int B,
+                                                                  double* __restrict__ U, int tiles, const uint8_t* __restrict__ marks) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[kBlockLds<TN>];
+    const int id = xcd_tile(tiles);
+    if (id < 0) return;
+    const int row0 = id / (K / TN) * BT, col0 = id % (K / TN) * TN;
+    bool seq = marks == nullptr;
+    if (!seq) {
+        const int t = threadIdx.x, kbase = col0 / B * B;
+        int steps = 0;                              // matrix steps of four channels that hold a marked one
+        for (int c0 = 0; c0 < B; c0 += 256) {
+            const int c = c0 + t;
+            unsigned long long m = __ballot(c < B && marks[(size_t)row0 * K + min(max(perm[kbase + min(c, B - 1)], 0), K - 1)] != 0);
+            m |= m >> 1; m |= m >> 2;
+            steps += __popcll(m & 0x1111111111111111ull);
+        }
+        int* sum = reinterpret_cast<int*>(smem);
+        if (t % kWave == 0) sum[t / kWave] = steps;
+        __syncthreads();
+        seq = (sum[0] + sum[1] + sum[2] + sum[3]) * kRedoShare * 4 > B;
+        __syncthreads();
+    }
+    if (!seq) blockdiag_mfma_tile<true, TN>(Z, perm, R, M, K, B, U, nullptr, row0, col0, smem, nullptr);
+    else blockdiag_seq_tile<TN>(Z, perm, R, M, K, B, U, row0, col0, smem);
 }
 
 // One workgroup per row: absmax and codes from fp64 U.
@@ -1335,22 +1376,20 @@ hipError_t launch_dense_rotate_quant(hipStream_t st, const uint16_t* X, const ui
 hipError_t launch_blockperm_rotate_quant(hipStream_t st, const uint16_t* X, int M, int K, int B, const uint16_t* R1,
                                          const int32_t* perm, const uint16_t* R2, int act_bits, double* U, double* Zp,
                                          int8_t* q, float* scale, int32_t* zero, const float* prescale) {
-    static_assert(DT == 64 && SC == 128, "both kernels of the second product walk the same tiles");
-    const int tiles_m = (M + DT - 1) / DT;
-    const dim3 grid((tiles_m + 7) / 8 * 8 * (K / SC)), block(256);
-    const int32_t* none = nullptr;
-    hipLaunchKernelGGL(blockdiag_stage_kernel<false>, grid, block, 0, st, static_cast<const void*>(X), none, R1, M, K, B, Zp, prescale,
-                       tiles_m, q);
+    const int tiles_m = (M + BT - 1) / BT, tiles = tiles_m * (K / BTN);
+    uint8_t* marks = prescale ? nullptr : reinterpret_cast<uint8_t*>(q);
+    hipLaunchKernelGGL(blockdiag_first_kernel, dim3((tiles + 7) / 8 * 8), dim3(256), 0, st, X, R1, M, K, B, Zp, prescale, tiles, marks);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (!prescale) {
-        hipLaunchKernelGGL(blockdiag_stage_kernel<true>, grid, block, 0, st, static_cast<const void*>(Zp), perm, R2, M, K, B, U,
-                           static_cast<const float*>(nullptr), tiles_m, q);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(blockdiag_rotate_seq_f64_kernel, grid, block, 0, st, Zp, perm, R2, M, K, B, U, tiles_m,
-                       static_cast<const int8_t*>(prescale ? nullptr : q));
+    // Columns of the second product's tiles: 64 where the fullest CU then has less to do (up to one and a half tiles of 128 columns
+    // per CU; at most one: a workgroup's own time halves).  Whole rotation, us, 64 / 128 columns: 256 x 3072 (96 tiles) 40.6 / 46.5, with
+    // a pre-scale 43.0 / 51.1; 2048 x 1536 (384 tiles) 119 / 125 and 136 / 148; beyond, the operands' second trip through LDS counts:
+    // 4096 x 1536 (768) 198 / 174 and 233 / 217, 8192 x 1152 (1152) 165 / 159 and 196 / 195.
+    const int n = 2 * tiles;
+    if (tiles <= 384)
+        hipLaunchKernelGGL(blockdiag_second_kernel<64>, dim3((n + 7) / 8 * 8), dim3(256), 0, st, Zp, perm, R2, M, K, B, U, n, marks);
+    else
+        hipLaunchKernelGGL(blockdiag_second_kernel<128>, dim3((tiles + 7) / 8 * 8), dim3(256), 0, st, Zp, perm, R2, M, K, B, U, tiles, marks);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const QuantSpec qs = make_spec(act_bits, 1, zero);

@@ -304,10 +304,29 @@ def test_blockperm_rotate_quant_bit_exact(lrq, M, K, B, a_bits, asym):
     assert np.array_equal(u, u_ref)
 
 
-@pytest.mark.parametrize("M,K,B,spread", [(200, 384, 128, 4), (130, 512, 256, 7), (129, 256, 128, 12), (70, 256, 128, 40)])
-def test_blockperm_significands_of_every_width(lrq, M, K, B, spread):
-    """Exponents spread over 2^+-spread make z = x.R1 use up to all 53 bits of its significand: the second product then mixes
-    fused and separately rounded steps (small spreads) or takes separate roundings for whole row tiles (large ones)."""
+def _blockperm_forms(z, perm, B):
+    """Per (64-row tile, block of the second product): matrix steps of four channels that hold a z with more than 45 significant
+    bits, and whether they are so many that the tile takes separate roundings throughout (kRedoShare of the kernel's source)."""
+    import os
+    import re
+    import paper_2508_03485_amd as m
+    with open(os.path.join(os.path.dirname(m.__file__), "csrc", "rotate_quant.hip")) as f:
+        share = int(re.search(r"constexpr int kRedoShare = (\d+);", f.read()).group(1))
+    M, K = z.shape
+    wide = np.zeros(((M + 63) // 64 * 64, K), bool)
+    wide[:M] = (z.view(np.uint64) & np.uint64(0xff)) != 0
+    steps = wide.reshape(-1, 64, K).any(1)[:, perm].reshape(-1, K // B, B // 4, 4).any(-1).sum(-1)
+    return steps, steps * 4 * share > B
+
+
+@pytest.mark.parametrize("M,K,B,spread,forms", [
+    (200, 384, 128, 4, "fused redone"), (130, 512, 256, 7, "fused redone separate"), (129, 256, 128, 12, "fused redone separate"),
+    (70, 256, 128, 40, "separate"), (200, 384, 384, 4, "fused redone separate"), (300, 768, 256, 3, "fused redone separate"),
+    (4150, 768, 128, 5, "fused redone separate"),       # 390 tiles of 64 x 128: the wide tiles of the second product
+])
+def test_blockperm_significands_of_every_width(lrq, M, K, B, spread, forms):
+    """Exponents spread over 2^+-spread make z = x.R1 use up to all 53 bits of its significand: a tile of the second product
+    is then fused throughout, fused with some steps redone, or rounded separately throughout - each case in the forms it names."""
     print(f"case blockperm widths M={M} K={K} B={B} spread={spread}", flush=True)
     rng = synth.rng_for(910, M, K, spread)
     x = rng.standard_normal((M, K))
@@ -315,18 +334,47 @@ def test_blockperm_significands_of_every_width(lrq, M, K, B, spread):
     x[M // 2:, :: 17] *= np.exp2(float(spread))
     X = synth.f32_to_bf16_bits(x.astype(np.float32))
     bp, rot = _blockperm_inputs(lrq, K, B, M)
-    z = oracle.rotate_blockperm(oracle.bf16_bits_to_f64(X), oracle.bf16_bits_to_f64(bp[0]), np.arange(K),
-                                np.broadcast_to(np.eye(B), (K // B, B, B)))
-    share = float(((z.view(np.uint64) & np.uint64(0xff)) != 0).mean())
-    print(f"share of z with more than 45 bits: {share:.2e}", flush=True)
+    z = oracle.rotate_blockdiag(oracle.bf16_bits_to_f64(X), oracle.bf16_bits_to_f64(bp[0]))
+    steps, separate = _blockperm_forms(z, bp[1], B)
+    taken = {"fused": (steps == 0).any(), "redone": ((steps > 0) & ~separate).any(), "separate": separate.any()}
+    assert {f for f, t in taken.items() if t} == set(forms.split())
     import torch
     ws = torch.zeros(lrq.ars_workspace_bytes(M, K, rot, 8), dtype=torch.uint8, device="cuda")
     q, s = lrq.ars_rotate_quant(bf16_to_dev(X), rot, 8, workspace=ws)
     u = ws[:M * K * 8].view(torch.float64).view(M, K).cpu().numpy()
-    assert np.array_equal(u, oracle.rotate_blockperm(oracle.bf16_bits_to_f64(X), oracle.bf16_bits_to_f64(bp[0]), bp[1],
-                                                     oracle.bf16_bits_to_f64(bp[2])))
+    u_ref = oracle.rotate_blockdiag(z[:, bp[1]], oracle.bf16_bits_to_f64(bp[2]))
+    assert np.array_equal(u, u_ref)
     q_ref, s_ref = oracle.ars_rotate_quant(X, 8, "blockperm", blockperm=bp)
     assert np.array_equal(q.cpu().numpy(), q_ref) and np.array_equal(s.cpu().numpy(), s_ref)
+
+
+def test_blockperm_wide_sums_do_not_slow_the_rotation_down(lrq):
+    """Activations of widely spread magnitudes: tiles that would redo many steps take separate roundings, and the rotation stays near
+    its time on ordinary activations (it took 2.05 times that while the form was chosen by the share of wide z alone - a single one
+    makes its whole step redone).  Separate roundings everywhere take 1.2 times; limit 1.5."""
+    import torch
+    M, K, B = 2048, 1536, 256
+    print(f"case blockperm clustered M={M} K={K} B={B}", flush=True)
+    _, rot = _blockperm_inputs(lrq, K, B, M)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn(M, K, generator=gen, device="cuda")
+    spread = x * torch.exp2(2.3 * torch.randn(M, K, generator=gen, device="cuda"))
+    q, s = torch.empty(M, K, dtype=torch.int8, device="cuda"), torch.empty(M, device="cuda")
+    ws = torch.zeros(lrq.ars_workspace_bytes(M, K, rot, 8), dtype=torch.uint8, device="cuda")
+    times = []
+    for v in (x, spread):
+        X, best = v.to(torch.bfloat16), 1e9
+        for _ in range(20):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                lrq.ars_rotate_quant(X, rot, 8, q=q, scale=s, workspace=ws)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        times.append(best)
+    print(f"ordinary {100 * times[0]:.1f} us, spread {100 * times[1]:.1f} us", flush=True)
+    assert times[1] < 1.5 * times[0]
 
 
 def test_blockperm_qlinear_against_oracle(lrq):
