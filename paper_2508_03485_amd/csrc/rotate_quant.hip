@@ -795,7 +795,8 @@ __global__ __launch_bounds__(256, 2) void blockdiag_rotate_mfma_f64_kernel(const
 //   The first product marks the channels of a row tile that hold such a z (a byte each, at the head of the tile's q rows, which
 //   the quantizer overwrites later).  A workgroup counts the steps its own channels would redo and takes the separately rounded
 //   form on the vector units (blockdiag_seq_tile) where they are more than one in kRedoShare; there also goes everything with a
-//   pre-scale, whose fp32 factors fill the significands.
+//   pre-scale, whose fp32 factors fill the significands, and a tile whose R holds an infinity or a NaN (times the zeros of
+//   the identity these would reach other columns).
 //   The channels are gathered straight from z (indices clamped into [0, K): a malformed perm gives wrong values, never an
 //   out-of-range access).
 // LDS rows: 34 doubles (left) and 2 TN + 32 bytes (R), which put the 32 lanes of a fragment read on distinct banks.
@@ -813,8 +814,9 @@ __device__ __forceinline__ int xcd_tile(int tiles) {
     return id < tiles ? id : -1;
 }
 
+// Returns whether R held a value that is not finite (GATHER; then nothing is stored), the same in every thread.
 template <bool GATHER, int TN>
-__device__ __forceinline__ void blockdiag_mfma_tile(const void* __restrict__ src, const int32_t* __restrict__ perm,
+__device__ __forceinline__ bool blockdiag_mfma_tile(const void* __restrict__ src, const int32_t* __restrict__ perm,
                                                     const uint16_t* __restrict__ R, int M, int K, int B, double* __restrict__ dst,
                                                     const float* __restrict__ ps, int row0, int col0, unsigned char* smem,
                                                     uint8_t* __restrict__ marks) {
@@ -836,6 +838,7 @@ __device__ __forceinline__ void blockdiag_mfma_tile(const void* __restrict__ src
     double ln[8];                                   // the stage in flight
     v4u xn, rn[RV];
     int4 pn0 = {0, 0, 0, 0}, pn1 = {0, 0, 0, 0};    // indices of the stage after it
+    unsigned nonfinite = 0;                         // bits 15, 31: a half of some dword of R has all exponent bits set
     auto load_perm = [&](int k0) {
         if constexpr (GATHER) {
             const int4* p = reinterpret_cast<const int4*>(perm + kbase + lk + k0);
@@ -869,7 +872,14 @@ __device__ __forceinline__ void blockdiag_mfma_tile(const void* __restrict__ src
 #pragma unroll
         for (int i = 0; i < 4; ++i) ld[i] = make_double2(ln[2 * i], ln[2 * i + 1]);
 #pragma unroll
-        for (int v = 0; v < RV; ++v) *reinterpret_cast<v4u*>(&Rs[buf * BKS * RS + (rk + v * (BKS / RV)) * RS + rc * 2]) = rn[v];
+        for (int v = 0; v < RV; ++v) {
+            *reinterpret_cast<v4u*>(&Rs[buf * BKS * RS + (rk + v * (BKS / RV)) * RS + rc * 2]) = rn[v];
+            if constexpr (GATHER) {
+                const unsigned w[4] = {rn[v][0], rn[v][1], rn[v][2], rn[v][3]};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) nonfinite |= (w[i] & 0x7f807f80u) + 0x00800080u;
+            }
+        }
     };
     load_perm(0);
     load(0);
@@ -942,6 +952,9 @@ __device__ __forceinline__ void blockdiag_mfma_tile(const void* __restrict__ src
         if (more) stage(cur ^ 1, k0 + BKS);         // its last readers passed the barrier that closed the previous stage
         __syncthreads();
     }
+    if constexpr (GATHER) {
+        if (__syncthreads_or((nonfinite & 0x80008000u) != 0)) return true;
+    }
     bool wide[NJ] = {};
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -970,6 +983,7 @@ __device__ __forceinline__ void blockdiag_mfma_tile(const void* __restrict__ src
             if (t < TN) marks[(size_t)row0 * K + col0 + t] = of[t] | of[TN + t];
         }
     }
+    return false;
 }
 
 // The second product's tile with separate roundings throughout, on the fp64 vector units.  TN / 16 x 4 outputs per thread, 16 k per
@@ -1095,8 +1109,8 @@ __global__ __launch_bounds__(256, 3) void blockdiag_second_kernel(const double* 
         seq = (sum[0] + sum[1] + sum[2] + sum[3]) * kRedoShare * 4 > B;
         __syncthreads();
     }
-    if (!seq) blockdiag_mfma_tile<true, TN>(Z, perm, R, M, K, B, U, nullptr, row0, col0, smem, nullptr);
-    else blockdiag_seq_tile<TN>(Z, perm, R, M, K, B, U, row0, col0, smem);
+    if (!seq) seq = blockdiag_mfma_tile<true, TN>(Z, perm, R, M, K, B, U, nullptr, row0, col0, smem, nullptr);
+    if (seq) blockdiag_seq_tile<TN>(Z, perm, R, M, K, B, U, row0, col0, smem);
 }
 
 // One workgroup per row: absmax and codes from fp64 U.

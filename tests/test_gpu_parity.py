@@ -348,6 +348,34 @@ def test_blockperm_significands_of_every_width(lrq, M, K, B, spread, forms):
     assert np.array_equal(q.cpu().numpy(), q_ref) and np.array_equal(s.cpu().numpy(), s_ref)
 
 
+def test_blockperm_second_rotation_that_is_not_finite(lrq):
+    """An infinity or a NaN in a column of R2 reaches that column of u only, also where steps are redone (there every column of a
+    tile takes part in products with zeros)."""
+    import torch
+    M, K, B = 200, 384, 128
+    print(f"case blockperm non-finite R2 M={M} K={K} B={B}", flush=True)
+    rng = synth.rng_for(910, M, K, 4)
+    x = rng.standard_normal((M, K))
+    x[: M // 2] *= np.exp2(rng.integers(-4, 5, size=(M // 2, K)))
+    X = synth.f32_to_bf16_bits(x.astype(np.float32))
+    (R1, perm, R2), rot = _blockperm_inputs(lrq, K, B, M)
+    z = oracle.rotate_blockdiag(oracle.bf16_bits_to_f64(X), oracle.bf16_bits_to_f64(R1))
+    steps, separate = _blockperm_forms(z, perm, B)
+    redone = np.flatnonzero(((steps > 0) & ~separate).any(0))
+    assert redone.size
+    R2 = R2.copy()
+    R2[redone, :, 5] = 0x7f80
+    R2[redone[0], 7, 100] = 0x7fc0
+    rot.R2 = bf16_to_dev(R2)
+    ws = torch.zeros(lrq.ars_workspace_bytes(M, K, rot, 8), dtype=torch.uint8, device="cuda")
+    lrq.ars_rotate_quant(bf16_to_dev(X), rot, 8, workspace=ws)
+    u = ws[:M * K * 8].view(torch.float64).view(M, K).cpu().numpy()
+    with np.errstate(all="ignore"):
+        u_ref = oracle.rotate_blockdiag(z[:, perm], oracle.bf16_bits_to_f64(R2))
+    assert np.isnan(u_ref).any() and np.isfinite(u_ref[:, redone[0] * B + 4]).all()
+    assert np.array_equal(u, u_ref, equal_nan=True)
+
+
 def test_blockperm_wide_sums_do_not_slow_the_rotation_down(lrq):
     """Activations of widely spread magnitudes: tiles that would redo many steps take separate roundings, and the rotation stays near
     its time on ordinary activations (it took 2.05 times that while the form was chosen by the share of wide z alone - a single one
