@@ -86,10 +86,15 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
 }
 
-// fp32(a + zero * colsum).  The sum can exceed 32 bits but is a whole number below 2^53 (|zero| <= 2^31, |colsum| <= 127 K), so
-// fp64 holds it exactly and the conversion rounds it once, as it would a 64-bit integer; that takes three instructions where the
-// 64-bit multiply and conversion take about twenty (2333 x 1152 -> 1091: 2 us of a 15 us launch).
+// fp32(a + zero * colsum).  The sum can exceed 32 bits.  Up to kZpF64K channels it is a whole number below 2^53 (|zero| <= 2^31,
+// |colsum| <= 127 K, |a| <= 127^2 K), so fp64 holds it exactly and the conversion rounds it once, as it would a 64-bit integer; that
+// takes three instructions where the 64-bit multiply and conversion take about twenty (2333 x 1152 -> 1091: 2 us of a 15 us
+// launch).  Longer rows take the integers, in a kernel of their own (ZP64), so that the others do not carry them.
+constexpr int kZpF64K = 32768;
 __device__ __forceinline__ float zp_sum(int a, double zero, double colsum) { return (float)fma(zero, colsum, (double)a); }
+__device__ __forceinline__ float zp_sum64(int a, double zero, double colsum) {
+    return (float)((long long)a + (long long)(int)zero * (long long)(int)colsum);
+}
 
 // One K block of the main loop.  The A tiles rotate through three LDS buffers: block kb multiplies from `cur`
 // (tile kb), stages tile kb+2 (held in aS, which is then reloaded with tile kb+4) into `st`, and - because tile kb+1
@@ -179,7 +184,7 @@ __device__ __forceinline__ void kblock(unsigned char* smem, int cur, int st, int
 // (launch_qgemm picks): 128 x 256 (NTW = 2, 128 accumulator registers per lane, two workgroups per CU), 160 x 128, 128 x 128
 // (NTW = 1, 64 accumulator registers, three per CU) and 64 x 128 (256-row shapes - half the decode work per MFMA - measured
 // no faster, or slower, on every workload).  ZP: zero-point form (epilogue term).
-template <int BITS, int BM, int NTW, bool ZP, bool A4P = false>
+template <int BITS, int BM, int NTW, bool ZP, bool A4P = false, bool ZP64 = false>
 __global__ __launch_bounds__(256, BM * NTW <= 128 ? 3 : (BM * NTW <= 256 ? 2 : 1)) void qgemm_kernel(
     const int8_t* __restrict__ q, const float* __restrict__ scale, int M, int K, int N,
     const uint8_t* __restrict__ gcodes, const int8_t* __restrict__ lut, const float* __restrict__ wscale,
@@ -364,7 +369,7 @@ __global__ __launch_bounds__(256, BM * NTW <= 128 ? 3 : (BM * NTW <= 256 ? 2 : 1
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
             const int a = acc[i][ct][x];
-            const float tot = ZP ? zp_sum(a, zv, cq[ct][x]) : (float)a;
+            const float tot = ZP64 ? zp_sum64(a, zv, cq[ct][x]) : (ZP ? zp_sum(a, zv, cq[ct][x]) : (float)a);
             y[x] = (tot * sv) * wq[ct][x] + bq[ct][x];
         }
     };
@@ -604,6 +609,16 @@ hipError_t launch(hipStream_t st, const int8_t* q, const float* scale, const int
     return hipGetLastError();
 }
 
+// the zero-point form of rows longer than kZpF64K
+template <int BITS>
+hipError_t launch_long(hipStream_t st, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
+                       const lrq_tlq_weight& w, const float* bias, int fp32, void* Y) {
+    const int tiles_m = (M + 127) / 128, tiles_n = (w.N + 127) / 128;
+    hipLaunchKernelGGL((qgemm_kernel<BITS, 128, 1, true, false, true>), dim3(tiles_m * tiles_n), dim3(256), 0, st, q, scale, M, K, w.N,
+                       w.gemm_codes, w.lut, w.wscale, bias, fp32, Y, tiles_m, tiles_n, zero, w.colsum, 0);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_qgemm(hipStream_t st, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
@@ -612,6 +627,10 @@ hipError_t launch_qgemm(hipStream_t st, const int8_t* q, const float* scale, con
     const int fp32 = out_dtype == LRQ_OUT_FP32;
 #define LRQ_SHAPE(F, ...) (w.bits == 4 ? F<4, __VA_ARGS__>(st, q, scale, zero, M, K, w, bias, fp32, Y, packed4)   \
                                        : F<3, __VA_ARGS__>(st, q, scale, zero, M, K, w, bias, fp32, Y, packed4))
+    if (zero && K > kZpF64K) {
+        if (w.bits == 4) return launch_long<4>(st, q, scale, zero, M, K, w, bias, fp32, Y);
+        return launch_long<3>(st, q, scale, zero, M, K, w, bias, fp32, Y);
+    }
     // Small products.  Up to this many outputs, K split over the waves of a workgroup is faster than tiles that walk all of K in
     // sequence (M x K -> N, us, split against the best tile: 512 x 1152 -> 1152 7.0 / 7.5, 64 x 3072 -> 9216 12.0 / 14.5, 256 x 3072 ->
     // 3072 12.2 / 14.6, 16 x 3072 -> 12288 6.2 / 14.2; beyond it the operands are fetched too often: 1024 x 1152 -> 1152 10.1 / 7.7).

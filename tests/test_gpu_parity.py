@@ -680,6 +680,53 @@ def test_qgemm_against_oracle(lrq, M, N, K, w_bits, a_bits):
         assert np.array_equal(acc.astype(np.float64), ref_acc)
 
 
+@pytest.mark.parametrize("M,N", [(24, 32), (1700, 1024)])
+def test_qgemm_zero_point_sum_of_rows_past_fp64(lrq, M, N):
+    """K = 49152 (weights assembled from three packed ones): acc + zero * colsum reaches past 2^53, where one token in each row
+    pair lies one above the middle of two fp32 values - rounded to fp64 first it becomes the middle and goes down."""
+    import torch
+    K, P = 49152, 16384
+    print(f"case qgemm long rows M={M} N={N} K={K}", flush=True)
+    one = to_dev(np.array([1.0], np.float32))
+    parts = [lrq.tlq_quantize_pack(to_dev(synth.make_weights(N, P, (943, N, i))), 4, 7, one, one) for i in range(K // P)]
+    w = lrq.TLQWeight(N, K, 4, 7, torch.device("cuda"))
+    w.gemm_codes.copy_(torch.cat([p.gemm_codes.view(N // 32, -1) for p in parts], dim=1).reshape(-1))
+    codes = np.concatenate([oracle.unpack_codes(p.codes.cpu().numpy(), 4, P) for p in parts], axis=1) & 15
+    lut = np.full((N, 16), 127, np.int8)
+    lut[:, 1] = 1
+    w.lut.copy_(to_dev(lut))
+    w.wscale.fill_(1.0)
+    levels = np.take_along_axis(lut, codes.astype(np.int64), axis=1)
+    colsum = levels.astype(np.int64).sum(axis=1)
+    w.colsum.copy_(to_dev(colsum.astype(np.int32)))
+
+    rng = synth.rng_for(943, M, N)
+    q = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
+    zero = rng.integers(-2 ** 31, 2 ** 31, size=M)
+    for t in range(0, min(M, 64), 2):                    # channel t % N of token t: total = 2^29 + 1 modulo 2^31
+        n = t % N
+        ones, rest = np.flatnonzero(levels[n] == 1), np.flatnonzero(levels[n] == 127)
+        while True:
+            z = int(rng.integers(2 ** 31 - 2 ** 24, 2 ** 31))
+            a = (2 ** 29 + 1 - z * int(colsum[n])) % 2 ** 31
+            a -= 2 ** 31 if a >= 2 ** 30 else 0
+            if abs(a) < 2 ** 29:
+                break
+        r = (a + 63) % 127 - 63
+        s = (a - r) // 127
+        q[t] = 0
+        q[t, ones[0]] = r
+        q[t, rest] = s // len(rest)
+        q[t, rest[: s % len(rest)]] += 1
+        zero[t] = z
+        assert z * int(colsum[n]) + a > 2 ** 53
+    acc = torch.from_numpy(q).cuda().double() @ torch.from_numpy(levels).cuda().double().T      # exact: below 2^30
+    total = acc.cpu().numpy().astype(np.int64) + zero[:, None] * colsum[None, :]
+    y = lrq.qgemm(to_dev(q), torch.ones(M, device="cuda"), w, out_dtype=torch.float32, zero=to_dev(zero.astype(np.int32)))
+    assert (total.astype(np.float64).astype(np.float32) != total.astype(np.float32)).sum() >= min(M, 64) // 2
+    assert np.array_equal(y.cpu().numpy(), total.astype(np.float32))
+
+
 @pytest.mark.parametrize("M,N,K,w_bits,form", [
     (5, 70, 64, 3, "symmetric"),          # split K: 16-row tiles, fewer K blocks than waves, cut channel tile, odd pairs
     (17, 33, 1600, 4, "zero_point"),      # 25 blocks: a second batch that only one wave has
