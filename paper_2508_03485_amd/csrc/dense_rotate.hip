@@ -695,9 +695,10 @@ __device__ __forceinline__ double exact_element_wave(const uint16_t* X, const ui
 template <bool ASYM>
 __global__ __launch_bounds__(256) void dense_exact_amax_kernel(const uint16_t* X, const uint16_t* Rt, int M, int K,
                                                                const int* __restrict__ ccount, const uint16_t* __restrict__ cidx,
-                                                               unsigned long long* __restrict__ amax_bits) {
+                                                               unsigned long long* __restrict__ amax_bits, int* __restrict__ nwhole) {
     __shared__ __attribute__((aligned(16))) unsigned char stage[4 * 2 * XE_BUF];
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i == 0) *nwhole = 0;                             // for dense_quant_flag_kernel
     int row = 0, col = 0, side = 0;
     bool have = false;
     if (i < (long)M * CAPC * (ASYM ? 2 : 1)) {
@@ -717,14 +718,15 @@ __global__ __launch_bounds__(256) void dense_exact_amax_kernel(const uint16_t* X
 }
 
 // ---- codes from u~ with the exact amax (zero-point form: the exact maximum and minimum); the elements the bound leaves
-// undecided go to the row's list (one wave per row)
+// undecided go to the row's list (one wave per row); rows to recompute as a whole go to a list of their own
 template <bool ASYM>
 __global__ __launch_bounds__(256) void dense_quant_flag_kernel(const float* __restrict__ Ut, int M, int K, double qmax,
                                                                const double* __restrict__ eps,
                                                                const unsigned long long* __restrict__ amax_bits,
                                                                int8_t* __restrict__ q, float* __restrict__ scale,
                                                                int32_t* __restrict__ zero, int* __restrict__ fcount,
-                                                               uint16_t* __restrict__ fidx, int capf, int* __restrict__ mode) {
+                                                               uint16_t* __restrict__ fidx, int capf, int* __restrict__ mode,
+                                                               int* __restrict__ nwhole, int* __restrict__ whole) {
     extern __shared__ int lds_cnt[];            // one counter per wave
     const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave, row = blockIdx.x * 4 + wv;
     if (lane == 0) lds_cnt[wv] = 0;
@@ -732,7 +734,10 @@ __global__ __launch_bounds__(256) void dense_quant_flag_kernel(const float* __re
     __builtin_amdgcn_wave_barrier();
     if (row >= M) return;
     if (mode[row]) {                            // recomputed as a whole later
-        if (lane == 0) fcount[row] = 0;
+        if (lane == 0) {
+            fcount[row] = 0;
+            whole[atomicAdd(nwhole, 1)] = row;
+        }
         return;
     }
     const RowQuant rq = row_quant<ASYM>(amax_bits[2 * (size_t)row], amax_bits[2 * (size_t)row + 1], qmax);
@@ -768,6 +773,7 @@ __global__ __launch_bounds__(256) void dense_quant_flag_kernel(const float* __re
         if (n > capf) {
             mode[row] = 1;
             fcount[row] = 0;
+            whole[atomicAdd(nwhole, 1)] = row;
         } else {
             fcount[row] = n;
         }
@@ -873,21 +879,21 @@ __global__ __launch_bounds__(256, 3) void dense_exact_codes_kernel(const uint16_
     }
 }
 
-// ---- rows recomputed as a whole (a workgroup looks at RPW rows, usually to find that none is marked; one row each took twice
-// as long over it): every column's chain, twice - once for the maximum (zero-point form: maximum and minimum), once for the codes - with the row of x in LDS; R
-// is read row by row, coalesced.
-constexpr int RPW = 8;
+// ---- rows recomputed as a whole: every column's chain, twice - once for the maximum (zero-point form: maximum and minimum), once
+// for the codes - with the row of x in LDS; R is read row by row, coalesced, two columns a thread.  Bound by the latency of a row's
+// chains where few rows are marked, by the reads of R where many are; so a row has a workgroup to itself as long as there are
+// any (the grid walks the list of marked rows, whose order does not matter) and a thread keeps 32 loads in flight.  Rotate and
+// quantize, us, one row marked / 512 neighbours / all, 8192 x 1024: 211 / 282 / 2420 (95 with none; eight neighbouring rows to a
+// workgroup and one load after the other 1410 / 7120 / 7230; a workgroup per row of X, a column a thread 513 / 550 / 2990).
 template <bool ASYM>
 __global__ __launch_bounds__(256) void dense_exact_rows_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ R,
-                                                               int M, int K, double qmax, const int* __restrict__ mode,
-                                                               int8_t* __restrict__ q, float* __restrict__ scale,
-                                                               int32_t* __restrict__ zero) {
+                                                               int K, double qmax, const int* __restrict__ nwhole,
+                                                               const int* __restrict__ whole, int8_t* __restrict__ q,
+                                                               float* __restrict__ scale, int32_t* __restrict__ zero) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const int t = threadIdx.x, first = blockIdx.x * RPW;
-    const bool marked = t % kWave < RPW && first + t % kWave < M && mode[first + t % kWave] != 0;
-    unsigned long long todo = __ballot(marked);          // the same in every wave
-    for (; todo; todo &= todo - 1) {
-        const int row = first + __ffsll((long long)todo) - 1;
+    const int t = threadIdx.x, n = *nwhole;
+    for (int w = blockIdx.x; w < n; w += gridDim.x) {
+        const int row = whole[w];
         __syncthreads();                                     // the previous row's x and maxima have been read
         uint16_t* xr = reinterpret_cast<uint16_t*>(lds_raw);
         double* red = reinterpret_cast<double*>(lds_raw + (((size_t)K * 2 + 15) & ~(size_t)15));
@@ -896,16 +902,27 @@ __global__ __launch_bounds__(256) void dense_exact_rows_kernel(const uint16_t* _
         RowQuant rq = {};
         for (int pass = 0; pass < 2; ++pass) {
             double mx = ASYM ? -INFINITY : 0.0, mn = -INFINITY;      // mn: maximum of -u
-            for (int col = t; col < K; col += 256) {
+            for (int col = 2 * t; col < K; col += 512) {
                 const uint16_t* r = R + col;
-                double u = 0.0;
-                for (int k = 0; k < K; ++k)
-                    u = fma((double)__uint_as_float((unsigned)xr[k] << 16), (double)__uint_as_float((unsigned)r[(size_t)k * K] << 16), u);
+                double u0 = 0.0, u1 = 0.0;
+                for (int k = 0; k < K; k += 32) {            // 32 loads in flight: K % 128 == 0
+                    unsigned rv[32];
+#pragma unroll
+                    for (int i = 0; i < 32; ++i) rv[i] = *reinterpret_cast<const unsigned*>(r + (size_t)(k + i) * K);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < 32; ++i) {
+                        const double x = (double)__uint_as_float((unsigned)xr[k + i] << 16);
+                        u0 = fma(x, (double)bf16_lo(rv[i]), u0);
+                        u1 = fma(x, (double)bf16_hi(rv[i]), u1);
+                    }
+                }
                 if (pass == 0) {
-                    mx = fmax(mx, ASYM ? u : fabs(u));
-                    if (ASYM) mn = fmax(mn, -u);
+                    mx = fmax(mx, ASYM ? fmax(u0, u1) : fmax(fabs(u0), fabs(u1)));
+                    if (ASYM) mn = fmax(mn, fmax(-u0, -u1));
                 } else {
-                    q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
+                    q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u0, rq, qmax);
+                    q[(size_t)row * K + col + 1] = (int8_t)exact_code<ASYM>(u1, rq, qmax);
                 }
             }
             if (pass == 0) {
@@ -1007,6 +1024,9 @@ hipError_t launch_dense_fast(hipStream_t st, const uint16_t* X, const uint16_t* 
     uint16_t* fidx = reinterpret_cast<uint16_t*>(base + L.fidx);
     int* foffs = reinterpret_cast<int*>(base + L.foffs);
     int* mode = reinterpret_cast<int*>(base + L.mode);
+    // rows to recompute as a whole, listed when the segment maxima and the candidate counts have been read for the last time
+    int* nwhole = reinterpret_cast<int*>(segmax);
+    int* whole = ccount;
     const double qmax = (double)((1 << (act_bits - 1)) - 1);
     // ETA * m for the runs of the matrix instruction, 2^-24 for each of the GROUP - 1 fp32 additions of a group and for the
     // fp32 store of u~
@@ -1028,13 +1048,13 @@ hipError_t launch_dense_fast(hipStream_t st, const uint16_t* X, const uint16_t* 
         hipLaunchKernelGGL((dense_row_candidates_kernel<false, ASYM>), dim3((M + 3) / 4), dim3(256), 0, st, X, Ut, segmax, M, K, rowmax,
                            scalars, err_factor, eps, amax, ccount, cidx, mode);
     hipLaunchKernelGGL(dense_exact_amax_kernel<ASYM>, dim3((unsigned)(((long)M * CAPC * (ASYM ? 2 : 1) + 255) / 256)), dim3(256), 0, st,
-                       X, Rt, M, K, ccount, cidx, amax);
+                       X, Rt, M, K, ccount, cidx, amax, nwhole);
     hipLaunchKernelGGL(dense_quant_flag_kernel<ASYM>, dim3((M + 3) / 4), dim3(256), 4 * sizeof(int), st, Ut, M, K, qmax, eps, amax, q,
-                       scale, zero, fcount, fidx, L.capf, mode);
+                       scale, zero, fcount, fidx, L.capf, mode, nwhole, whole);
     hipLaunchKernelGGL(dense_scan_counts_kernel, dim3(1), dim3(1024), 0, st, fcount, M, foffs);
     hipLaunchKernelGGL(dense_exact_codes_kernel<ASYM>, dim3(2048), dim3(256), 0, st, X, Rt, M, K, qmax, foffs, fidx, L.capf, amax, q);
     const size_t rows_lds = (((size_t)K * 2 + 15) & ~(size_t)15) + 8 * sizeof(double);
-    hipLaunchKernelGGL(dense_exact_rows_kernel<ASYM>, dim3((M + RPW - 1) / RPW), dim3(256), rows_lds, st, X, R, M, K, qmax, mode,
+    hipLaunchKernelGGL(dense_exact_rows_kernel<ASYM>, dim3(M < 2048 ? M : 2048), dim3(256), rows_lds, st, X, R, K, qmax, nwhole, whole,
                        q, scale, zero);
     return hipGetLastError();
 }

@@ -270,6 +270,53 @@ def test_dense_rotation_random_shapes(lrq, seed):
         assert np.array_equal(a.cpu().numpy(), b)
 
 
+def _equal_maxima_inputs(M, K, marked):
+    """Sylvester Hadamard matrix as the rotation; the marked rows hold one spike, so that every |u| of theirs is a maximum."""
+    R = synth.f32_to_bf16_bits((oracle.hadamard_matrix(K) / np.sqrt(K)).astype(np.float32))
+    x = synth.rng_for(944, M, K).standard_normal((M, K)).astype(np.float32)
+    x[marked] = 0.0
+    x[marked, np.asarray(marked) % K] = 3.0
+    return synth.f32_to_bf16_bits(x), R
+
+
+@pytest.mark.parametrize("asym", [False, True])
+def test_dense_rows_recomputed_as_a_whole_past_the_grid(lrq, asym):
+    """More rows to recompute as a whole than the kernel has workgroups (2048), beside rows that are not."""
+    M, K = 2200, 256
+    print(f"case dense whole rows M={M} K={K} asym={asym}", flush=True)
+    X, R = _equal_maxima_inputs(M, K, [r for r in range(M) if r % 20])
+    got = lrq.ars_rotate_quant(bf16_to_dev(X), lrq.Rotation("dense", 0, bf16_to_dev(R)), 8, asym=asym)
+    ref = oracle.ars_rotate_quant_asym(X, 8, "dense", 0, R) if asym else oracle.ars_rotate_quant(X, 8, "dense", R_bits=R)
+    for a, b in zip(got, ref):
+        assert np.array_equal(a.cpu().numpy(), b)
+
+
+def test_dense_run_of_rows_recomputed_as_a_whole_is_not_serial(lrq):
+    """64 neighbouring rows to recompute as a whole take about the time of one (they have a workgroup each; eight rows to a
+    workgroup took 7 times as long).  Limit 2."""
+    import torch
+    M, K = 256, 1024
+    print(f"case dense run of whole rows M={M} K={K}", flush=True)
+    times = []
+    for marked in ([7], list(range(64))):
+        X, R = _equal_maxima_inputs(M, K, marked)
+        Xd, Rd = bf16_to_dev(X), bf16_to_dev(R)
+        rot = lrq.Rotation("dense", 0, Rd, prepared=lrq.ars_dense_prepare(Rd))
+        ws = torch.empty(lrq.ars_workspace_bytes(M, K, rot, 8), dtype=torch.uint8, device="cuda")
+        q, s = torch.empty(M, K, dtype=torch.int8, device="cuda"), torch.empty(M, device="cuda")
+        best = 1e9
+        for _ in range(10):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            lrq.ars_rotate_quant(Xd, rot, 8, q=q, scale=s, workspace=ws)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        times.append(best)
+    print(f"one row {1e3 * times[0]:.0f} us, run of 64 {1e3 * times[1]:.0f} us", flush=True)
+    assert times[1] < 2 * times[0]
+
+
 def _blockperm_inputs(lrq, K, B, seed):
     R1 = synth.make_block_rotations(K, B, (903, K, seed), 0)
     R2 = synth.make_block_rotations(K, B, (903, K, seed), 1)
