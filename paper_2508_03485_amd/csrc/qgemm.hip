@@ -146,32 +146,35 @@ __device__ __forceinline__ void kblock(unsigned char* smem, int cur, int st, int
     constexpr int DIST = AF_DIST;                   // A fragments are read this many row tiles ahead
 #pragma unroll
     for (int p = 0; p < DIST; ++p) af[p] = afp[p];
-    // Two row tiles at a time, their matrix instructions in an order that changes one operand per instruction: the matrix pipe
-    // is limited by the power its operands' toggling draws (35100 x 12288 -> 3072, us: weight operand changing with every
-    // instruction 1207, back and forth over the column tiles 1196, this order 1187 - 1193).
-    static_assert(AF_DIST == 2 && RT % 2 == 0, "row tiles are walked in pairs, one pair read ahead");
+    // Order of the matrix instructions (operand changes cost power, decode needs issue slots between them).  4-bit codes: two row
+    // tiles at a time, one operand changing per instruction; 3-bit codes, whose decode is a third shorter: one row tile at a time,
+    // back and forth over the column tiles, except in 64-row tiles.  One order for all costs some of them (us, row by row / pairs:
+    // 35100 x 12288 -> 3072 at 4 bits 1235 / 1228, at 3 bits 1035 / 1070; 2502 x 12288 -> 1152, one tile per CU, 64.3 / 61.3 and
+    // 50.2 / 56.2; 64-row tiles at 3 bits, 2500 x 12288 -> 896, 48.4 / 46.5).
+    constexpr int WALK = BITS == 4 || RT == 4 ? 2 : 1;
+    static_assert(AF_DIST == 2 && RT % 2 == 0, "the first pair of the next block is read at row tile RT - 2");
 #pragma unroll
-    for (int p = 0; p < RT; p += 2) {
+    for (int p = 0; p < RT; p += WALK) {
         if (p == RT - 2) {          // next block's first fragments, early enough to land before the closing barrier
 #pragma unroll
             for (int pp = 0; pp < DIST; ++pp)
                 afp[pp] = *reinterpret_cast<const v4i*>(&smem[nx + (pp / 2) * 4 * PLANE + (pp % 2) * 256 + rd_off]);
-        } else {
-#pragma unroll
-            for (int pp = 0; pp < DIST; ++pp)
-                af[p + DIST + pp] = *reinterpret_cast<const v4i*>(&Acur[((p + DIST) / 2) * 4 * PLANE + pp * 256 + rd_off]);
         }
 #pragma unroll
-        for (int d = 0; d < 2 * DPB; ++d) {
+        for (int pp = p + DIST; pp < p + DIST + WALK; ++pp)
+            if (pp < RT) af[pp] = *reinterpret_cast<const v4i*>(&Acur[(pp / 2) * 4 * PLANE + (pp % 2) * 256 + rd_off]);
+#pragma unroll
+        for (int d = 0; d < WALK * DPB; ++d) {
             const int dd = p * DPB + d, ct = dd / 4;
             if (dd < CT * 4) bdNxt[ct][dd % 4] = (int)decode_dword<BITS>(bRaw[ct / 2], L[ct], ct % 2, dd % 4, C);
         }
 #pragma unroll
-        for (int c = 0; c < 2 * CT; ++c) {
-            const int ct = c / 2, i = p + ((c + 1) / 2) % 2;
+        for (int c = 0; c < WALK * CT; ++c) {
+            const int ct = WALK == 2 ? c / 2 : (p % 2 ? CT - 1 - c : c);
+            const int i = WALK == 2 ? p + ((c + 1) / 2) % 2 : p;
             acc[i][ct] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bdCur[ct], af[i], acc[i][ct], 0, 0, 0);
         }
-        if (p == RT - 2) {
+        if (p + WALK == RT) {
 #pragma unroll
             for (int j = 0; j < NTW; ++j) bRaw[j] = load_braw<BITS>(bptr[j] + (size_t)kbn * UNIT);
         }
