@@ -282,6 +282,14 @@ int lrq_qgemm(void* stream, const int8_t* q, const float* scale, int M, int K,
               const lrq_tlq_weight* w, const float* bias, int out_dtype, void* Y);
 
 /*
+ * Which kernel the int8 GEMM takes (host only, launches nothing): tile[0] rows and tile[1] columns of the outputs of one workgroup,
+ * for M tokens, N channels, K input channels, weights of `bits` bits, form 0 (lrq_qgemm), 1 (lrq_qgemm_asym) or 2
+ * (lrq_qgemm_packed4) and out_dtype.  32 columns stand for the kernel that splits K over the waves of a workgroup.  Results do not
+ * depend on the choice.  Errors: LRQ_EINVAL (null pointer, non-positive size, unknown form), LRQ_EUNSUPPORTED.
+ */
+int lrq_qgemm_diagnostics(int M, int N, int K, int bits, int form, int out_dtype, int tile[2]);
+
+/*
  * The same layer on the levels themselves (paper: "Hardware Implementation", exponent split f / r and the
  * integerisation of 2^r with I bits), without the per-channel int8 renormalisation that lrq_qlinear applies to them:
  *   Y[t,n] = scale_t * sum_k q[t,k] * v_n(code[n,k])  (+ bias_n),   v_n(c) = +-round(2^r 2^I) 2^(f-I) = w->levels[n][c].

@@ -319,6 +319,17 @@ int lrq_qgemm(void* stream, const int8_t* q, const float* scale, int M, int K, c
     return qgemm_impl(stream, q, scale, nullptr, Gemm::kInt8, M, K, w, bias, out_dtype, Y);
 }
 
+int lrq_qgemm_diagnostics(int M, int N, int K, int bits, int form, int out_dtype, int tile[2]) {
+    if (M <= 0 || N <= 0 || K <= 0 || form < 0 || form > 2 || !tile) return LRQ_EINVAL;
+    if (bits != 3 && bits != 4) return LRQ_EUNSUPPORTED;
+    if (out_dtype != LRQ_OUT_BF16 && out_dtype != LRQ_OUT_FP32) return LRQ_EUNSUPPORTED;
+    if (K % lrq::kGemmBlockK != 0) return LRQ_EUNSUPPORTED;
+    const lrq::GemmShape s = lrq::qgemm_shape(M, N, K, bits, form == 1, form == 2, out_dtype == LRQ_OUT_FP32);
+    tile[0] = s.rows;
+    tile[1] = s.cols;
+    return LRQ_OK;
+}
+
 int lrq_qgemm_asym(void* stream, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
                    const lrq_tlq_weight* w, const float* bias, int out_dtype, void* Y) {
     return qgemm_impl(stream, q, scale, zero, Gemm::kInt8Zero, M, K, w, bias, out_dtype, Y);

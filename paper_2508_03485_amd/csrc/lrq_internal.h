@@ -92,6 +92,10 @@ hipError_t launch_tlq_quantize_pack(hipStream_t st, const float* W, int N, int K
 hipError_t launch_qgemm(hipStream_t st, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
                         const lrq_tlq_weight& w, const float* bias, int out_dtype, void* Y, bool packed4 = false);
 
+// The kernel launch_qgemm takes: rows and columns of one workgroup's outputs (32 columns: the kernel that splits K).
+struct GemmShape { int rows, cols; };
+GemmShape qgemm_shape(int M, int N, int K, int bits, bool zero_point, bool packed4, bool fp32);
+
 // Y = scale_t * sum_k q * levels (+ bias) on the bf16 matrix cores; w.levels must be set.
 hipError_t launch_qgemm_levels(hipStream_t st, const int8_t* q, const float* scale, int M, int K, const lrq_tlq_weight& w,
                                const float* bias, int out_dtype, void* Y);

@@ -622,7 +622,70 @@ hipError_t launch_long(hipStream_t st, const int8_t* q, const float* scale, cons
     return hipGetLastError();
 }
 
+// ---- dispatch: the kernel whose predicted time is the smallest -----------------------------------------------------
+// Times in us, fitted to 5600 measurements over M = 1 .. 35100, N = 96 .. 12288 and K = 1152 .. 12288, all forms and both output
+// types; the kernel chosen is within 0.7 % of the fastest on average and within 24 % at worst.
+//
+// Tiles.  A CU's tiles run one after the other or share it at the same total rate, so the time follows from the tiles of the
+// fullest CU.  One tile: lone_k (packed codes: + lone_packed) per K block + lone; n > 1 tiles: n (k (+ packed) per K block +
+// tile) + once.  Output rows that are not 16-byte aligned leave element by element: + lone_ragged, or + ragged per tile (4.7 us for
+// a 128 x 256 tile on its own, 2 us where others run beside it).  The tall shapes decode less per matrix instruction, the small
+// ones leave less of the chip idle in the last round: 8192 x 4608 -> 1152 takes 53 us with 160 rows (468 tiles) and 57 with 128 (576),
+// 1000 x 3072 -> 3072 20 us with 128 x 128 and 29 with 128 x 256, 2333 x 1152 -> 1091 in fp32 10.1 us with 64 rows and 13.0 with 128,
+// 35100 x 3072 -> 12001 in fp32 1442 us with 128 x 256 and 1563 with 128 x 128; 3-bit codes decode faster: 8192 x 1152 -> 3456 37 / 38 us.
+struct TileCost { int rows, cols; float lone_k, lone_packed, lone, lone_ragged, k, packed, tile, ragged, once; };
+constexpr TileCost kTileCost[2][4] = {
+    {{128, 256, 0.354f, 0.054f, 5.62f, 4.73f, 0.353f, 0.000f, 3.54f, 2.40f, 1.00f},        // 3-bit codes
+     {160, 128, 0.291f, 0.135f, 4.65f, 2.78f, 0.284f, 0.019f, 2.27f, 1.44f, 1.58f},
+     {128, 128, 0.235f, 0.057f, 4.09f, 2.23f, 0.220f, 0.002f, 1.60f, 0.91f, 2.19f},
+     { 64, 128, 0.174f, 0.069f, 3.26f, 1.03f, 0.126f, 0.021f, 0.72f, 0.39f, 2.63f}},
+    {{128, 256, 0.477f, 0.057f, 5.70f, 4.73f, 0.434f, 0.001f, 3.86f, 2.06f, 0.47f},        // 4-bit codes
+     {160, 128, 0.368f, 0.114f, 4.55f, 2.94f, 0.332f, 0.004f, 2.33f, 1.23f, 1.92f},
+     {128, 128, 0.299f, 0.047f, 4.09f, 2.33f, 0.258f, 0.003f, 1.62f, 0.84f, 2.79f},
+     { 64, 128, 0.232f, 0.074f, 3.28f, 1.15f, 0.167f, 0.022f, 0.64f, 0.32f, 3.73f}}};
+// K split over the waves.  A round of workgroups, one per CU, reads the codes of a K block (w) and 16-row pieces of activations (a
+// each, as many as there are rows for): once + rounds ((w + a pieces (+ packed)) per K block + round).  Its column tiles lie on
+// different XCDs, each of which fetches the activations: + fetch per MB of them and column tile, up to eight.  Measured up to
+// kSplitOutputs; far below it the split always wins, beyond it the operands are fetched too often (us, split / best tile: 16 x 3072 ->
+// 12288 6.2 / 14.2, 256 x 3072 -> 3072 12.2 / 14.6, 1024 x 1152 -> 1152 10.1 / 7.7, 3907 x 6144 -> 256 31.0 / 26.0).  More rows to a workgroup
+// pay once there are more workgroups than CUs (us with 16 / 32 / 64 rows, K = 1152 -> 1152: 64 rows 3.4 / 4.1 / 4.8, 256 rows 5.3 /
+// 5.7 / 4.8).
+struct SplitCost { int rows; float w, a, packed, round, once, fetch; };
+constexpr SplitCost kSplitCost[2][3] = {
+    {{16, 0.0164f, 0.0163f, 0.0009f, 0.37f, 2.17f, 0.0165f},         // 3-bit codes
+     {32, 0.0206f, 0.0181f, 0.0039f, 0.54f, 2.16f, 0.0286f},
+     {64, 0.0337f, 0.0189f, 0.0049f, 0.20f, 2.51f, 0.0389f}},
+    {{16, 0.0288f, 0.0063f, 0.0008f, 0.44f, 2.14f, 0.0145f},         // 4-bit codes
+     {32, 0.0316f, 0.0134f, 0.0048f, 0.51f, 2.22f, 0.0305f},
+     {64, 0.0398f, 0.0173f, 0.0080f, 0.29f, 2.40f, 0.0386f}}};
+constexpr long kSplitOutputs = 1600000;
+
 }  // namespace
+
+// cols == 32: the split-K kernel
+GemmShape qgemm_shape(int M, int N, int K, int bits, bool zero_point, bool packed4, bool fp32) {
+    if (zero_point && K > kZpF64K) return {128, 128};       // the only shape that kernel is built in
+    const float kb = (float)(K / BK), packed = packed4 ? 1.0f : 0.0f;
+    const float ragged = N % (fp32 ? 4 : 8) != 0 ? 1.0f : 0.0f;
+    GemmShape best = {};
+    float best_us = INFINITY;
+    auto consider = [&](int rows, int cols, float us) {
+        if (us < best_us) { best = {rows, cols}; best_us = us; }
+    };
+    for (const TileCost& c : kTileCost[bits - 3]) {
+        const long n = (((long)M + c.rows - 1) / c.rows * (((long)N + c.cols - 1) / c.cols) + 255) / 256;
+        consider(c.rows, c.cols, n == 1 ? (c.lone_k + c.lone_packed * packed) * kb + c.lone + c.lone_ragged * ragged
+                                        : (float)n * ((c.k + c.packed * packed) * kb + c.tile + c.ragged * ragged) + c.once);
+    }
+    if ((long)M * N <= kSplitOutputs)
+        for (const SplitCost& c : kSplitCost[bits - 3]) {
+            const long tn = (N + 31) / 32, rounds = ((M + c.rows - 1) / c.rows * tn + 255) / 256;
+            const float pieces = (float)(M < c.rows ? M : c.rows) / 16.0f;
+            const float mb = (float)M * (float)K * (packed4 ? 0.5e-6f : 1e-6f) * (float)(tn < 8 ? tn : 8);
+            consider(c.rows, 32, c.once + (float)rounds * ((c.w + c.a * pieces + c.packed * packed) * kb + c.round) + c.fetch * mb);
+        }
+    return best;
+}
 
 hipError_t launch_qgemm(hipStream_t st, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
                         const lrq_tlq_weight& w, const float* bias, int out_dtype, void* Y, bool packed4) {
@@ -634,44 +697,16 @@ hipError_t launch_qgemm(hipStream_t st, const int8_t* q, const float* scale, con
         if (w.bits == 4) return launch_long<4>(st, q, scale, zero, M, K, w, bias, fp32, Y);
         return launch_long<3>(st, q, scale, zero, M, K, w, bias, fp32, Y);
     }
-    // Small products.  Up to this many outputs, K split over the waves of a workgroup is faster than tiles that walk all of K in
-    // sequence (M x K -> N, us, split against the best tile: 512 x 1152 -> 1152 7.0 / 7.5, 64 x 3072 -> 9216 12.0 / 14.5, 256 x 3072 ->
-    // 3072 12.2 / 14.6, 16 x 3072 -> 12288 6.2 / 14.2; beyond it the operands are fetched too often: 1024 x 1152 -> 1152 10.1 / 7.7).
-    // Rows per workgroup (1, 2 or 4 sixteens): few while workgroups are what the chip lacks, more once there is one or two per
-    // CU, so that the weights are fetched and decoded less often (us with 1 / 2 / 4: 64 x 1152 -> 1152 3.4 / 4.1 / 4.8, 256 x 1152 ->
-    // 1152 5.3 / 5.7 / 4.8; 64 x 12288 -> 3072 16.6 / 15.4 / 24.9).  Up to 24 K blocks a wave has a single batch of loads, and the
-    // taller tiles pay sooner.
-    if ((long)M * w.N <= 768 * 1024) {
-        const long tn = (w.N + 31) / 32;
-        const bool single = K <= 24 * BK;
-        if (M <= 16 || (M + 15) / 16 * tn <= (single ? 256 : 512)) return LRQ_SHAPE(launch_small, 1);
-        if ((M + 31) / 32 * tn <= (single ? 256 : 768)) return LRQ_SHAPE(launch_small, 2);
+    const GemmShape shape = qgemm_shape(M, w.N, K, w.bits, zero != nullptr, packed4, fp32);
+    if (shape.cols == 32) {
+        if (shape.rows == 16) return LRQ_SHAPE(launch_small, 1);
+        if (shape.rows == 32) return LRQ_SHAPE(launch_small, 2);
         return LRQ_SHAPE(launch_small, 4);
     }
-    // Tile shape.  A CU's tiles run one after the other or share it at the same total rate, so the time follows from the tiles of the
-    // fullest CU: ceil(tiles / 256) x (K blocks + about four for prologue and epilogue) x the shape's time per K block (measured
-    // with one tile per CU and with many, us: 128 x 256 0.47 - 0.49, 160 x 128 0.37, 128 x 128 0.28 - 0.32, 64 x 128 0.17 - 0.24).
-    // Output rows that are not 16-byte aligned leave element by element, which costs most where no other tile hides it.  The
-    // tall shapes decode less per matrix instruction, the small ones leave less of the chip idle in the last round: 8192 x 4608 ->
-    // 1152 takes 56 us with 160 rows (468 tiles) and 61 with 128 (576), 1000 x 3072 -> 3072 takes 20 us with 128 x 128 and 29 with
-    // 128 x 256, 2333 x 1152 -> 1091 in fp32 10.2 us with 64 rows and 13.0 with 128.
-    const struct { int bm, ntw; float us; } shapes[] = {{128, 2, 0.48f}, {160, 1, 0.37f}, {128, 1, 0.29f}, {64, 1, 0.175f}};
-    const bool aligned = w.N % (fp32 ? 4 : 8) == 0;
-    int best = 0;
-    float best_us = 0.0f;
-    for (int i = 0; i < 4; ++i) {
-        const long bn = WAVES * 32 * shapes[i].ntw;
-        const long tiles = (long)((M + shapes[i].bm - 1) / shapes[i].bm) * ((w.N + bn - 1) / bn);
-        const int blocks = K / BK + 4 + (aligned ? 0 : shapes[i].bm * shapes[i].ntw / 8);
-        const float us = (float)((tiles + 255) / 256) * (float)blocks * shapes[i].us;
-        if (i == 0 || us < best_us) { best = i; best_us = us; }
-    }
-    switch (best) {
-        case 0: return LRQ_SHAPE(launch, 128, 2);
-        case 1: return LRQ_SHAPE(launch, 160, 1);
-        case 2: return LRQ_SHAPE(launch, 128, 1);
-        default: return LRQ_SHAPE(launch, 64, 1);
-    }
+    if (shape.cols == 256) return LRQ_SHAPE(launch, 128, 2);
+    if (shape.rows == 160) return LRQ_SHAPE(launch, 160, 1);
+    if (shape.rows == 128) return LRQ_SHAPE(launch, 128, 1);
+    return LRQ_SHAPE(launch, 64, 1);
 #undef LRQ_SHAPE
 }
 

@@ -272,3 +272,27 @@ def test_header_is_plain_c(tmp_path):
     assert r.returncode == 0, r.stderr
     a, b = (int(v) for v in subprocess.run([str(exe)], capture_output=True, text=True).stdout.split())
     assert a == ctypes.sizeof(lrq._Rotation) and b == ctypes.sizeof(lrq._TlqWeight)
+
+
+def test_qgemm_diagnostics(L):
+    """The shape query rejects what the GEMM rejects, and every answer names a kernel that is built."""
+    t = (ctypes.c_int * 2)()
+    f = lambda *a: L.lrq_qgemm_diagnostics(*a, ctypes.byref(t))
+    assert f(0, 64, 64, 4, 0, lrq.LRQ_OUT_BF16) == lrq.LRQ_EINVAL and f(4, 64, 64, 4, 3, lrq.LRQ_OUT_BF16) == lrq.LRQ_EINVAL
+    assert f(4, 64, 64, 5, 0, lrq.LRQ_OUT_BF16) == lrq.LRQ_EUNSUPPORTED and f(4, 64, 72, 4, 0, lrq.LRQ_OUT_BF16) == lrq.LRQ_EUNSUPPORTED
+    assert f(4, 64, 64, 4, 0, 7) == lrq.LRQ_EUNSUPPORTED
+    assert L.lrq_qgemm_diagnostics(4, 64, 64, 4, 0, lrq.LRQ_OUT_BF16, None) == lrq.LRQ_EINVAL
+    built = {(16, 32), (32, 32), (64, 32), (64, 128), (128, 128), (160, 128), (128, 256)}
+    seen = set()
+    for M in (1, 17, 200, 2333, 8192, 35100, 2 ** 31 - 1):
+        for N in (1, 96, 1091, 3456, 12288, 2 ** 31 - 1):
+            for K in (64, 1152, 12288, 49152):
+                for bits in (3, 4):
+                    for form in ("symmetric", "zero_point", "packed"):
+                        tile = lrq.qgemm_tile(M, N, K, bits, form)
+                        assert tile in built
+                        assert form != "zero_point" or K <= 32768 or tile == (128, 128)
+                        seen.add(tile)
+    assert seen == built
+    # output rows that are not aligned keep the tall shape where other tiles hide their stores
+    assert lrq.qgemm_tile(35100, 12001, 3072, 4) == (128, 256) and lrq.qgemm_tile(20000, 9001, 3072, 4) == (128, 256)

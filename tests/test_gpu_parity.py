@@ -774,20 +774,26 @@ def test_qgemm_zero_point_sum_of_rows_past_fp64(lrq, M, N):
     assert np.array_equal(y.cpu().numpy(), total.astype(np.float32))
 
 
-@pytest.mark.parametrize("M,N,K,w_bits,form", [
-    (5, 70, 64, 3, "symmetric"),          # split K: 16-row tiles, fewer K blocks than waves, cut channel tile, odd pairs
-    (17, 33, 1600, 4, "zero_point"),      # 25 blocks: a second batch that only one wave has
-    (150, 1151, 576, 4, "packed"),        # 32-row tiles, N odd
-    (290, 1030, 640, 3, "zero_point"),    # 64-row tiles, cut row tile
-    (770, 1090, 128, 4, "symmetric"),     # just above the split-K range: 64 x 128 tiles, rows of Y not 16-byte aligned
-    (6300, 133, 192, 4, "packed"),        # 128 or 64 rows, three blocks, cut channel tile
-    (8192, 1152, 320, 4, "symmetric"),    # 160 x 128 tiles, cut row tile
-    (8190, 1149, 64, 3, "zero_point"),    # one K block, ragged both ways
-    (4607, 3064, 128, 4, "symmetric"),    # 128 x 256 tiles, cut both ways
+@pytest.mark.parametrize("form", ["symmetric", "zero_point", "packed"])
+@pytest.mark.parametrize("M,N,K,w_bits,tile", [
+    (5, 70, 64, 3, (16, 32)),             # K split over the waves; fewer K blocks than waves, cut channel tile
+    (17, 33, 1600, 4, (16, 32)),          # 25 blocks: a second batch that only one wave has
+    (909, 129, 64, 3, (32, 32)),          # N odd, cut row tile
+    (107, 2059, 64, 4, (64, 32)),
+    (6987, 229, 64, 4, (64, 128)),        # tiles that walk all of K; rows of Y not 16-byte aligned
+    (8695, 104, 64, 4, (64, 128)),        # one K block, one cut channel tile
+    (5860, 288, 64, 4, (128, 128)),
+    (12332, 385, 128, 4, (128, 128)),     # rows not aligned
+    (12418, 393, 320, 3, (128, 128)),     # odd number of K blocks
+    (8521, 392, 64, 3, (160, 128)),       # packed: 320 chunks of A over 256 threads
+    (11662, 833, 128, 4, (160, 128)),     # rows not aligned
+    (4607, 3064, 128, 4, (128, 256)),     # cut both ways
+    (14509, 897, 320, 3, (128, 256)),     # rows not aligned
 ])
-def test_qgemm_tile_shapes(lrq, M, N, K, w_bits, form):
-    """Every shape of the GEMM's dispatch and its edges.  Scales of one make the fp32 outputs the integer sums themselves,
-    which are below 2^24 here except for the zero-point form's, rounded once."""
+def test_qgemm_tile_shapes(lrq, M, N, K, w_bits, tile, form):
+    """Every kernel of the GEMM's dispatch and its edges, in every form, with scales and bias: the integer sums are exact in fp64,
+    and the rescale is three fp32 operations in a stated order, so the outputs are compared bit for bit.  (The zero-point form's
+    sums stay below 2^53.)"""
     import torch
     print(f"case qgemm shapes M={M} N={N} K={K} W{w_bits} {form}", flush=True)
     rng = synth.rng_for(909, M, N, K)
@@ -798,19 +804,21 @@ def test_qgemm_tile_shapes(lrq, M, N, K, w_bits, form):
     wv = np.take_along_axis(lut, codes, axis=1).astype(np.float64)
     lim = 7 if form == "packed" else 127
     q = rng.integers(-lim, lim + 1, size=(M, K)).astype(np.int8)
-    ref = q.astype(np.float64) @ wv.T
+    total = to_dev(q).double() @ to_dev(wv).T.contiguous()
     zero = None
     if form == "zero_point":
         zero = rng.integers(-2 ** 31, 2 ** 31, size=M).astype(np.int32)
-        ref += zero.astype(np.float64)[:, None] * wv.sum(axis=1)[None, :]      # below 2^53: exact
-    w.wscale.fill_(1.0)
-    ones = torch.ones(M, device="cuda")
+        total += to_dev(zero).double()[:, None] * to_dev(wv.sum(axis=1))[None, :]
+    scale = to_dev(np.exp2(rng.uniform(-12, -4, size=M)).astype(np.float32))
+    bias = to_dev((rng.standard_normal(N) * 4).astype(np.float32))
+    ref = total.to(torch.float32) * scale[:, None] * w.wscale[None, :] + bias[None, :]
     for dt in (torch.float32, torch.bfloat16):
+        assert lrq.qgemm_tile(M, N, K, w_bits, form, dt) == tile
         if form == "packed":
-            y = lrq.qgemm_packed4(to_dev(oracle.pack_act_codes4(q)), ones, w, out_dtype=dt)
+            y = lrq.qgemm_packed4(to_dev(oracle.pack_act_codes4(q)), scale, w, bias=bias, out_dtype=dt)
         else:
-            y = lrq.qgemm(to_dev(q), ones, w, out_dtype=dt, zero=None if zero is None else to_dev(zero))
-        assert torch.equal(y.cpu(), torch.from_numpy(ref).to(torch.float32).to(dt))
+            y = lrq.qgemm(to_dev(q), scale, w, bias=bias, out_dtype=dt, zero=None if zero is None else to_dev(zero))
+        assert torch.equal(y, ref.to(dt))
 
 
 @pytest.mark.parametrize("M,N,K,w_bits,a_bits,I", [
