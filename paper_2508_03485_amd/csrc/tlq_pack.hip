@@ -432,7 +432,8 @@ hipError_t launch_tlq_quantize_pack(hipStream_t st, const float* W, int N, int K
                                     const lrq_tlq_weight& out, const float* gamma_grid, int n_gamma, float* gamma_pos,
                                     float* gamma_neg) {
     // Weights per thread: the smallest count that holds the row (K = 1152 fills 4.5 of 5); above 6144 the row goes through the
-    // registers in passes of 16.
+    // registers in passes of 16.  There the row's logarithms leave room for few partial sums beside a second workgroup on the CU: a
+    // grid of one or two candidates takes two at a time (6528 x 8328, one candidate: 860 us, eight at a time 1076).
 #define LRQ_GO(NE, REGS, NC)                                                                                                  \
     {                                                                                                                         \
         const size_t lds = sizeof(SearchLds<NC>) + (size_t)K * (REGS ? 1 : sizeof(double));                                   \
@@ -443,7 +444,7 @@ hipError_t launch_tlq_quantize_pack(hipStream_t st, const float* W, int N, int K
                            out.beta, out.lut, out.wscale, out.gemm_codes, out.colsum, gamma_grid, n_gamma, gamma_pos,         \
                            gamma_neg, out.levels, out.err_pos, out.err_neg, out.lut_fp8, out.wscale_fp8);                     \
     }
-    const int ne = (K + NT - 1) / NT;
+    const int ne = (K + NT - 1) / NT, candidates = (n_alpha > n_beta ? n_alpha : n_beta) * (n_gamma > 0 ? n_gamma : 1);
     if (ne <= 3) LRQ_GO(3, true, 8)
     else if (ne <= 5) LRQ_GO(5, true, 8)
     else if (ne <= 6) LRQ_GO(6, true, 8)
@@ -451,6 +452,7 @@ hipError_t launch_tlq_quantize_pack(hipStream_t st, const float* W, int N, int K
     else if (ne <= 12) LRQ_GO(12, true, 8)
     else if (ne <= 18) LRQ_GO(18, true, 8)
     else if (ne <= 24) LRQ_GO(24, true, 8)
+    else if (candidates <= 2) LRQ_GO(16, false, 2)
     else if (K <= 12288) LRQ_GO(16, false, 8)
     else LRQ_GO(16, false, 4)
 #undef LRQ_GO

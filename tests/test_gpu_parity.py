@@ -628,6 +628,13 @@ def test_tlq_weights_that_are_not_finite(lrq, K, bits):
         _check_weight(lrq, W, bits, 7, GRID[:9], GRID[:12])
 
 
+@pytest.mark.parametrize("K,bits,n", [(6208, 4, 1), (12288, 3, 2), (16384, 4, 1)])
+def test_tlq_search_of_few_candidates_on_long_rows(lrq, K, bits, n):
+    """Rows that go through LDS with a grid of one or two candidates (two at a time)."""
+    print(f"case tlq few candidates K={K} b={bits} n={n}", flush=True)
+    _check_weight(lrq, synth.make_weights(6, K, (945, K, bits)), bits, 7, GRID[:n], GRID[1:2])
+
+
 def test_tlq_search_with_quotients_past_the_reciprocal_range(lrq):
     """Two neighbouring fp32 magnitudes per sign: s is about 2e-8 and log2|w| / s about 3e8, where the search divides instead of
     multiplying by 1 / s.  s itself is the difference of two nearly equal logarithms from two math libraries, so only what
