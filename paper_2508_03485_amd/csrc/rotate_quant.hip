@@ -635,13 +635,12 @@ __global__ __launch_bounds__(128) void dense_rotate_fewrows_kernel(const uint16_
     U[(size_t)row * K + col] = u;
 }
 
-// Block-diagonal product on the fp64 matrix cores: dst[:, block g] = src[:, block g] . R_g with src bf16 [M, K] and
-// R [K/B, B, B] bf16 (B = K is the dense rotation, one block).  v_mfma_f64_16x16x4_f64 accumulates its four k in
+// Dense rotation on the fp64 matrix cores: dst = src . R with src bf16 [M, K] and R bf16 [K, K], K a multiple of 128.
+// v_mfma_f64_16x16x4_f64 accumulates its four k in
 // ascending order, one fused multiply-add each, so chaining the instructions over ascending k gives the same bits as
 // the scalar chain above, and - every product of two bf16 values (times an fp32 pre-scale) being exact in fp64 - the
 // same bits as a sum with separately rounded multiply and add (a GPU test compares U with the definition bit for bit).
-// Workgroup = 4 waves (2 x 2), tile 128 x 128, wave tile 64 x 64 (16 accumulator tiles); B must be a multiple of
-// 128 so that a column tile lies inside one block.
+// Workgroup = 4 waves (2 x 2), tile 128 x 128, wave tile 64 x 64 (16 accumulator tiles).
 // The operand tiles stay in LDS as bf16 and are widened to fp64 when a fragment is read: a K step holds 64 k per
 // barrier, the global -> LDS path is a plain 16-byte copy, and LDS traffic is a quarter of what fp64 tiles would cost.
 // Row strides: 144 bytes for the left tile (36 dwords: the 16 rows a fragment read touches land on 16 distinct banks,
@@ -651,10 +650,10 @@ constexpr int MT_ = 128;
 
 // MR: rows of the workgroup tile, 128 or 64 (wave tile MR / 2 x 64); the tile rows start at row_begin + blockIdx.y * MR.
 template <int MR = MT_>
-__global__ __launch_bounds__(256, 2) void blockdiag_rotate_mfma_f64_kernel(const uint16_t* __restrict__ src,
-                                                                                 const uint16_t* __restrict__ R, int M, int K,
-                                                                                 int B, double* __restrict__ dst,
-                                                                                 const float* __restrict__ ps, int row_begin) {
+__global__ __launch_bounds__(256, 2) void dense_rotate_mfma_f64_kernel(const uint16_t* __restrict__ src,
+                                                                       const uint16_t* __restrict__ R, int M, int K,
+                                                                       double* __restrict__ dst, const float* __restrict__ ps,
+                                                                       int row_begin) {
     constexpr int KS = 64;                          // k per step
     constexpr int XS = 144, RS = 288;               // row strides in bytes
     constexpr int XT = MR * XS, RT = KS * RS;       // tile bytes
@@ -668,7 +667,6 @@ __global__ __launch_bounds__(256, 2) void blockdiag_rotate_mfma_f64_kernel(const
     const int t = threadIdx.x, lane = t % 64, wv = t / 64;
     const int wm = wv / 2, wn = wv % 2;
     const int row0 = row_begin + blockIdx.y * MR, col0 = blockIdx.x * MT_;
-    const int g = col0 / B, kbase = g * B, cb = col0 - kbase;
     v4d acc[RI][4];
 #pragma unroll
     for (int i = 0; i < RI; ++i)
@@ -683,7 +681,7 @@ __global__ __launch_bounds__(256, 2) void blockdiag_rotate_mfma_f64_kernel(const
         const int c = t + 256 * i, row = c / XCH, cc = c % XCH;
         int grow = row0 + row;
         if (grow >= M) grow = M - 1;
-        xsrc[i] = reinterpret_cast<const unsigned char*>(src) + ((size_t)grow * K + kbase) * XE + cc * 16;
+        xsrc[i] = reinterpret_cast<const unsigned char*>(src) + (size_t)grow * K * XE + cc * 16;
         xdst[i] = row * XS + cc * 16;
     }
     const unsigned char* rsrc[RL];
@@ -691,16 +689,16 @@ __global__ __launch_bounds__(256, 2) void blockdiag_rotate_mfma_f64_kernel(const
 #pragma unroll
     for (int i = 0; i < RL; ++i) {
         const int c = t + 256 * i, row = c / 16, cc = c % 16;
-        rsrc[i] = reinterpret_cast<const unsigned char*>(R + (size_t)g * B * B + (size_t)row * B + cb) + cc * 16;
+        rsrc[i] = reinterpret_cast<const unsigned char*>(R + (size_t)row * K + col0) + cc * 16;
         rdst[i] = row * RS + cc * 16;
     }
-    const int nk = B / KS;
+    const int nk = K / KS;
     {
 #pragma unroll
         for (int i = 0; i < XL; ++i) *reinterpret_cast<uint4*>(&Xs[0][xdst[i]]) = *reinterpret_cast<const uint4*>(xsrc[i]);
 #pragma unroll
         for (int i = 0; i < RL; ++i) *reinterpret_cast<uint4*>(&Rs[0][rdst[i]]) = *reinterpret_cast<const uint4*>(rsrc[i]);
-        if (t < KS) Ps[0][t] = ps ? ps[kbase + t] : 1.0f;
+        if (t < KS) Ps[0][t] = ps ? ps[t] : 1.0f;
     }
     __syncthreads();
     for (int kb = 0; kb < nk; ++kb) {
@@ -715,15 +713,12 @@ __global__ __launch_bounds__(256, 2) void blockdiag_rotate_mfma_f64_kernel(const
             xn2 = *reinterpret_cast<const uint4*>(xsrc[2] + (size_t)kn * KS * XE);
             xn3 = *reinterpret_cast<const uint4*>(xsrc[3] + (size_t)kn * KS * XE);
         }
-        uint4 rn0 = *reinterpret_cast<const uint4*>(rsrc[0] + (size_t)kn * KS * B * 2);
-        uint4 rn1 = *reinterpret_cast<const uint4*>(rsrc[1] + (size_t)kn * KS * B * 2);
-        uint4 rn2 = rn0, rn3 = rn0;
-        if constexpr (RL == 4) {
-            rn2 = *reinterpret_cast<const uint4*>(rsrc[2] + (size_t)kn * KS * B * 2);
-            rn3 = *reinterpret_cast<const uint4*>(rsrc[3] + (size_t)kn * KS * B * 2);
-        }
+        uint4 rn0 = *reinterpret_cast<const uint4*>(rsrc[0] + (size_t)kn * KS * K * 2);
+        uint4 rn1 = *reinterpret_cast<const uint4*>(rsrc[1] + (size_t)kn * KS * K * 2);
+        uint4 rn2 = *reinterpret_cast<const uint4*>(rsrc[2] + (size_t)kn * KS * K * 2);
+        uint4 rn3 = *reinterpret_cast<const uint4*>(rsrc[3] + (size_t)kn * KS * K * 2);
         float pn = 1.0f;
-        if (ps && t < KS) pn = ps[kbase + kn * KS + t];
+        if (ps && t < KS) pn = ps[kn * KS + t];
         const unsigned char* xa = &Xs[cur][(wm * (MR / 2) + lane % 16) * XS + (lane / 16) * XE];
         const unsigned char* rb = &Rs[cur][(lane / 16) * RS + (wn * 64 + lane % 16) * 2];
 #pragma unroll 2
@@ -759,10 +754,8 @@ __global__ __launch_bounds__(256, 2) void blockdiag_rotate_mfma_f64_kernel(const
             }
             *reinterpret_cast<uint4*>(rw + rdst[0]) = rn0;
             *reinterpret_cast<uint4*>(rw + rdst[1]) = rn1;
-            if constexpr (RL == 4) {
-                *reinterpret_cast<uint4*>(rw + rdst[2]) = rn2;
-                *reinterpret_cast<uint4*>(rw + rdst[3]) = rn3;
-            }
+            *reinterpret_cast<uint4*>(rw + rdst[2]) = rn2;
+            *reinterpret_cast<uint4*>(rw + rdst[3]) = rn3;
             if (t < KS) Ps[cur ^ 1][t] = pn;
         }
         __syncthreads();
@@ -1367,12 +1360,12 @@ hipError_t launch_dense_rotate_quant(hipStream_t st, const uint16_t* X, const ui
         int full_m = tiles_m;
         if (tiles > resident && tiles < 4L * resident && tiles % resident != 0 && tiles % resident < resident / 2)
             full_m = (int)((tiles / resident) * resident / tiles_n);
-        hipLaunchKernelGGL((blockdiag_rotate_mfma_f64_kernel<MT_>), dim3(tiles_n, full_m), dim3(256), 0, st, X, R, M, K,
-                           K, U, prescale, 0);
+        hipLaunchKernelGGL((dense_rotate_mfma_f64_kernel<MT_>), dim3(tiles_n, full_m), dim3(256), 0, st, X, R, M, K, U,
+                           prescale, 0);
         if (full_m < tiles_m) {
             const int row_begin = full_m * MT_;
-            hipLaunchKernelGGL((blockdiag_rotate_mfma_f64_kernel<64>), dim3(tiles_n, (M - row_begin + 63) / 64),
-                               dim3(256), 0, st, X, R, M, K, K, U, prescale, row_begin);
+            hipLaunchKernelGGL((dense_rotate_mfma_f64_kernel<64>), dim3(tiles_n, (M - row_begin + 63) / 64),
+                               dim3(256), 0, st, X, R, M, K, U, prescale, row_begin);
         }
     } else {
         dim3 grid(K / DT, (M + DT - 1) / DT);
