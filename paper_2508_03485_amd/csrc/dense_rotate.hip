@@ -597,11 +597,6 @@ __global__ __launch_bounds__(256) void dense_row_candidates_kernel(const uint16_
 // in flight while the current ones are summed.
 constexpr int XE_ROW = 144, XE_BUF = 64 * XE_ROW;        // one operand's staging buffer of a wave (9216 bytes)
 
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 struct Pieces {
     v4u x[8], r[8];
 };
@@ -658,7 +653,7 @@ __device__ __forceinline__ double exact_element_wave(const uint16_t* X, const ui
 #pragma unroll
             for (int i = 0; i < 8; ++i) xv[i] = nxt.x[i];
         }
-        wave_lds_sync();
+        wave_sync();
         nxt = load_pieces(xp, rp, (size_t)(b + AHEAD < nb ? b + AHEAD : b) * 128);     // past the end: a harmless re-read
         asm volatile("" ::: "memory");                   // keeps these loads ahead of the arithmetic below
         __builtin_amdgcn_sched_barrier(0);
@@ -667,7 +662,7 @@ __device__ __forceinline__ double exact_element_wave(const uint16_t* X, const ui
             if (!XDIRECT) xv[i] = *reinterpret_cast<const v4u*>(xs + rd + i * 16);
             rv[i] = *reinterpret_cast<const v4u*>(rs + rd + i * 16);
         }
-        wave_lds_sync();                                 // the reads are issued before the next batch is staged
+        wave_sync();                                 // the reads are issued before the next batch is staged
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll

@@ -10,6 +10,12 @@ namespace lrq {
 
 inline size_t round256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// Orders a wave's own LDS writes before its own later LDS reads (the LDS pipe serves one wave's requests in order; this
+// only stops the compiler from moving accesses across it).  Enough for LDS regions that one wave alone uses.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 // ---- launchers implemented in the .hip files; each returns hipGetLastError() after the launch ----
 

@@ -71,13 +71,6 @@ __device__ __forceinline__ unsigned decode_dword(const BRaw<BITS>& raw, const un
     }
 }
 
-// Orders a wave's own LDS writes before its own later LDS reads (the LDS pipe serves one wave's requests in
-// order; this only stops the compiler from moving accesses across it).  Enough for wave-private LDS regions.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // two floats -> two bf16 (round-to-nearest-even, v_cvt_pk_bf16_f32), a in the low half
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));

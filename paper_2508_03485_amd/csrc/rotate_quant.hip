@@ -325,13 +325,6 @@ __global__ __launch_bounds__(640) void hadamard_quant_e32_kernel(const uint16_t*
     }
 }
 
-// Orders a wave's own LDS writes before its own later LDS reads (the LDS pipe serves one wave's requests in order; this
-// only stops the compiler from moving accesses across it).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // ---------------------------------------------------------------- two-pass Hadamard, 256 <= h <= 4096
 // Pass 1: every lane owns 32 contiguous elements (stages 0..4 in registers).  Pass 2: the G = h / 32 lanes
 // of a block exchange the block transposed through LDS - a lane then owns, for its 32 / G (at least one)
