@@ -232,7 +232,9 @@ int lrq_ars_dense_diagnostics(int M, int K, size_t offsets[4]);
 size_t lrq_ars_dense_prepared_bytes(int K);
 int lrq_ars_dense_prepare(void* stream, const void* R, int K, void* prepared, size_t prepared_bytes);
 
-/* Workspace of lrq_qlinear (bytes): activation codes, scales and rotation scratch. */
+/* Workspace of lrq_qlinear (bytes): activation codes, scales and rotation scratch, and for large products with 4-bit weights room for
+ * the decoded weights (about N * K bytes) unless the rotation scratch holds them.  A workspace without that room
+ * (lrq_workspace_bytes for N = 0) is accepted: the call then decodes inside the GEMM, slower, with the same outputs. */
 size_t lrq_workspace_bytes(int M, int N, int K, const lrq_rotation* rot, int act_bits);
 
 /*
@@ -246,7 +248,8 @@ size_t lrq_workspace_bytes(int M, int N, int K, const lrq_rotation* rot, int act
  *   bias       float [N] or NULL.
  *   out_dtype  LRQ_OUT_BF16 (round-to-nearest-even) | LRQ_OUT_FP32.       Y: [M, N] out.
  *   ws         device workspace of at least lrq_workspace_bytes(M, N, K, rot, act_bits) bytes.
- * Runs as the rotate+quantize kernel(s) followed by the decode+MFMA GEMM kernel on the same stream.
+ * Runs as the rotate+quantize kernel(s) followed by the decode+MFMA GEMM kernel (large products: a decoding kernel and an int8
+ * GEMM) on the same stream.
  * Requires K % 64 == 0.
  */
 int lrq_qlinear(void* stream, const void* X, int M, int K, const lrq_rotation* rot, int act_bits,
@@ -276,7 +279,8 @@ int lrq_qlinear_static(void* stream, const void* X, int M, int K, const lrq_rota
 
 /*
  * lrq_qgemm - the GEMM + rescale stage of lrq_qlinear alone, on activation codes already produced by
- * lrq_ars_rotate_quant (q int8 [M,K], scale float [M]).  Same formula, same constraints; no workspace.
+ * lrq_ars_rotate_quant (q int8 [M,K], scale float [M]).  Same formula, same constraints; no workspace, so the weights are
+ * always decoded inside the GEMM.
  */
 int lrq_qgemm(void* stream, const int8_t* q, const float* scale, int M, int K,
               const lrq_tlq_weight* w, const float* bias, int out_dtype, void* Y);

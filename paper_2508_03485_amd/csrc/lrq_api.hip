@@ -270,10 +270,30 @@ int lrq_ars_rotate_quant_asym(void* stream, const void* X, int M, int K, const l
     return ars_impl(stream, X, M, K, rot, act_bits, q, scale, zero, true, ws, ws_bytes);
 }
 
+// What every linear call needs: codes, scales, rotation scratch, zero-points.
+static size_t base_workspace(int M, int K, const lrq_rotation* rot, bool asym) {
+    return round256((size_t)M * K) + round256((size_t)M * sizeof(float)) + ars_layout(M, K, rot).total +
+           (asym ? round256((size_t)M * sizeof(int32_t)) : 0);
+}
+
+// Whether the decoded weights go where the rotation's scratch was (LRQ_ROT_DENSE_F64 leaves u there for its caller).
+static bool wide_in_scratch(int M, int K, const lrq_rotation* rot, size_t bytes) {
+    return rot && rot->kind != LRQ_ROT_DENSE_F64 && ars_layout(M, K, rot).total >= bytes;
+}
+
+// Room for the weights that the wide GEMM reads decoded, beyond base_workspace: none where that kernel serves no form of the
+// product, or where the rotation's scratch, free by then, holds them.
+static size_t wide_workspace(int M, int N, int K, const lrq_rotation* rot) {
+    if (N <= 0 || K % lrq::kGemmBlockK != 0) return 0;
+    const size_t bytes = lrq::qgemm_wide_bytes(N, K);
+    if (wide_in_scratch(M, K, rot, bytes)) return 0;
+    return lrq::qgemm_wide_rows(M, N, K, 4, false, false) > 0 || lrq::qgemm_wide_rows(M, N, K, 4, true, false) > 0 ? round256(bytes) : 0;
+}
+
 size_t lrq_workspace_bytes(int M, int N, int K, const lrq_rotation* rot, int act_bits) {
-    (void)N; (void)act_bits;
+    (void)act_bits;
     if (M <= 0 || K <= 0) return 0;
-    return round256((size_t)M * K) + round256((size_t)M * sizeof(float)) + ars_layout(M, K, rot).total;
+    return base_workspace(M, K, rot, false) + wide_workspace(M, N, K, rot);
 }
 
 size_t lrq_workspace_bytes_asym(int M, int N, int K, const lrq_rotation* rot, int act_bits) {
@@ -350,9 +370,10 @@ static int qlinear_impl(void* stream, const void* X, int M, int K, const lrq_rot
     if (!Y || !aligned16(Y) || w->K != K) return LRQ_EINVAL;
     if (out_dtype != LRQ_OUT_BF16 && out_dtype != LRQ_OUT_FP32) return LRQ_EUNSUPPORTED;
     if (K % lrq::kGemmBlockK != 0) return LRQ_EUNSUPPORTED;
-    const size_t need = asym ? lrq_workspace_bytes_asym(M, w->N, K, rot, act_bits) : lrq_workspace_bytes(M, w->N, K, rot, act_bits);
+    const size_t need = base_workspace(M, K, rot, asym);
     if (!ws || ws_bytes < need || !aligned16(ws)) return LRQ_EWORKSPACE;
-    // workspace: q | scale | rotation scratch | zero (zero-point form only)
+    // workspace: q | scale | rotation scratch | zero (zero-point form only) | decoded weights (wide GEMM only; in the rotation scratch
+    // where they fit; without room for them the other GEMM kernels run)
     char* base = static_cast<char*>(ws);
     int8_t* q = reinterpret_cast<int8_t*>(base);
     float* scale = reinterpret_cast<float*>(base + round256((size_t)M * K));
@@ -361,8 +382,20 @@ static int qlinear_impl(void* stream, const void* X, int M, int K, const lrq_rot
     hipStream_t s = static_cast<hipStream_t>(stream);
     st = run_rotate_quant(s, X, M, K, rot, act_bits, q, scale, zero, rot_ws);
     if (st != LRQ_OK) return st;
-    hipError_t e = kind == Gemm::kLevels ? lrq::launch_qgemm_levels(s, q, scale, M, K, *w, bias, out_dtype, Y)
-                                         : lrq::launch_qgemm(s, q, scale, zero, M, K, *w, bias, out_dtype, Y);
+    hipError_t e;
+    if (kind == Gemm::kLevels) {
+        e = lrq::launch_qgemm_levels(s, q, scale, M, K, *w, bias, out_dtype, Y);
+    } else {
+        void* wide = nullptr;
+        const size_t bytes = lrq::qgemm_wide_bytes(w->N, K);
+        if (wide_in_scratch(M, K, rot, bytes)) wide = rot_ws;
+        else if (ws_bytes >= need + bytes) wide = base + need;
+        const int rows = wide ? lrq::qgemm_wide_rows(M, w->N, K, w->bits, asym, out_dtype == LRQ_OUT_FP32) : 0;
+        if (rows > 0)
+            e = lrq::launch_qgemm_wide(s, q, scale, zero, M, K, *w, bias, Y, wide, rows);
+        else
+            e = lrq::launch_qgemm(s, q, scale, zero, M, K, *w, bias, out_dtype, Y);
+    }
     return e == hipSuccess ? LRQ_OK : LRQ_EHIP;
 }
 
@@ -497,7 +530,7 @@ int lrq_qlinear_fp8(void* stream, const void* X, int M, int K, const lrq_rotatio
     st = check_gemm_common(w, K, out_dtype);
     if (st != LRQ_OK) return st;
     if (!w->lut_fp8 || !w->wscale_fp8) return LRQ_EINVAL;
-    if (!ws || ws_bytes < lrq_workspace_bytes(M, w->N, K, rot, 4) || !aligned16(ws)) return LRQ_EWORKSPACE;
+    if (!ws || ws_bytes < base_workspace(M, K, rot, false) || !aligned16(ws)) return LRQ_EWORKSPACE;
     char* base = static_cast<char*>(ws);
     uint8_t* q8 = reinterpret_cast<uint8_t*>(base);
     float* scale = reinterpret_cast<float*>(base + round256((size_t)M * K));
@@ -519,7 +552,7 @@ int lrq_qlinear_static(void* stream, const void* X, int M, int K, const lrq_rota
                        const lrq_tlq_weight* w, const float* bias, int out_dtype, void* Y) {
     // sizes first: a layer that does not fit is refused before anything else is looked at or launched
     if (M <= 0 || K <= 0 || !w || w->N <= 0) return LRQ_EINVAL;
-    if (lrq_workspace_bytes(M, w->N, K, rot, act_bits) > kStaticScratchBytes) return LRQ_ESCRATCH;
+    if (base_workspace(M, K, rot, false) > kStaticScratchBytes) return LRQ_ESCRATCH;
     void* ws = nullptr;
     const int st = static_scratch(&ws);
     if (st != LRQ_OK) return st;

@@ -98,9 +98,18 @@ hipError_t launch_tlq_quantize_pack(hipStream_t st, const float* W, int N, int K
 hipError_t launch_qgemm(hipStream_t st, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
                         const lrq_tlq_weight& w, const float* bias, int out_dtype, void* Y, bool packed4 = false);
 
-// The kernel launch_qgemm takes: rows and columns of one workgroup's outputs (32 columns: the kernel that splits K).
-struct GemmShape { int rows, cols; };
+// The kernel launch_qgemm takes: rows and columns of one workgroup's outputs (32 columns: the kernel that splits K), and its
+// predicted time.
+struct GemmShape { int rows, cols; float us; };
 GemmShape qgemm_shape(int M, int N, int K, int bits, bool zero_point, bool packed4, bool fp32);
+
+// The same product with the weights decoded once, into qgemm_wide_bytes(N, K) bytes of workspace (16-byte aligned), and tiles of
+// rows x 256, bf16 outputs (qgemm_wide.hip).  qgemm_wide_rows: the rows with the smallest predicted time, 0 where the kernel launch_qgemm takes is
+// predicted to be as fast or the shape is not served.
+size_t qgemm_wide_bytes(int N, int K);
+int qgemm_wide_rows(int M, int N, int K, int bits, bool zero_point, bool fp32);
+hipError_t launch_qgemm_wide(hipStream_t st, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
+                             const lrq_tlq_weight& w, const float* bias, void* Y, void* ws, int rows);
 
 // Y = scale_t * sum_k q * levels (+ bias) on the bf16 matrix cores; w.levels must be set.
 hipError_t launch_qgemm_levels(hipStream_t st, const int8_t* q, const float* scale, int M, int K, const lrq_tlq_weight& w,

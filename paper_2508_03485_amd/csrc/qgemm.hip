@@ -9,7 +9,7 @@
 // this instruction and 3.3 POP/s with v_mfma_i32_32x32x32_i8: the matrix pipe is power-limited and this shape draws
 // less per operation.)
 // The epilogue rescales in fp32 and goes through LDS so that every lane stores 16 contiguous bytes.
-#include "lrq_internal.h"
+#include "qgemm_common.h"
 
 namespace lrq {
 namespace {
@@ -69,24 +69,6 @@ __device__ __forceinline__ unsigned decode_dword(const BRaw<BITS>& raw, const un
         const unsigned idx = (g % 2 == 0 ? w : (w >> 4)) & 0x07070707u;
         return perm(L[1], L[0], idx);
     }
-}
-
-// two floats -> two bf16 (round-to-nearest-even, v_cvt_pk_bf16_f32), a in the low half
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
-    const f32x2 v = {a, b};
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
-}
-
-// fp32(a + zero * colsum).  The sum can exceed 32 bits.  Up to kZpF64K channels it is a whole number below 2^53 (|zero| <= 2^31,
-// |colsum| <= 127 K, |a| <= 127^2 K), so fp64 holds it exactly and the conversion rounds it once, as it would a 64-bit integer; that
-// takes three instructions where the 64-bit multiply and conversion take about twenty (2333 x 1152 -> 1091: 2 us of a 15 us
-// launch).  Longer rows take the integers, in a kernel of their own (ZP64), so that the others do not carry them.
-constexpr int kZpF64K = 32768;
-__device__ __forceinline__ float zp_sum(int a, double zero, double colsum) { return (float)fma(zero, colsum, (double)a); }
-__device__ __forceinline__ float zp_sum64(int a, double zero, double colsum) {
-    return (float)((long long)a + (long long)(int)zero * (long long)(int)colsum);
 }
 
 // One K block of the main loop.  The A tiles rotate through three LDS buffers: block kb multiplies from `cur`
@@ -657,13 +639,12 @@ constexpr long kSplitOutputs = 1600000;
 
 // cols == 32: the split-K kernel
 GemmShape qgemm_shape(int M, int N, int K, int bits, bool zero_point, bool packed4, bool fp32) {
-    if (zero_point && K > kZpF64K) return {128, 128};       // the only shape that kernel is built in
+    if (zero_point && K > kZpF64K) return {128, 128, 0.0f};       // the only shape that kernel is built in
     const float kb = (float)(K / BK), packed = packed4 ? 1.0f : 0.0f;
     const float ragged = N % (fp32 ? 4 : 8) != 0 ? 1.0f : 0.0f;
-    GemmShape best = {};
-    float best_us = INFINITY;
+    GemmShape best = {0, 0, INFINITY};
     auto consider = [&](int rows, int cols, float us) {
-        if (us < best_us) { best = {rows, cols}; best_us = us; }
+        if (us < best.us) best = {rows, cols, us};
     };
     for (const TileCost& c : kTileCost[bits - 3]) {
         const long n = (((long)M + c.rows - 1) / c.rows * (((long)N + c.cols - 1) / c.cols) + 255) / 256;

@@ -828,6 +828,45 @@ def test_qgemm_tile_shapes(lrq, M, N, K, w_bits, tile, form):
         assert torch.equal(y, ref.to(dt))
 
 
+@pytest.mark.parametrize("M,N,K,w_bits,asym", [
+    (14009, 1672, 448, 4, False),      # 192 rows, two tiles to some workgroups, odd number of K blocks, cut both ways
+    (9734, 1232, 1152, 4, True),       # 192 rows, zero-points, one round, N no multiple of a channel group
+    (8708, 3224, 320, 4, False),       # 224 rows, five K blocks: the next tile's loads start in the third
+    (16484, 656, 1536, 4, True),       # 224 rows, zero-points
+    (19991, 2216, 320, 4, False),      # 256 rows, three rounds
+    (19174, 1288, 3072, 4, True),      # 256 rows, zero-points
+])
+def test_qlinear_with_weights_decoded_once(lrq, M, N, K, w_bits, asym):
+    """The wide GEMM of lrq_qlinear (256-column tiles on decoded weights in the workspace): the integer sums are exact in fp64 and the
+    rescale is three fp32 operations in a stated order, so outputs are compared bit for bit; a workspace without room for
+    the weights gives the same outputs through the other kernels."""
+    import torch
+    print(f"case wide M={M} N={N} K={K} W{w_bits} asym={asym}", flush=True)
+    gd = to_dev(np.array([1.0, 1.5], np.float32))
+    w = lrq.tlq_quantize_pack(to_dev(synth.make_weights(N, K, (911, N, K))), w_bits, 7, gd, gd)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    X = (torch.randn(M, K, generator=gen, device="cuda") + 0.5).to(torch.bfloat16)
+    bias = torch.randn(N, generator=gen, device="cuda")
+    rot = lrq.Rotation("none")
+    full = lrq.workspace_bytes(M, N, K, rot, 8, asym=asym)
+    base = sum((v + 255) // 256 * 256 for v in (M * K, 4 * M, 4 * M if asym else 0))
+    assert full >= base + N * K
+    ws = torch.full((full,), 90, dtype=torch.uint8, device="cuda")
+    y = lrq.qlinear(X, rot, 8, w, bias=bias, workspace=ws, asym=asym)
+    assert (ws[base:base + N * K] != 90).any()                           # the wide kernel ran: it has written the decoded weights
+    part = torch.full((base,), 90, dtype=torch.uint8, device="cuda")
+    assert torch.equal(lrq.qlinear(X, rot, 8, w, bias=bias, workspace=part, asym=asym), y)
+    q, scale, *zero = lrq.ars_rotate_quant(X, rot, 8, asym=asym)
+    lut = w.lut.cpu().numpy().astype(np.int64)
+    codes = oracle.unpack_codes(w.codes.cpu().numpy(), w_bits, K).astype(np.int64) & (2 ** w_bits - 1)
+    wv = np.take_along_axis(lut, codes, axis=1).astype(np.float64)
+    total = q.double() @ to_dev(wv).T.contiguous()
+    if asym:
+        total += zero[0].double()[:, None] * to_dev(wv.sum(axis=1))[None, :]
+    ref = total.to(torch.float32) * scale[:, None] * w.wscale[None, :] + bias[None, :]
+    assert torch.equal(y, ref.to(torch.bfloat16))
+
+
 @pytest.mark.parametrize("M,N,K,w_bits,a_bits,I", [
     (256, 1152, 1152, 4, 8, 7),   # config 1
     (300, 352, 1152, 4, 8, 7),    # ragged M, N not a multiple of the workgroup tile
