@@ -15,8 +15,8 @@
 //
 // Error bound.  A run of m = CHUNK / 16 chained v_mfma_f32_32x32x16_bf16 starts from a zero accumulator.  Model of one
 // instruction, D = C + sum_{i<16} a_i b_i: every addend is aligned to the largest one and truncated below 2^-26 of it, the
-// sum is rounded or truncated to 24 bits: |D - exact| <= (17 * 2^-26 + 2^-23) * (|C| + sum |a_i b_i|) < ETA * (|C| + sum |a_i b_i|),
-// ETA = 2^-21 (measured on this chip: at most 5.8 * 2^-24 over adversarial exponent mixes).  Over a run, |C| is at most
+// sum is rounded or truncated to 24 bits: |D - exact| <= ETA * (|C| + sum |a_i b_i|), ETA = 17 * 2^-26 + 2^-23 = 6.25 * 2^-24
+// (measured on this chip: at most 5.8 * 2^-24 over adversarial exponent mixes).  Over a run, |C| is at most
 // the sum of |a b| of the run's earlier steps, so the run's error is at most ETA * m * S_run.  GROUP runs are then summed
 // in fp32 by ordinary vector additions (round to nearest: each errs by at most 2^-24 of its result, which is at most the
 // group's sum of |a b|): (GROUP - 1) * 2^-24 * S_group.  Groups are added to an fp64 accumulator (exact to 2^-53).  In all
@@ -587,113 +587,34 @@ __global__ __launch_bounds__(256) void dense_row_candidates_kernel(const uint16_
     }
 }
 
-// ---- the definition's chain for single elements: u = sum over ascending k of x[row, k] * R[k, col], one fused
-// multiply-add per term (the products are exact).  Every lane of a wave owns one element, but the wave fetches the
-// operands together: in one load instruction eight neighbouring lanes read the eight 16-byte pieces of one element's
-// next 128 bytes (64 k) of its x row / R column (Rt holds R's columns contiguously), so every cache line is requested
-// once and used in full - a lane reading its own stream 16 bytes at a time asks for each line eight times over and the
-// chain then runs at a tenth of its arithmetic rate.  The pieces go through a wave-private LDS buffer (element rows
-// padded to 144 bytes: conflict-free 16-byte reads) to the lane that owns the element; the loads of the next 64 k are
-// in flight while the current ones are summed.
-constexpr int XE_ROW = 144, XE_BUF = 64 * XE_ROW;        // one operand's staging buffer of a wave (9216 bytes)
+// ---- amax candidates: the definition's chain, u = sum over ascending k of x[row, k] * R[k, col], every addition rounded.
+// A chain is serial and there is about one per row, so few waves run and a chain's latency is the kernel's time where the operands'
+// traffic is not.  Eight lanes share an element: each reads one 16-byte piece of the element's next 64 k of its x row and
+// R column (Rt holds R's columns contiguously; the eight pieces are one cache line) and forms its products (exact in fp64), then
+// the sum goes from lane to lane, each adding its own products; the other lanes' sums mean nothing meanwhile.  A k costs two vector
+// instructions that way instead of five and no trip through LDS; XA_DEPTH lines of an element are in flight.  A lane per element, the
+// operands handed out through LDS, took 67.3 us at 35100 x 3072 (432 MB at 6.4 TB/s) and 23.8 us at 8192 x 1152; this takes 71 and
+// 12.3 us.  (Products through LDS to a wave that only adds: 107 and 14.7 us.)
+constexpr int XA_DEPTH = 6;
 
-struct Pieces {
-    v4u x[8], r[8];
-};
-// (xp / rp are not __restrict__: see dense_rotate_bf16_kernel)
-__device__ __forceinline__ Pieces load_pieces(const unsigned char* const (&xp)[8], const unsigned char* const (&rp)[8], size_t off) {
-    Pieces p;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        p.x[q] = *reinterpret_cast<const v4u*>(xp[q] + off);
-        p.r[q] = *reinterpret_cast<const v4u*>(rp[q] + off);
-    }
-    return p;
+// DPP move of a double within rows of 16 lanes (0x111: from the lane below, 0x100 + n: from n lanes above)
+template <int CTRL>
+__device__ __forceinline__ double row_shift(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
 }
 
-// All 64 lanes must call this together (lanes without an element pass any valid row / col and ignore the result).
-// K % 64 == 0.  lds: this wave's 2 * XE_BUF bytes (XE_BUF with XDIRECT).
-// XDIRECT: every lane reads its own x row itself, 16 bytes at a time, and only the R columns go through LDS - for waves whose
-// neighbouring lanes share rows (the list of undecided elements keeps a row's entries together, about nine to a row at
-// config 4): lanes with the same address are served by one request, so the cooperative fetch buys nothing for x there
-// and its trip through LDS is half of the kernel's LDS traffic.
-// AHEAD (1 or 2; 2 needs K % 128 == 0): batches of 64 k in flight.  Two where few waves run (the amax candidates: 65.8 -> 63.9 us
-// at 35100 x 3072), one where many do and registers decide how many (the undecided elements, three waves per SIMD instead of
-// two: 270 -> 257 us).  Either way a wave spends about 50 cycles on a k; products formed in fp32
-// (exact in range, one conversion per term instead of two) measured the same, so the conversions are not what it waits for.
-template <bool XDIRECT, int AHEAD>
-__device__ __forceinline__ double exact_element_wave(const uint16_t* X, const uint16_t* Rt, int K, int row, int col,
-                                                     unsigned char* lds) {
-    const int lane = threadIdx.x % kWave;
-    const unsigned char* xp[8];
-    const unsigned char* rp[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int e = 8 * q + lane / 8;                 // the element whose piece (lane % 8) this lane fetches in load q
-        const int er = __shfl(row, e, kWave), ec = __shfl(col, e, kWave);
-        xp[q] = XDIRECT ? reinterpret_cast<const unsigned char*>(X + (size_t)row * K) + q * 16
-                        : reinterpret_cast<const unsigned char*>(X + (size_t)er * K) + (lane % 8) * 16;
-        rp[q] = reinterpret_cast<const unsigned char*>(Rt + (size_t)ec * K) + (lane % 8) * 16;
-    }
-    unsigned char* xs = lds;
-    unsigned char* rs = XDIRECT ? lds : lds + XE_BUF;
-    const int wr = (lane / 8) * XE_ROW + (lane % 8) * 16;        // + 8 q rows for load q
-    const int rd = lane * XE_ROW;
-    const int nb = K / 64;
-    double u = 0.0;
-    auto batch = [&](Pieces& nxt, int b) {
-        // stage batch b (the previous batch was read into registers before this point)
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            if (!XDIRECT) *reinterpret_cast<v4u*>(xs + wr + 8 * q * XE_ROW) = nxt.x[q];
-            *reinterpret_cast<v4u*>(rs + wr + 8 * q * XE_ROW) = nxt.r[q];
-        }
-        v4u xv[8], rv[8];
-        if (XDIRECT) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) xv[i] = nxt.x[i];
-        }
-        wave_sync();
-        nxt = load_pieces(xp, rp, (size_t)(b + AHEAD < nb ? b + AHEAD : b) * 128);     // past the end: a harmless re-read
-        asm volatile("" ::: "memory");                   // keeps these loads ahead of the arithmetic below
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (!XDIRECT) xv[i] = *reinterpret_cast<const v4u*>(xs + rd + i * 16);
-            rv[i] = *reinterpret_cast<const v4u*>(rs + rd + i * 16);
-        }
-        wave_sync();                                 // the reads are issued before the next batch is staged
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                u = fma((double)bf16_lo(xv[i][d]), (double)bf16_lo(rv[i][d]), u);
-                u = fma((double)bf16_hi(xv[i][d]), (double)bf16_hi(rv[i][d]), u);
-            }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    Pieces p0 = load_pieces(xp, rp, 0);
-    if constexpr (AHEAD == 1) {
-        for (int b = 0; b < nb; ++b) batch(p0, b);
-    } else {
-        Pieces p1 = load_pieces(xp, rp, 128);
-        for (int b = 0; b < nb; b += 2) {
-            batch(p0, b);
-            batch(p1, b + 1);
-        }
-    }
-    return u;
-}
-
-// amax candidates: thread i -> slot i / M of row i % M (slot 0 of every row first, so that the waves are full); the
+// thread group i of slot-major order -> slot i / M of row i % M (slot 0 of every row first, so that the waves are full); the
 // zero-point form runs the slots of side 0 (maximum), then those of side 1 (minimum, kept as the maximum of -u).
-template <bool ASYM>
+template <bool ASYM, int LPA>
 __global__ __launch_bounds__(256) void dense_exact_amax_kernel(const uint16_t* X, const uint16_t* Rt, int M, int K,
                                                                const int* __restrict__ ccount, const uint16_t* __restrict__ cidx,
                                                                unsigned long long* __restrict__ amax_bits, int* __restrict__ nwhole) {
-    __shared__ __attribute__((aligned(16))) unsigned char stage[4 * 2 * XE_BUF];
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i == 0) *nwhole = 0;                             // for dense_quant_flag_kernel
+    constexpr int PP = 8 / LPA, DEPTH = XA_DEPTH / PP;       // pieces of a lane, lines in flight
+    const int p = threadIdx.x % LPA;
+    const long i = ((long)blockIdx.x * 256 + threadIdx.x) / LPA;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *nwhole = 0;                // for dense_quant_kernel
     int row = 0, col = 0, side = 0;
     bool have = false;
     if (i < (long)M * CAPC * (ASYM ? 2 : 1)) {
@@ -705,14 +626,179 @@ __global__ __launch_bounds__(256) void dense_exact_amax_kernel(const uint16_t* X
         col = have ? (int)cidx[((size_t)row * 2 + side) * CAPC + slot] : 0;
     }
     if (__ballot(have) == 0ull) return;                  // nothing in this wave
-    const double u = exact_element_wave<false, 2>(X, Rt, K, row, col, stage + (threadIdx.x / kWave) * 2 * XE_BUF);
-    if (have) {
+    if (!have) row = 0;
+    const uint4* xp = reinterpret_cast<const uint4*>(X + (size_t)row * K) + p * PP;
+    const uint4* rp = reinterpret_cast<const uint4*>(Rt + (size_t)col * K) + p * PP;
+    const int nb = K / 64;
+    uint4 xr[DEPTH][PP], rr[DEPTH][PP];
+    auto load = [&](int d, int b) {
+        const int at = (b < nb ? b : nb - 1) * 8;        // past the end: a harmless re-read
+#pragma unroll
+        for (int c = 0; c < PP; ++c) {
+            xr[d][c] = xp[at + c];
+            rr[d][c] = rp[at + c];
+        }
+    };
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) load(d, d);
+    double u = 0.0;
+    for (int b0 = 0; b0 < nb; b0 += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            if (b0 + d < nb) {
+                double v[8 * PP];
+#pragma unroll
+                for (int c = 0; c < PP; ++c) {
+                    const unsigned xw[4] = {xr[d][c].x, xr[d][c].y, xr[d][c].z, xr[d][c].w};
+                    const unsigned rw[4] = {rr[d][c].x, rr[d][c].y, rr[d][c].z, rr[d][c].w};
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        v[8 * c + 2 * w] = (double)bf16_lo(xw[w]) * (double)bf16_lo(rw[w]);
+                        v[8 * c + 2 * w + 1] = (double)bf16_hi(xw[w]) * (double)bf16_hi(rw[w]);
+                    }
+                }
+                load(d, b0 + d + DEPTH);
+#pragma unroll
+                for (int l = 0; l < LPA; ++l) {
+#pragma unroll
+                    for (int w = 0; w < 8 * PP; ++w) u += v[w];
+                    u = l < LPA - 1 ? row_shift<0x111>(u) : row_shift<0x100 + LPA - 1>(u);      // to the next lane; from the last back to the first
+                }
+            }
+        }
+    }
+    if (have && p == 0) {
         if constexpr (ASYM) atomicMax(&amax_bits[2 * (size_t)row + side], okey(side == 0 ? u : -u));
         else atomicMax(&amax_bits[2 * (size_t)row], (unsigned long long)__double_as_longlong(fabs(u)));
     }
 }
 
-// ---- codes from u~ with the exact amax (zero-point form: the exact maximum and minimum); the elements the bound leaves
+// ---- codes from u~ with the exact amax (zero-point form: the exact maximum and minimum), one wave per row.  The elements that the
+// bound leaves undecided are listed in LDS and settled right away: 16 lanes sum the products of one element in fp64, each every
+// sixteenth piece of 8 k.  That sum is not the definition's (its additions round in another order), but both lie within
+// K 2^-53 S of the real number, and that bound settles the code unless u inv comes within some 1e-11 of a half-integer; what is
+// left then (exact ties) runs the definition's chain, an element to a lane.  Rows with more undecided elements than capf go to a list
+// and are recomputed as a whole.  While some waves wait for operands (an element reads its R column, 2 K bytes, mostly from the
+// Infinity Cache), others stream u~: flagging, a prefix sum over the rows' counts and the chains for all undecided elements take 11.5 +
+// 4.7 + 25.8 us at 8192 x 1152 as kernels of their own (below), this one 15.2 us; where it is used: quant_in_one.
+template <bool ASYM>
+__global__ __launch_bounds__(256) void dense_quant_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Rt,
+                                                          const float* __restrict__ Ut, int M, int K, double qmax, double err_factor,
+                                                          const double* __restrict__ eps,
+                                                          const unsigned long long* __restrict__ amax_bits, int8_t* __restrict__ q,
+                                                          float* __restrict__ scale, int32_t* __restrict__ zero,
+                                                          int* __restrict__ fcount, int capf, int* __restrict__ mode,
+                                                          int* __restrict__ nwhole, int* __restrict__ whole) {
+    extern __shared__ uint16_t lds_idx[];       // per wave: capf undecided elements, capf ties
+    __shared__ int lds_cnt[4][2];
+    const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave, row = blockIdx.x * 4 + wv;
+    if (lane < 2) lds_cnt[wv][lane] = 0;
+    wave_sync();
+    if (row >= M) return;
+    if (mode[row]) {                            // recomputed as a whole later
+        if (lane == 0) {
+            fcount[row] = 0;
+            whole[atomicAdd(nwhole, 1)] = row;
+        }
+        return;
+    }
+    const RowQuant rq = row_quant<ASYM>(amax_bits[2 * (size_t)row], amax_bits[2 * (size_t)row + 1], qmax);
+    const double inv = rq.inv, e = eps[row];
+    const double keep = 0.5 - (e * inv * (1.0 + 1e-6) + 1e-12);            // |p - rint(p)| below this: the code is settled
+    const float4* us = reinterpret_cast<const float4*>(Ut + (size_t)row * K);
+    uint16_t* myidx = lds_idx + (size_t)wv * 2 * capf;
+    for (int c = lane; c < K / 8; c += kWave) {
+        const float4 v0 = us[2 * c], v1 = us[2 * c + 1];
+        const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        unsigned b[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const double p = (double)v[i] * inv;
+            double r = (p + kMagic) - kMagic;
+            if (!(fabs(p - r) < keep)) {
+                const int slot = atomicAdd(&lds_cnt[wv][0], 1);
+                if (slot < capf) myidx[slot] = (uint16_t)(c * 8 + i);
+            }
+            r = ASYM ? fmin(fmax(r - rq.zsub, -(qmax + 1.0)), qmax) : fmin(fmax(r, -qmax), qmax);
+            b[i] = (unsigned)__double2loint(r + kMagic) & 0xffu;
+        }
+        *reinterpret_cast<uint2*>(q + (size_t)row * K + (size_t)c * 8) =
+            make_uint2(b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24), b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24));
+    }
+    wave_sync();
+    const int n = lds_cnt[wv][0];
+    if (lane == 0) {
+        scale[row] = rq.scale;
+        if (ASYM) zero[row] = rq.izero;
+        fcount[row] = n > capf ? 0 : n;
+        if (n > capf) {
+            mode[row] = 1;
+            whole[atomicAdd(nwhole, 1)] = row;
+        }
+    }
+    if (n == 0 || n > capf) return;
+    // the byte stores below follow the stores above of other lanes to the same bytes
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    // two sums of at most K rounded additions each: 2 K 2^-53 S, S = e / err_factor
+    const double keep2 = 0.5 - (e / err_factor * ldexp((double)K, -52) * inv * (1.0 + 1e-6) + 1e-12);
+    constexpr int LPE = 16;                     // lanes that share an element
+    const int l = lane % LPE;
+    const uint4* xs = reinterpret_cast<const uint4*>(X + (size_t)row * K) + l;
+    for (int i0 = 0; i0 < n; i0 += 64 / LPE) {
+        const int i = i0 + lane / LPE;
+        const int col = (int)myidx[i < n ? i : n - 1];
+        const uint4* rs = reinterpret_cast<const uint4*>(Rt + (size_t)col * K) + l;
+        double u = 0.0;
+        constexpr int AHEAD = 3;
+        for (int c = 0; c < K / 8; c += LPE * AHEAD) {
+            uint4 xv[AHEAD], rv[AHEAD];
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) {
+                const int at = c + LPE * a < K / 8 ? c + LPE * a : c;        // past the end: not added
+                xv[a] = xs[at];
+                rv[a] = rs[at];
+            }
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) {
+                if (c + LPE * a < K / 8) {
+                    const unsigned xw[4] = {xv[a].x, xv[a].y, xv[a].z, xv[a].w}, rw[4] = {rv[a].x, rv[a].y, rv[a].z, rv[a].w};
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        u = fma((double)bf16_lo(xw[d]), (double)bf16_lo(rw[d]), u);
+                        u = fma((double)bf16_hi(xw[d]), (double)bf16_hi(rw[d]), u);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int o = LPE / 2; o > 0; o >>= 1) u += __shfl_xor(u, o, kWave);
+        const double p = u * inv, r = (p + kMagic) - kMagic;
+        if (l == 0 && i < n) {
+            if (fabs(p - r) < keep2) q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
+            else myidx[capf + atomicAdd(&lds_cnt[wv][1], 1)] = (uint16_t)col;
+        }
+    }
+    wave_sync();
+    const int ties = lds_cnt[wv][1];
+    for (int i = lane; i < ties; i += kWave) {
+        const int col = (int)myidx[capf + i];
+        const uint4* xr = reinterpret_cast<const uint4*>(X + (size_t)row * K);
+        const uint4* rr = reinterpret_cast<const uint4*>(Rt + (size_t)col * K);
+        double u = 0.0;
+        for (int c = 0; c < K / 8; ++c) {
+            const uint4 xv = xr[c], rv = rr[c];
+            const unsigned xw[4] = {xv.x, xv.y, xv.z, xv.w}, rw[4] = {rv.x, rv.y, rv.z, rv.w};
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                u = fma((double)bf16_lo(xw[d]), (double)bf16_lo(rw[d]), u);
+                u = fma((double)bf16_hi(xw[d]), (double)bf16_hi(rw[d]), u);
+            }
+        }
+        q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
+    }
+}
+
+// ---- the same with a list: codes from u~ with the exact amax (zero-point form: the exact maximum and minimum); the elements the bound leaves
 // undecided go to the row's list (one wave per row); rows to recompute as a whole go to a list of their own
 template <bool ASYM>
 __global__ __launch_bounds__(256) void dense_quant_flag_kernel(const float* __restrict__ Ut, int M, int K, double qmax,
@@ -844,6 +930,79 @@ __global__ __launch_bounds__(1024) void dense_scan_counts_kernel(const int* __re
     if (t == 0) offs[M] = carry;
 }
 
+// ---- the definition's chain for single elements: u = sum over ascending k of x[row, k] * R[k, col], one fused
+// multiply-add per term (the products are exact).  Every lane of a wave owns one element, but the wave fetches the
+// operands together: in one load instruction eight neighbouring lanes read the eight 16-byte pieces of one element's
+// next 128 bytes (64 k) of its x row / R column (Rt holds R's columns contiguously), so every cache line is requested
+// once and used in full - a lane reading its own stream 16 bytes at a time asks for each line eight times over and the
+// chain then runs at a tenth of its arithmetic rate.  The pieces go through a wave-private LDS buffer (element rows
+// padded to 144 bytes: conflict-free 16-byte reads) to the lane that owns the element; the loads of the next 64 k are
+// in flight while the current ones are summed.
+constexpr int XE_ROW = 144, XE_BUF = 64 * XE_ROW;        // staging buffer of a wave (9216 bytes)
+
+struct Pieces {
+    v4u x[8], r[8];
+};
+// (xp / rp are not __restrict__: see dense_rotate_bf16_kernel)
+__device__ __forceinline__ Pieces load_pieces(const unsigned char* const (&xp)[8], const unsigned char* const (&rp)[8], size_t off) {
+    Pieces p;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        p.x[q] = *reinterpret_cast<const v4u*>(xp[q] + off);
+        p.r[q] = *reinterpret_cast<const v4u*>(rp[q] + off);
+    }
+    return p;
+}
+
+// All 64 lanes must call this together (lanes without an element pass any valid row / col and ignore the result).
+// K % 64 == 0.  lds: this wave's XE_BUF bytes.  Every lane reads its own x row itself, 16 bytes at a time, and only the R columns go
+// through LDS: neighbouring lanes share rows (the list keeps a row's entries together, about seven to a row at 35100 x 3072), and lanes with the
+// same address are served by one request.  One batch of 64 k in flight: registers decide how many waves run (two batches, with two waves
+// per SIMD instead of three: 257 -> 270 us).
+__device__ __forceinline__ double exact_element_wave(const uint16_t* X, const uint16_t* Rt, int K, int row, int col,
+                                                     unsigned char* lds) {
+    const int lane = threadIdx.x % kWave;
+    const unsigned char* xp[8];
+    const unsigned char* rp[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int e = 8 * q + lane / 8;                 // the element whose piece (lane % 8) this lane fetches in load q
+        const int ec = __shfl(col, e, kWave);
+        xp[q] = reinterpret_cast<const unsigned char*>(X + (size_t)row * K) + q * 16;
+        rp[q] = reinterpret_cast<const unsigned char*>(Rt + (size_t)ec * K) + (lane % 8) * 16;
+    }
+    unsigned char* rs = lds;
+    const int wr = (lane / 8) * XE_ROW + (lane % 8) * 16;        // + 8 q rows for load q
+    const int rd = lane * XE_ROW;
+    const int nb = K / 64;
+    double u = 0.0;
+    Pieces nxt = load_pieces(xp, rp, 0);
+    for (int b = 0; b < nb; ++b) {
+        // stage batch b (the previous batch was read into registers before this point)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) *reinterpret_cast<v4u*>(rs + wr + 8 * q * XE_ROW) = nxt.r[q];
+        v4u xv[8], rv[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) xv[i] = nxt.x[i];
+        wave_sync();
+        nxt = load_pieces(xp, rp, (size_t)(b + 1 < nb ? b + 1 : b) * 128);     // past the end: a harmless re-read
+        asm volatile("" ::: "memory");                   // keeps these loads ahead of the arithmetic below
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) rv[i] = *reinterpret_cast<const v4u*>(rs + rd + i * 16);
+        wave_sync();                                 // the reads are issued before the next batch is staged
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                u = fma((double)bf16_lo(xv[i][d]), (double)bf16_lo(rv[i][d]), u);
+                u = fma((double)bf16_hi(xv[i][d]), (double)bf16_hi(rv[i][d]), u);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return u;
+}
+
 // ---- undecided elements: exact value, exact code.  Thread i takes list entry i (row found by bisection of offs).
 template <bool ASYM>
 __global__ __launch_bounds__(256, 3) void dense_exact_codes_kernel(const uint16_t* X, const uint16_t* Rt, int M, int K, double qmax,
@@ -866,7 +1025,7 @@ __global__ __launch_bounds__(256, 3) void dense_exact_codes_kernel(const uint16_
             row = lo;
             col = (int)fidx[(size_t)row * capf + (i - offs[row])];
         }
-        const double u = exact_element_wave<true, 1>(X, Rt, K, row, col, stage + (threadIdx.x / kWave) * XE_BUF);
+        const double u = exact_element_wave(X, Rt, K, row, col, stage + (threadIdx.x / kWave) * XE_BUF);
         if (have) {
             const RowQuant rq = row_quant<ASYM>(amax_bits[2 * (size_t)row], amax_bits[2 * (size_t)row + 1], qmax);
             q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
@@ -998,6 +1157,16 @@ hipError_t launch_dense_prepare(hipStream_t st, const uint16_t* R, int K, void* 
 }
 
 namespace {
+// Lanes per amax candidate: eight shorten a chain, four cost less work where the waves fill the chip (rotate and quantize, us, eight /
+// four: 1000 x 3072 112.2 / 118.6, 5000 x 1152 77.7 / 79.0, 9000 x 1152 108.6 / 107.5, 9000 x 2048 201.4 / 198.1).
+bool amax_eight_lanes(int M) { return M <= 6144; }
+// One kernel for codes and undecided elements, or flags, a list and chains with a lane per element.  The one kernel needs no
+// chain's latency and two launches less; with the list, some 20000 elements per XCD walk K side by side and find their R columns in its
+// L2 more often (53 % of the requests against 14 % at 35100 x 3072), which counts where R is larger than that L2.  Rotate and quantize,
+// us, one kernel / list: 300 x 1152 36.6 / 57.0, 8192-row range at K = 1152 94 / 109, 35100 x 2048 653 / 676, 9000 x 2304 232 / 230,
+// 2500 x 3072 142.8 / 151.8, 5000 x 3072 233.9 / 230.5, 35100 x 3072 1373 / 1318, 300 x 4608 177 / 153.
+bool quant_in_one(int M, int K) { return K <= 2048 || (K <= 3072 && M <= 4096); }
+
 template <bool ASYM>
 hipError_t launch_dense_fast(hipStream_t st, const uint16_t* X, const uint16_t* R, const void* prepared, int M, int K, int act_bits,
                              void* ws, int8_t* q, float* scale, int32_t* zero) {
@@ -1025,7 +1194,7 @@ hipError_t launch_dense_fast(hipStream_t st, const uint16_t* X, const uint16_t* 
     const double qmax = (double)((1 << (act_bits - 1)) - 1);
     // ETA * m for the runs of the matrix instruction, 2^-24 for each of the GROUP - 1 fp32 additions of a group and for the
     // fp32 store of u~
-    const float err_factor = (float)(ldexp(1.0, -21) * (kChunk / 16) + ldexp(1.0, -24) * kGroup);
+    const float err_factor = (float)((ldexp(17.0, -26) + ldexp(1.0, -23)) * (kChunk / 16) + ldexp(1.0, -24) * kGroup);
 
     if (!prepared) {       // R's transpose and statistics: computed here, into the same layout inside the workspace
         const hipError_t e = launch_dense_prepare(st, R, K, base + L.rt);
@@ -1042,12 +1211,22 @@ hipError_t launch_dense_fast(hipStream_t st, const uint16_t* X, const uint16_t* 
     else
         hipLaunchKernelGGL((dense_row_candidates_kernel<false, ASYM>), dim3((M + 3) / 4), dim3(256), 0, st, X, Ut, segmax, M, K, rowmax,
                            scalars, err_factor, eps, amax, ccount, cidx, mode);
-    hipLaunchKernelGGL(dense_exact_amax_kernel<ASYM>, dim3((unsigned)(((long)M * CAPC * (ASYM ? 2 : 1) + 255) / 256)), dim3(256), 0, st,
-                       X, Rt, M, K, ccount, cidx, amax, nwhole);
-    hipLaunchKernelGGL(dense_quant_flag_kernel<ASYM>, dim3((M + 3) / 4), dim3(256), 4 * sizeof(int), st, Ut, M, K, qmax, eps, amax, q,
-                       scale, zero, fcount, fidx, L.capf, mode, nwhole, whole);
-    hipLaunchKernelGGL(dense_scan_counts_kernel, dim3(1), dim3(1024), 0, st, fcount, M, foffs);
-    hipLaunchKernelGGL(dense_exact_codes_kernel<ASYM>, dim3(2048), dim3(256), 0, st, X, Rt, M, K, qmax, foffs, fidx, L.capf, amax, q);
+    const long candidates = (long)M * CAPC * (ASYM ? 2 : 1);
+    if (amax_eight_lanes(M))
+        hipLaunchKernelGGL((dense_exact_amax_kernel<ASYM, 8>), dim3((unsigned)((candidates + 31) / 32)), dim3(256), 0, st, X, Rt, M, K,
+                           ccount, cidx, amax, nwhole);
+    else
+        hipLaunchKernelGGL((dense_exact_amax_kernel<ASYM, 4>), dim3((unsigned)((candidates + 63) / 64)), dim3(256), 0, st, X, Rt, M, K,
+                           ccount, cidx, amax, nwhole);
+    if (quant_in_one(M, K)) {
+        hipLaunchKernelGGL(dense_quant_kernel<ASYM>, dim3((M + 3) / 4), dim3(256), 4 * 2 * L.capf * sizeof(uint16_t), st, X, Rt, Ut, M, K,
+                           qmax, (double)err_factor, eps, amax, q, scale, zero, fcount, L.capf, mode, nwhole, whole);
+    } else {
+        hipLaunchKernelGGL(dense_quant_flag_kernel<ASYM>, dim3((M + 3) / 4), dim3(256), 4 * sizeof(int), st, Ut, M, K, qmax, eps, amax, q,
+                           scale, zero, fcount, fidx, L.capf, mode, nwhole, whole);
+        hipLaunchKernelGGL(dense_scan_counts_kernel, dim3(1), dim3(1024), 0, st, fcount, M, foffs);
+        hipLaunchKernelGGL(dense_exact_codes_kernel<ASYM>, dim3(2048), dim3(256), 0, st, X, Rt, M, K, qmax, foffs, fidx, L.capf, amax, q);
+    }
     const size_t rows_lds = (((size_t)K * 2 + 15) & ~(size_t)15) + 8 * sizeof(double);
     hipLaunchKernelGGL(dense_exact_rows_kernel<ASYM>, dim3(M < 2048 ? M : 2048), dim3(256), rows_lds, st, X, R, K, qmax, nwhole, whole,
                        q, scale, zero);

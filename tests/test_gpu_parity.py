@@ -270,6 +270,34 @@ def test_dense_rotation_random_shapes(lrq, seed):
         assert np.array_equal(a.cpu().numpy(), b)
 
 
+@pytest.mark.parametrize("M,K", [(70, 128), (66, 2048), (130, 3200), (4200, 2176), (6200, 128)])
+@pytest.mark.parametrize("asym", [False, True])
+def test_dense_rotation_exact_ties(lrq, M, K, asym):
+    """Every second row holds values that are half-integers in units of its quantizer's step (R is the identity on them: a permutation),
+    up to as many as its list of undecided elements holds; the others are ordinary.  One kernel for codes and undecided elements
+    or the list of them, four or eight lanes to a candidate of the maximum: against the all-fp64 evaluation, and the tied codes
+    against round-half-to-even."""
+    import torch
+    print(f"case dense ties M={M} K={K} asym={asym}", flush=True)
+    g = synth.rng_for(945, M, K)
+    perm = g.permutation(K)
+    R = np.zeros((K, K), np.float32)
+    R[np.arange(K), perm] = 1.0
+    x = g.standard_normal((M, K)).astype(np.float32)
+    ties = 20
+    x[::2] = np.rint(x[::2] * 20.0)
+    x[::2, 0], x[::2, 1] = 127.0, (-128.0 if asym else -100.0)
+    half = g.integers(-60, 60, size=(x[::2].shape[0], ties)) + 0.5
+    x[::2, 2:2 + ties] = half
+    X, Rd = synth.f32_to_bf16_bits(x), bf16_to_dev(synth.f32_to_bf16_bits(R))
+    got = lrq.ars_rotate_quant(bf16_to_dev(X), lrq.Rotation("dense", 0, Rd), 8, asym=asym)
+    ref = lrq.ars_rotate_quant(bf16_to_dev(X), lrq.Rotation("dense_f64", 0, Rd), 8, asym=asym)
+    for a, b in zip(got, ref):
+        assert torch.equal(a, b)
+    q = got[0].cpu().numpy()[::2][:, perm[2:2 + ties]].astype(np.float64)
+    assert np.array_equal(q, np.rint(half))              # the step is 1; zero-points: x_q - 128 with z = -128
+
+
 def _equal_maxima_inputs(M, K, marked):
     """Sylvester Hadamard matrix as the rotation; the marked rows hold one spike, so that every |u| of theirs is a maximum."""
     R = synth.f32_to_bf16_bits((oracle.hadamard_matrix(K) / np.sqrt(K)).astype(np.float32))
