@@ -303,6 +303,17 @@ size_t lrq_workspace_bytes_asym(int M, int N, int K, const lrq_rotation* rot, in
 
 enum class Gemm { kInt8, kInt8Zero, kLevels };
 
+// Whether the int8 layer runs as one kernel: a few tokens, and a rotation that every workgroup can repeat.
+static bool one_launch(int M, int N, int K, const lrq_rotation* rot) {
+    return (rot->kind == LRQ_ROT_NONE && lrq::qlinear_few_applies(M, N, K, 1)) ||
+           (rot->kind == LRQ_ROT_HADAMARD && lrq::qlinear_few_applies(M, N, K, rot->had_block));
+}
+static int run_one_launch(hipStream_t st, const void* X, int M, int K, const lrq_rotation* rot, int act_bits, bool asym,
+                          const lrq_tlq_weight* w, const float* bias, int out_dtype, void* Y) {
+    return lrq::launch_qlinear_few(st, static_cast<const uint16_t*>(X), M, K, rot->kind == LRQ_ROT_NONE ? 1 : rot->had_block, act_bits, asym,
+                                   rot->prescale, *w, bias, out_dtype, Y) == hipSuccess ? LRQ_OK : LRQ_EHIP;
+}
+
 // the *_levels calls need the bf16 level table, and levels that are bf16 values
 static int check_levels(const lrq_tlq_weight* w) {
     if (!w->levels) return LRQ_EINVAL;
@@ -380,6 +391,7 @@ static int qlinear_impl(void* stream, const void* X, int M, int K, const lrq_rot
     void* rot_ws = base + round256((size_t)M * K) + round256((size_t)M * sizeof(float));
     int32_t* zero = asym ? reinterpret_cast<int32_t*>(static_cast<char*>(rot_ws) + ars_layout(M, K, rot).total) : nullptr;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (kind != Gemm::kLevels && one_launch(M, w->N, K, rot)) return run_one_launch(s, X, M, K, rot, act_bits, asym, w, bias, out_dtype, Y);
     st = run_rotate_quant(s, X, M, K, rot, act_bits, q, scale, zero, rot_ws);
     if (st != LRQ_OK) return st;
     hipError_t e;
@@ -481,6 +493,7 @@ int lrq_qlinear_packed4(void* stream, const void* X, int M, int K, const lrq_rot
     float* scale = reinterpret_cast<float*>(base + round256((size_t)M * K / 2));
     void* rot_ws = base + round256((size_t)M * K / 2) + round256((size_t)M * sizeof(float));
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (one_launch(M, w->N, K, rot)) return run_one_launch(s, X, M, K, rot, 4, false, w, bias, out_dtype, Y);
     st = rotate_quant_packed4(s, X, M, K, rot, q4, scale, rot_ws);
     if (st != LRQ_OK) return st;
     return lrq::launch_qgemm(s, reinterpret_cast<const int8_t*>(q4), scale, nullptr, M, K, *w, bias, out_dtype, Y, true) == hipSuccess

@@ -111,6 +111,12 @@ int qgemm_wide_rows(int M, int N, int K, int bits, bool zero_point, bool fp32);
 hipError_t launch_qgemm_wide(hipStream_t st, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
                              const lrq_tlq_weight& w, const float* bias, void* Y, void* ws, int rows);
 
+// Rotate (Hadamard, had_block 1 = none), quantize and multiply a few tokens in one launch (qlinear_few.hip).  Same outputs as
+// the two stages.
+bool qlinear_few_applies(int M, int N, int K, int had_block);
+hipError_t launch_qlinear_few(hipStream_t st, const uint16_t* X, int M, int K, int had_block, int act_bits, bool asym, const float* prescale,
+                              const lrq_tlq_weight& w, const float* bias, int out_dtype, void* Y);
+
 // Y = scale_t * sum_k q * levels (+ bias) on the bf16 matrix cores; w.levels must be set.
 hipError_t launch_qgemm_levels(hipStream_t st, const int8_t* q, const float* scale, int M, int K, const lrq_tlq_weight& w,
                                const float* bias, int out_dtype, void* Y);

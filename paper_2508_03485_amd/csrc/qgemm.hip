@@ -14,8 +14,6 @@
 namespace lrq {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-
 constexpr int WAVES = 4;
 constexpr int BK = kGemmBlockK;     // 64
 constexpr int PLANE_PAD = 32;          // padding of a plane (swept 0 / 16 / 32 / 48: 32 leaves the fewest bank conflicts)
@@ -23,53 +21,6 @@ constexpr int AF_DIST = 2;             // A fragments are read this many row til
 constexpr int PLANE = 32 * 16 + PLANE_PAD;     // bytes of one (row tile, 16-byte k chunk) plane in LDS, padded
 constexpr int EPI_ROW = 64 * 2 + 16;   // bytes of one staged output row of a wave (up to 64 bf16 / 32 fp32) + pad
 constexpr int EPI_WAVE = 32 * EPI_ROW; // one 32-row slab per wave
-
-__device__ __forceinline__ unsigned perm(unsigned hi, unsigned lo, unsigned sel) {
-    return __builtin_amdgcn_perm(hi, lo, sel);
-}
-
-// Raw operand codes of one lane for one K block and one 32-channel tile: its 16-byte slot of the code tiling, i.e. the
-// 16 codes (k = 16 (lane / 16) + [0, 16) of the block) of channel lane % 16 of the tile in dwords 0, 1 and those of channel
-// 16 + lane % 16 in dwords 2, 3; one nibble each, either bit-width.
-template <int BITS>
-struct BRaw {
-    unsigned d[4];
-};
-
-template <int BITS>
-__device__ __forceinline__ BRaw<BITS> load_braw(const uint8_t* __restrict__ p) {
-    BRaw<BITS> r;
-    const uint4 v = *reinterpret_cast<const uint4*>(p);
-    r.d[0] = v.x; r.d[1] = v.y; r.d[2] = v.z; r.d[3] = v.w;
-    return r;
-}
-
-// Decode the 4 codes of operand dword g (0..3) of the slot's channel s (0 | 1).  Raw dword 2s + g/2 holds 8
-// codes, byte j = code[j] | code[4+j] << 4.
-// 4-bit: the level table has 16 entries (L[0..1] codes 0..7, L[2..3] codes 8..15 = negative twin): two 8-entry byte
-// permutes and a third that picks per byte by the code's sign bit.  C = 0x03020100 must live in a VGPR so that the
-// pick selector is a single v_and_or_b32.
-// 3-bit: 8-entry table, the masked nibbles are the selectors of one byte permute.
-template <int BITS>
-__device__ __forceinline__ unsigned decode_dword(const BRaw<BITS>& raw, const unsigned L[4], int s, int g, unsigned C) {
-    const unsigned w = raw.d[2 * s + g / 2];
-    if constexpr (BITS == 4) {
-        unsigned idx, pick;
-        if (g % 2 == 0) {
-            idx = w & 0x07070707u;
-            pick = ((w >> 1) & 0x04040404u) | C;
-        } else {
-            idx = (w >> 4) & 0x07070707u;
-            pick = ((w >> 5) & 0x04040404u) | C;
-        }
-        const unsigned a = perm(L[1], L[0], idx);
-        const unsigned b = perm(L[3], L[2], idx);
-        return perm(b, a, pick);
-    } else {
-        const unsigned idx = (g % 2 == 0 ? w : (w >> 4)) & 0x07070707u;
-        return perm(L[1], L[0], idx);
-    }
-}
 
 // One K block of the main loop.  The A tiles rotate through three LDS buffers: block kb multiplies from `cur`
 // (tile kb), stages tile kb+2 (held in aS, which is then reloaded with tile kb+4) into `st`, and - because tile kb+1

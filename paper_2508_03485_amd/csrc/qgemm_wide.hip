@@ -17,8 +17,6 @@
 namespace lrq {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-
 constexpr int BK = kGemmBlockK;                      // 64
 constexpr int BN = 256;
 constexpr int BUF = 256 * BK;                        // bytes of one operand tile of a stage (256 rows at most)

@@ -856,6 +856,42 @@ def test_qgemm_tile_shapes(lrq, M, N, K, w_bits, tile, form):
         assert torch.equal(y, ref.to(dt))
 
 
+@pytest.mark.parametrize("M,K,h,N,w_bits,a_bits,form", [
+    (1, 128, 1, 32, 4, 8, "symmetric"),            # the smallest; no rotation
+    (16, 1024, 32, 100, 3, 6, "zero_point"),       # M K at the limit; blocks inside a thread; cut channel tile
+    (3, 1152, 64, 96, 4, 8, "zero_point"),         # blocks across a pair of lanes, nine K blocks to some waves
+    (14, 1152, 128, 67, 3, 4, "packed"),           # across a quad; output rows of odd length
+    (5, 2304, 256, 200, 4, 8, "prescale"),         # the exchange through LDS, 4 / 2 / 1 element offsets to a lane
+    (7, 1536, 512, 8192, 4, 4, "packed"),          # as many workgroups as CUs
+    (16, 1024, 1024, 64, 4, 8, "zero_point"),      # all threads in the exchange
+    (5, 3072, 1024, 130, 3, 8, "prescale"),
+    (2, 8192, 1024, 33, 4, 8, "symmetric"),        # two rounds of K blocks
+])
+def test_qlinear_few_tokens_in_one_launch(lrq, M, K, h, N, w_bits, a_bits, form):
+    """The one-launch form of small calls against the two stages (each tested against the oracle), bit for bit, in both output types, at
+    the edges of its range."""
+    import torch
+    print(f"case few M={M} K={K} h={h} N={N} W{w_bits}A{a_bits} {form}", flush=True)
+    gd = to_dev(np.array([1.0, 1.5], np.float32))
+    w = lrq.tlq_quantize_pack(to_dev(synth.make_weights(N, K, (912, N, K))), w_bits, 7, gd, gd)
+    X = bf16_to_dev(_acts(M, K, 70 + M))
+    rot = lrq.Rotation("hadamard", h)
+    if form == "prescale":
+        rot.prescale = to_dev(np.exp2(synth.rng_for(912, K).uniform(-3, 3, K)).astype(np.float32))
+    asym = form == "zero_point"
+    bias = to_dev(synth.rng_for(912, N).standard_normal(N).astype(np.float32))
+    q, scale, *zero = lrq.ars_rotate_quant(X, rot, a_bits, asym=asym)
+    for dt in (torch.float32, torch.bfloat16):
+        ref = lrq.qgemm(q, scale, w, bias=bias, out_dtype=dt, zero=zero[0] if asym else None)
+        if form == "packed":
+            y = lrq.qlinear_packed4(X, rot, w, bias=bias, out_dtype=dt)
+        else:
+            ws = torch.full((lrq.workspace_bytes(M, N, K, rot, a_bits, asym=asym),), 90, dtype=torch.uint8, device="cuda")
+            y = lrq.qlinear(X, rot, a_bits, w, bias=bias, out_dtype=dt, workspace=ws, asym=asym)
+            assert bool((ws == 90).all())                  # one launch: codes and scales never left the workgroups
+        assert torch.equal(y, ref)
+
+
 @pytest.mark.parametrize("M,N,K,w_bits,asym", [
     (14009, 1672, 448, 4, False),      # 192 rows, two tiles to some workgroups, odd number of K blocks, cut both ways
     (9734, 1232, 1152, 4, True),       # 192 rows, zero-points, one round, N no multiple of a channel group
