@@ -121,15 +121,15 @@ ArsWs ars_layout(int M, int K, const lrq_rotation* rot) {
 }
 
 int run_rotate_quant(hipStream_t st, const void* X, int M, int K, const lrq_rotation* rot, int act_bits,
-                     int8_t* q, float* scale, int32_t* zero, void* ws) {
+                     int8_t* q, float* scale, int32_t* zero, void* ws, const lrq::DecodeJob* decode = nullptr) {
     hipError_t e = hipSuccess;
     const uint16_t* x = static_cast<const uint16_t*>(X);
     switch (rot->kind) {
         case LRQ_ROT_NONE:
-            e = lrq::launch_plain_quant(st, x, M, K, act_bits, q, scale, zero, rot->prescale);
+            e = lrq::launch_plain_quant(st, x, M, K, act_bits, q, scale, zero, rot->prescale, decode);
             break;
         case LRQ_ROT_HADAMARD:
-            e = lrq::launch_hadamard_quant(st, x, M, K, rot->had_block, act_bits, q, scale, zero, rot->prescale);
+            e = lrq::launch_hadamard_quant(st, x, M, K, rot->had_block, act_bits, q, scale, zero, rot->prescale, false, false, decode);
             break;
         case LRQ_ROT_BLOCKPERM:
             e = lrq::launch_blockperm_rotate_quant(
@@ -281,13 +281,21 @@ static bool wide_in_scratch(int M, int K, const lrq_rotation* rot, size_t bytes)
     return rot && rot->kind != LRQ_ROT_DENSE_F64 && ars_layout(M, K, rot).total >= bytes;
 }
 
+// Whether the launch of this rotation takes the decoding of the weights along.
+static bool decodes_along(int K, const lrq_rotation* rot) {
+    return rot && ((rot->kind == LRQ_ROT_NONE && lrq::hadamard_decodes(K, 1)) ||
+                   (rot->kind == LRQ_ROT_HADAMARD && lrq::hadamard_decodes(K, rot->had_block)));
+}
+
 // Room for the weights that the wide GEMM reads decoded, beyond base_workspace: none where that kernel serves no form of the
 // product, or where the rotation's scratch, free by then, holds them.
 static size_t wide_workspace(int M, int N, int K, const lrq_rotation* rot) {
     if (N <= 0 || K % lrq::kGemmBlockK != 0) return 0;
     const size_t bytes = lrq::qgemm_wide_bytes(N, K);
     if (wide_in_scratch(M, K, rot, bytes)) return 0;
-    return lrq::qgemm_wide_rows(M, N, K, 4, false, false) > 0 || lrq::qgemm_wide_rows(M, N, K, 4, true, false) > 0 ? round256(bytes) : 0;
+    const bool along = decodes_along(K, rot);
+    return lrq::qgemm_wide_rows(M, N, K, 4, false, false, along) > 0 || lrq::qgemm_wide_rows(M, N, K, 4, true, false, along) > 0
+               ? round256(bytes) : 0;
 }
 
 size_t lrq_workspace_bytes(int M, int N, int K, const lrq_rotation* rot, int act_bits) {
@@ -392,22 +400,31 @@ static int qlinear_impl(void* stream, const void* X, int M, int K, const lrq_rot
     int32_t* zero = asym ? reinterpret_cast<int32_t*>(static_cast<char*>(rot_ws) + ars_layout(M, K, rot).total) : nullptr;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (kind != Gemm::kLevels && one_launch(M, w->N, K, rot)) return run_one_launch(s, X, M, K, rot, act_bits, asym, w, bias, out_dtype, Y);
-    st = run_rotate_quant(s, X, M, K, rot, act_bits, q, scale, zero, rot_ws);
-    if (st != LRQ_OK) return st;
-    hipError_t e;
-    if (kind == Gemm::kLevels) {
-        e = lrq::launch_qgemm_levels(s, q, scale, M, K, *w, bias, out_dtype, Y);
-    } else {
-        void* wide = nullptr;
-        const size_t bytes = lrq::qgemm_wide_bytes(w->N, K);
+    void* wide = nullptr;
+    const size_t bytes = lrq::qgemm_wide_bytes(w->N, K);
+    if (kind != Gemm::kLevels) {
         if (wide_in_scratch(M, K, rot, bytes)) wide = rot_ws;
         else if (ws_bytes >= need + bytes) wide = base + need;
-        const int rows = wide ? lrq::qgemm_wide_rows(M, w->N, K, w->bits, asym, out_dtype == LRQ_OUT_FP32) : 0;
-        if (rows > 0)
-            e = lrq::launch_qgemm_wide(s, q, scale, zero, M, K, *w, bias, Y, wide, rows);
-        else
-            e = lrq::launch_qgemm(s, q, scale, zero, M, K, *w, bias, out_dtype, Y);
     }
+    const int rows = wide ? lrq::qgemm_wide_rows(M, w->N, K, w->bits, asym, out_dtype == LRQ_OUT_FP32, decodes_along(K, rot)) : 0;
+    const bool along = rows > 0 && decodes_along(K, rot);        // such rotations have no scratch
+    lrq::DecodeJob job;
+    if (along) {
+        job.gcodes = w->gemm_codes;
+        job.lut = w->lut;
+        job.out = static_cast<uint8_t*>(wide);
+        job.N = w->N;
+        job.KB = K / lrq::kGemmBlockK;
+    }
+    st = run_rotate_quant(s, X, M, K, rot, act_bits, q, scale, zero, rot_ws, along ? &job : nullptr);
+    if (st != LRQ_OK) return st;
+    hipError_t e;
+    if (kind == Gemm::kLevels)
+        e = lrq::launch_qgemm_levels(s, q, scale, M, K, *w, bias, out_dtype, Y);
+    else if (rows > 0)
+        e = lrq::launch_qgemm_wide(s, q, scale, zero, M, K, *w, bias, Y, wide, rows, along);
+    else
+        e = lrq::launch_qgemm(s, q, scale, zero, M, K, *w, bias, out_dtype, Y);
     return e == hipSuccess ? LRQ_OK : LRQ_EHIP;
 }
 

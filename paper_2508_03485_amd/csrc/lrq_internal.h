@@ -30,6 +30,15 @@ struct QuantSpec {
     int fp8;                // 1: 4-bit codes are written as FP8 E4M3 bit patterns
 };
 
+// Decoding of all weights for the wide GEMM (qgemm_wide.hip: out, qgemm_wide_bytes(N, K) bytes) by extra workgroups of the rotation's launch.
+struct DecodeJob {
+    const uint8_t* gcodes = nullptr;
+    const int8_t* lut = nullptr;
+    uint8_t* out = nullptr;
+    int N = 0, KB = 0;
+    unsigned first = 0;         // workgroups from this one on decode (set by the launcher)
+};
+
 // u = x.(I (x) H_h) in fp64, per-token statistics, round to codes.  K % 8 == 0, h | K, h power of two.
 // zero == nullptr selects the symmetric quantizer, otherwise the zero-point form (zero receives z + 2^(a-1)).
 // prescale (every launcher): nullptr, or fp32 [K] multiplied into x channel-wise before the rotation.
@@ -37,7 +46,9 @@ struct QuantSpec {
 // hadamard_packs_in_kernel is true may be launched that way.
 hipError_t launch_hadamard_quant(hipStream_t st, const uint16_t* X, int M, int K, int h, int act_bits,
                                  int8_t* q, float* scale, int32_t* zero, const float* prescale, bool packed = false,
-                                 bool fp8 = false);
+                                 bool fp8 = false, const DecodeJob* decode = nullptr);
+// whether launch_hadamard_quant takes a DecodeJob for this shape
+bool hadamard_decodes(int K, int h);
 // int8 codes in [-7, 7] -> FP8 E4M3 bit patterns, in place (n bytes, n % 16 == 0)
 hipError_t launch_codes_to_fp8(hipStream_t st, int8_t* q, size_t n);
 // Y = scale_t * wscale_fp8_n * sum_k q * lut_fp8 (+ bias) on the FP8 matrix cores; q8: E4M3 bit patterns [M, K]
@@ -48,7 +59,7 @@ bool hadamard_packs_in_kernel(int K, int h);
 hipError_t launch_pack_nibbles(hipStream_t st, const int8_t* q, int M, int K, uint8_t* q4);
 // u = x (no rotation), same quantizer.
 hipError_t launch_plain_quant(hipStream_t st, const uint16_t* X, int M, int K, int act_bits,
-                              int8_t* q, float* scale, int32_t* zero, const float* prescale);
+                              int8_t* q, float* scale, int32_t* zero, const float* prescale, const DecodeJob* decode = nullptr);
 // u = x.R in fp64 (k ascending), written to U [M,K] doubles, then quantized from U.
 hipError_t launch_dense_rotate_quant(hipStream_t st, const uint16_t* X, const uint16_t* R, int M, int K,
                                      int act_bits, double* U, int8_t* q, float* scale, int32_t* zero,
@@ -105,11 +116,12 @@ GemmShape qgemm_shape(int M, int N, int K, int bits, bool zero_point, bool packe
 
 // The same product with the weights decoded once, into qgemm_wide_bytes(N, K) bytes of workspace (16-byte aligned), and tiles of
 // rows x 256, bf16 outputs (qgemm_wide.hip).  qgemm_wide_rows: the rows with the smallest predicted time, 0 where the kernel launch_qgemm takes is
-// predicted to be as fast or the shape is not served.
+// predicted to be as fast or the shape is not served.  along: the weights are decoded by a DecodeJob.
 size_t qgemm_wide_bytes(int N, int K);
-int qgemm_wide_rows(int M, int N, int K, int bits, bool zero_point, bool fp32);
+int qgemm_wide_rows(int M, int N, int K, int bits, bool zero_point, bool fp32, bool along);
+// decoded: a DecodeJob ahead of this call has filled ws.
 hipError_t launch_qgemm_wide(hipStream_t st, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
-                             const lrq_tlq_weight& w, const float* bias, void* Y, void* ws, int rows);
+                             const lrq_tlq_weight& w, const float* bias, void* Y, void* ws, int rows, bool decoded);
 
 // Rotate (Hadamard, had_block 1 = none), quantize and multiply a few tokens in one launch (qlinear_few.hip).  Same outputs as
 // the two stages.

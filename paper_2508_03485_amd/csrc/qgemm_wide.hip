@@ -13,6 +13,7 @@
 // always hit L2 on top of that, 773 with no operand loads at all; two 128 x 256 workgroups per CU instead of this one take 1119, since they
 // fetch twice as much through the fabric (3.7 against 2.3 GB).
 #include "qgemm_common.h"
+#include "weight_decode.h"
 
 namespace lrq {
 namespace {
@@ -22,55 +23,12 @@ constexpr int BN = 256;
 constexpr int BUF = 256 * BK;                        // bytes of one operand tile of a stage (256 rows at most)
 constexpr int NBUF = 4;
 constexpr int OFF_B = NBUF * BUF, OFF_S = 2 * NBUF * BUF;
-constexpr int GROUP = 64 * BK;                       // bytes of a 64-channel group of decoded weights in one K block
+constexpr int GROUP = kWideGroup;
 // token scales, channel scales, biases; zero-point form: zero-points and level sums
 constexpr int LDS_BYTES = OFF_S + (3 * 256 + 2 * 256) * 4;
 
-// int8 levels of four 4-bit codes, one in the low nibble of each byte of w (level table of the codes' channel: entries 0-7 in L[0..1],
-// 8-15, the negative twin, in L[2..3])
-__device__ __forceinline__ unsigned decode_codes4(unsigned w, const unsigned (&L)[4]) {
-    const unsigned idx = w & 0x07070707u;
-    const unsigned lo = __builtin_amdgcn_perm(L[1], L[0], idx), hi = __builtin_amdgcn_perm(L[3], L[2], idx);
-    return __builtin_amdgcn_perm(hi, lo, ((w >> 1) & 0x04040404u) | 0x03020100u);
-}
-
-// Decoded weights: [64-channel group][K block][16-column tile ct 0..3][k chunk 0..3][column i 0..15] of 16 bytes (k = 16 chunk +
-// [0, 16) of the block): 1 KB a tile, the order of a wave's operand registers.  Column i of tile ct is channel
-// 32 (ct / 2) + 8 (i / 4) + 4 (ct % 2) + i % 4 of the group, so that a lane's accumulators of two neighbouring tiles are eight
-// neighbouring channels: 16 bytes of bf16, and the four lanes of a token store 64 contiguous bytes without a pass through LDS.
-// One wave per (32-channel tile, K block) unit of the code tiling; lane = its slot (lrq_internal.h).  Bound by its writes: 37.7 MB in 9 us.
-__global__ __launch_bounds__(256) void decode_weights_kernel(const uint8_t* __restrict__ gcodes, const int8_t* __restrict__ lut, int N,
-                                                             int KB, uint8_t* __restrict__ out) {
-    const int tl = blockIdx.x, lane = threadIdx.x % 64, c = lane % 16;
-    unsigned L[2][4];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        int n = tl * 32 + h * 16 + c;
-        if (n >= N) n = N - 1;
-        const uint4 lv = *reinterpret_cast<const uint4*>(lut + (size_t)n * 16);
-        L[h][0] = lv.x; L[h][1] = lv.y; L[h][2] = lv.z; L[h][3] = lv.w;
-    }
-    const uint8_t* src = gcodes + (size_t)tl * KB * 1024 + lane * 16;
-    uint8_t* dst = out + (size_t)(tl / 2) * KB * GROUP + (lane / 16) * 256;
-    int off[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int n = h * 16 + c;
-        off[h] = ((tl % 2) * 2 + (n / 4) % 2) * 1024 + ((n / 8) * 4 + n % 4) * 16;
-    }
-    const int step = gridDim.y * 4;
-    for (int kb = blockIdx.y * 4 + threadIdx.x / 64; kb < KB; kb += step) {
-        const uint4 raw = *reinterpret_cast<const uint4*>(src + (size_t)kb * 1024);
-        const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            v4i o;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) o[g] = (int)decode_codes4(w[2 * h + g / 2] >> (g % 2 * 4), L[h]);
-            *reinterpret_cast<v4i*>(dst + (size_t)kb * GROUP + off[h]) = o;
-        }
-    }
-}
+// The decoding pass on its own, for rotations whose launch does not take it.  Bound by its writes: 37.7 MB in 9 us.
+__global__ __launch_bounds__(256) void decode_weights_kernel(DecodeJob job) { decode_weights(job, blockIdx.x, gridDim.x, 4); }
 
 // 64 lanes x 16 bytes from global memory into LDS: lane l's bytes land at lds + 16 l.  In assembly, with no register written, because
 // the compiler would wait for every load of this kind before any later LDS read; the waits are the WAIT_LOADS below.
@@ -326,46 +284,55 @@ hipError_t launch_wide(hipStream_t st, const int8_t* q, const float* scale, cons
 
 // Times in us, decoding included, fitted (with 4 % between fit and measurement) to 600 measurements of each height over M = 200 ..
 // 35100, N = 96 .. 12288, K = 320 .. 12288.  A round of tiles, one per CU, takes k per K block + k_fill times the share of the CUs that
-// have a tile (the chip's clock falls with the work in flight) + its epilogue.  The lower tiles are taken where they fill the last round better (us with 192 / 224 /
-// 256 rows: 8192 x 1152 -> 4608 50.2 / 52.1 / 55.5, 4608 x 3072 -> 9216 136 / 128 / 143, 35100 x 3072 -> 12288 1165 / 1138 / 1104).
-// Against qgemm.hip, whose predicted time has to be 2 % longer: 35100 x 3072 -> 12288 1340 us at 4 bits, 8192 x 1152 -> 4608 56.0.  3-bit
+// have a tile (the chip's clock falls with the work in flight) + its epilogue (1.5 us above the fit: the boards differ most in how fast
+// all CUs' stores drain, 8192 x 1152 -> 4608 with three rounds of them 60.2 us against 62.9 on one and 67.8 against 64.4 on another).  The
+// lower tiles are taken where they fill the last round better (us with 192 / 224 / 256 rows: 8192 x 1152 -> 4608 50.2 / 52.1 / 55.5,
+// 4608 x 3072 -> 9216 136 / 128 / 143, 35100 x 3072 -> 12288 1165 / 1138 / 1104).  Decoded along with the rotation, the weights cost
+// neither their launch nor most of their time (8192 x 1152 -> 4608: 3 us of 62).
+// Against qgemm.hip, whose predicted time has to be 3 % longer: 35100 x 3072 -> 12288 1340 us at 4 bits.  3-bit
 // weights, whose decoding takes a third of the instructions, stay there: 35100 x 3072 -> 9216 835 us against 846 here.  So do outputs other than
-// bf16 rows of whole 16-byte pieces: fp32 outputs (22488 x 6144 -> 4736 616 us against 678, but 30107 x 3072 -> 490 87 against 62: every tile's 256 KB are written
-// at once) and ragged rows (element by element: 20688 x 2304 -> 2389 212 us against 143) rarely gain.
+// bf16 rows of whole 16-byte pieces: fp32 outputs (22488 x 6144 -> 4736 616 us against 678, but 30107 x 3072 -> 490 87 against 62: every tile's
+// 256 KB are written at once) and ragged rows (element by element: 20688 x 2304 -> 2389 212 us against 143) rarely gain.
 struct WideCost { int rows; float k, k_fill, tile, zero_point, once; };
-constexpr WideCost kWideCost[3] = {{192, 0.315f, 0.288f, 4.56f, 0.3f, 6.9f},
-                                   {224, 0.357f, 0.318f, 5.37f, 1.3f, 6.1f},
-                                   {256, 0.382f, 0.376f, 5.86f, 4.2f, 7.0f}};
-constexpr float kDecodePerByte = 0.17e-6f;
+constexpr WideCost kWideCost[3] = {{192, 0.315f, 0.288f, 6.06f, 0.3f, 6.9f},
+                                   {224, 0.357f, 0.318f, 6.87f, 1.3f, 6.1f},
+                                   {256, 0.382f, 0.376f, 7.36f, 4.2f, 7.0f}};
+constexpr float kDecodePerByte = 0.17e-6f, kAlong = 3.5f;
 
-int qgemm_wide_rows(int M, int N, int K, int bits, bool zero_point, bool fp32) {
+int qgemm_wide_rows(int M, int N, int K, int bits, bool zero_point, bool fp32, bool along) {
     if (bits != 4 || fp32 || N % 8 != 0) return 0;
     if (K < 4 * BK || (zero_point && K > kZpF64K)) return 0;         // three stages are in flight; longer sums need 64-bit integers
-    const float kb = (float)(K / BK);
+    const float kb = (float)(K / BK), decode = kDecodePerByte * (float)N * (float)K;
     float best = INFINITY;
     int rows = 0;
     for (const WideCost& c : kWideCost) {
         const long tiles = ((long)M + c.rows - 1) / c.rows * (((long)N + BN - 1) / BN), n = (tiles + 255) / 256;
-        const float us = c.once + kDecodePerByte * (float)N * (float)K +
+        const float us = c.once + (along ? 0.5f * decode - kAlong : decode) +
                          (float)n * ((c.k + c.k_fill * (float)tiles / (256.0f * (float)n)) * kb + c.tile + (zero_point ? c.zero_point : 0.0f));
         if (us < best) {
             best = us;
             rows = c.rows;
         }
     }
-    return best * 1.02f < qgemm_shape(M, N, K, 4, zero_point, false, false).us ? rows : 0;
+    return best * 1.03f < qgemm_shape(M, N, K, 4, zero_point, false, false).us ? rows : 0;
 }
 
 size_t qgemm_wide_bytes(int N, int K) { return ((size_t)N + 63) / 64 * 64 * K; }
 
 hipError_t launch_qgemm_wide(hipStream_t st, const int8_t* q, const float* scale, const int32_t* zero, int M, int K,
-                             const lrq_tlq_weight& w, const float* bias, void* Y, void* ws, int rows) {
+                             const lrq_tlq_weight& w, const float* bias, void* Y, void* ws, int rows, bool decoded) {
     uint8_t* wdec = static_cast<uint8_t*>(ws);
-    const int units = (w.N + 31) / 32, KB = K / BK;
-    const dim3 grid(units, KB < 32 ? (KB + 3) / 4 : 8);
-    hipLaunchKernelGGL(decode_weights_kernel, grid, dim3(256), 0, st, w.gemm_codes, w.lut, w.N, KB, wdec);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (!decoded) {
+        DecodeJob job;
+        job.gcodes = w.gemm_codes;
+        job.lut = w.lut;
+        job.out = wdec;
+        job.N = w.N;
+        job.KB = K / BK;
+        hipLaunchKernelGGL(decode_weights_kernel, dim3(decode_groups(job, 4)), dim3(256), 0, st, job);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     switch (rows) {
         case 192:
             return zero ? launch_wide<6, true>(st, q, scale, zero, M, K, w, bias, Y, wdec) : launch_wide<6, false>(st, q, scale, zero, M, K, w, bias, Y, wdec);

@@ -5,6 +5,7 @@
 // decision q = rint(u * (qmax / amax)) is one division and one multiplication in IEEE fp64, so the
 // integer codes do not depend on the order in which a kernel schedules its work.
 #include "rotate_common.h"
+#include "weight_decode.h"
 
 namespace lrq {
 namespace {
@@ -102,10 +103,21 @@ __global__ void hadamard_quant_generic_kernel(const uint16_t* __restrict__ X, in
 // DPP moves (a Hadamard block is 2 / 4 adjacent lanes).  A workgroup holds R whole rows, so the only
 // exchange through LDS is the per-row maximum (one 64-bit LDS atomic per quad).  All arithmetic is
 // fp64 and every stage is taken in ascending stride order, like the definition's recursion.
-template <int LOG2H, bool ASYM>
+__device__ __forceinline__ bool decode_workgroup() { return false; }
+__device__ __forceinline__ int rotation_workgroups() { return gridDim.x; }
+__device__ __forceinline__ int rotation_workgroups(const DecodeJob& job) { return job.first; }
+__device__ __forceinline__ bool decode_workgroup(const DecodeJob& job) {
+    if (blockIdx.x < job.first) return false;
+    decode_weights(job, blockIdx.x - job.first, gridDim.x - job.first, blockDim.x / kWave);
+    return true;
+}
+
+// Job: DecodeJob where workgroups past the rotation's own decode weights, else nothing (as a run-time check it costs 0.2 us of a 9 us call)
+template <int LOG2H, bool ASYM, typename... Job>
 __global__ __launch_bounds__(640) void hadamard_quant_e32_kernel(const uint16_t* __restrict__ X, int M, int K,
                                                                   int rows_per_wg, QuantSpec qs,
-                                                                  int8_t* __restrict__ q, float* __restrict__ scale) {
+                                                                  int8_t* __restrict__ q, float* __restrict__ scale, Job... job) {
+    if (decode_workgroup(job...)) return;
     __shared__ unsigned long long amax_bits[2][32];          // [0]: max |u| (or key of max u), [1]: key of max -u
     const int lpr = K / E32;                       // lanes per row
     const int t = threadIdx.x;
@@ -204,11 +216,13 @@ template <int PAD, int STRIDE = 18>
 __device__ __forceinline__ int lds_row(int slot) { return STRIDE * slot + PAD * (slot >> 5); }
 constexpr int lds_pad(int log2h) { return log2h == 12 ? 8 : (log2h == 11 ? 16 : 4); }
 
-template <int LOG2H, bool PERSIST, bool ASYM, bool PRE, bool ONE = false>
+template <int LOG2H, bool PERSIST, bool ASYM, bool PRE, bool ONE, typename... Job>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PERSIST || PRE ? 2 : 3, PERSIST || PRE ? 2 : 3)))
 void hadamard_quant_2pass_kernel(const uint16_t* __restrict__ X, int M, int K,
                                                                    int rows_per_wg, QuantSpec qs,
-                                                                   int8_t* __restrict__ q, float* __restrict__ scale) {
+                                                                   int8_t* __restrict__ q, float* __restrict__ scale, Job... job) {
+    if (decode_workgroup(job...)) return;
+    const int nwg = rotation_workgroups(job...);
     constexpr int G = 1 << (LOG2H - 5);            // pass-1 lanes per block
     constexpr int NG = G < 32 ? G : 32;            // values per element offset held by a pass-2 lane
     constexpr int EPL = 32 / NG;                   // element offsets per pass-2 lane (4, 2, 1)
@@ -252,7 +266,7 @@ void hadamard_quant_2pass_kernel(const uint16_t* __restrict__ X, int M, int K,
     }
     if constexpr (IN_WAVE) __syncthreads();        // amax_bits is clear
     int par = 0;
-    for (int grp = blockIdx.x; grp < ngroups; grp += gridDim.x, par ^= 1) {
+    for (int grp = blockIdx.x; grp < ngroups; grp += nwg, par ^= 1) {
         const int row = grp * rows_per_wg + rw;
         const bool live = inwg && row < M;
         double v[E32], w[E32];
@@ -300,7 +314,7 @@ void hadamard_quant_2pass_kernel(const uint16_t* __restrict__ X, int M, int K,
             }
         }
         if constexpr (PERSIST) {   // next group's data: in flight while pass 2 runs (pass-1 registers are dead by now)
-            int rn = (grp + gridDim.x) * rows_per_wg + rw;
+            int rn = (grp + nwg) * rows_per_wg + rw;
             if (!inwg || rn >= M) rn = M - 1;
             const uint4* src = reinterpret_cast<const uint4*>(X + (size_t)rn * K + (size_t)slot * E32);
 #pragma unroll
@@ -1072,6 +1086,7 @@ static bool e32_shape(int K, int h) { return h <= 128 && K % 128 == 0 && K / E32
 static bool twopass_shape(int K, int h) { return h >= 256 && h <= 4096 && K % 128 == 0 && K / E32 <= 512; }
 bool hadamard_packs_in_kernel(int K, int h) { return e32_shape(K, h) || twopass_shape(K, h); }
 
+bool hadamard_decodes(int K, int h) { return e32_shape(K, h) || twopass_shape(K, h); }
 hipError_t launch_codes_to_fp8(hipStream_t st, int8_t* q, size_t n) {
     const size_t n16 = n / 16;
     hipLaunchKernelGGL(codes_to_fp8_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, st, q, n16);
@@ -1090,13 +1105,22 @@ static void launch_quant_from_f64(hipStream_t st, const double* U, int M, int K,
 }
 
 hipError_t launch_hadamard_quant(hipStream_t st, const uint16_t* X, int M, int K, int h, int act_bits,
-                                 int8_t* q, float* scale, int32_t* zero, const float* prescale, bool packed, bool fp8) {
+                                 int8_t* q, float* scale, int32_t* zero, const float* prescale, bool packed, bool fp8,
+                                 const DecodeJob* decode) {
     QuantSpec qs = make_spec(act_bits, h, zero, prescale);
     if (packed || fp8) {
         if ((packed && fp8) || zero || act_bits != 4 || !hadamard_packs_in_kernel(K, h)) return hipErrorInvalidValue;
         qs.packed = packed;
         qs.fp8 = fp8;
     }
+    if (decode && !hadamard_decodes(K, h)) return hipErrorInvalidValue;
+    // the rotation's workgroups come first; those of the decoding run beside the last of them
+    auto grid_with = [&](DecodeJob& job, unsigned blocks, int threads) {
+        if (decode) job = *decode;
+        job.first = blocks;
+        return dim3(blocks + (decode ? decode_groups(job, threads / kWave) : 0));
+    };
+    DecodeJob job;
     if (e32_shape(K, h)) {
         // R whole rows per workgroup, at most four waves (finer granularity measured faster than nine; 7 rows of 1152 fill four waves)
         const int lpr = K / E32;
@@ -1104,14 +1128,17 @@ hipError_t launch_hadamard_quant(hipStream_t st, const uint16_t* X, int M, int K
         if (R < 1) R = 1;
         if (R > 32) R = 32;
         const int nt = ((lpr * R + kWave - 1) / kWave) * kWave;
-        const dim3 grid((M + R - 1) / R), block(nt);
-#define LRQ_CASE(L)                                                                                              \
-    case L:                                                                                                      \
-        if (qs.asym) hipLaunchKernelGGL((hadamard_quant_e32_kernel<L, true>), grid, block, 0, st, X, M, K, R, qs, q, scale); \
-        else hipLaunchKernelGGL((hadamard_quant_e32_kernel<L, false>), grid, block, 0, st, X, M, K, R, qs, q, scale);        \
+        const dim3 grid = grid_with(job, (M + R - 1) / R, nt), block(nt);
+#define LRQ_E32(L, A)                                                                                                                    \
+    if (decode) hipLaunchKernelGGL((hadamard_quant_e32_kernel<L, A, DecodeJob>), grid, block, 0, st, X, M, K, R, qs, q, scale, job);     \
+    else hipLaunchKernelGGL((hadamard_quant_e32_kernel<L, A>), grid, block, 0, st, X, M, K, R, qs, q, scale);
+#define LRQ_CASE(L)                                                    \
+    case L:                                                            \
+        if (qs.asym) { LRQ_E32(L, true) } else { LRQ_E32(L, false) }   \
         break;
         switch (ilog2(h)) { LRQ_CASE(0) LRQ_CASE(1) LRQ_CASE(2) LRQ_CASE(3) LRQ_CASE(4) LRQ_CASE(5) LRQ_CASE(6) LRQ_CASE(7) }
 #undef LRQ_CASE
+#undef LRQ_E32
         return hipGetLastError();
     }
     if (twopass_shape(K, h)) {
@@ -1139,34 +1166,28 @@ hipError_t launch_hadamard_quant(hipStream_t st, const uint16_t* X, int M, int K
             one = false;
             ldsb = ldsb_two;
         }
-        const dim3 grid(persist ? 256 * per_cu : groups), block(nt);
-#define LRQ_ATTR(L, P, A, S, O) { hipError_t e = allow_large_lds(reinterpret_cast<const void*>(hadamard_quant_2pass_kernel<L, P, A, S, O>), 158 * 1024); if (e != hipSuccess) return e; }
-#define LRQ_ATTR2(L, P, O) { if (qs.asym && qs.prescale) LRQ_ATTR(L, P, true, true, O) else if (qs.asym) LRQ_ATTR(L, P, true, false, O) else if (qs.prescale) LRQ_ATTR(L, P, false, true, O) else LRQ_ATTR(L, P, false, false, O) }
+        const dim3 grid = grid_with(job, persist ? 256 * per_cu : groups, nt), block(nt);
+        auto go = [&](auto kernel, auto... jobs) {
+            const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(kernel), 158 * 1024);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(kernel, grid, block, ldsb, st, X, M, K, R, qs, q, scale, jobs...);
+            return hipGetLastError();
+        };
+#define LRQ_FORM(L, P, A, S, O)                                                          \
+    (decode ? go(hadamard_quant_2pass_kernel<L, P, A, S, O, DecodeJob>, job)             \
+            : go(hadamard_quant_2pass_kernel<L, P, A, S, O>))
+#define LRQ_GO(L, P, O)                                                                                       \
+    (qs.asym ? (qs.prescale ? LRQ_FORM(L, P, true, true, O) : LRQ_FORM(L, P, true, false, O))                 \
+             : (qs.prescale ? LRQ_FORM(L, P, false, true, O) : LRQ_FORM(L, P, false, false, O)))
         switch (ilog2(h)) {
-            case 8: LRQ_ATTR2(8, false, false) break;
-            case 9: LRQ_ATTR2(9, false, false) break;
-            case 10: LRQ_ATTR2(10, false, false) break;
-            case 11: LRQ_ATTR2(11, false, false) break;
-            case 12: if (one) LRQ_ATTR2(12, true, true) else if (persist) LRQ_ATTR2(12, true, false) else LRQ_ATTR2(12, false, false) break;
-        }
-#undef LRQ_ATTR2
-#undef LRQ_ATTR
-#define LRQ_GO(L, P, O)                                                                                                   \
-    {                                                                                                                     \
-        if (qs.asym && qs.prescale) hipLaunchKernelGGL((hadamard_quant_2pass_kernel<L, P, true, true, O>), grid, block, ldsb, st, X, M, K, R, qs, q, scale);   \
-        else if (qs.asym) hipLaunchKernelGGL((hadamard_quant_2pass_kernel<L, P, true, false, O>), grid, block, ldsb, st, X, M, K, R, qs, q, scale);       \
-        else if (qs.prescale) hipLaunchKernelGGL((hadamard_quant_2pass_kernel<L, P, false, true, O>), grid, block, ldsb, st, X, M, K, R, qs, q, scale);   \
-        else hipLaunchKernelGGL((hadamard_quant_2pass_kernel<L, P, false, false, O>), grid, block, ldsb, st, X, M, K, R, qs, q, scale);                   \
-    }
-        switch (ilog2(h)) {
-            case 8: LRQ_GO(8, false, false) break;
-            case 9: LRQ_GO(9, false, false) break;
-            case 10: LRQ_GO(10, false, false) break;
-            case 11: LRQ_GO(11, false, false) break;
-            case 12: if (one) LRQ_GO(12, true, true) else if (persist) LRQ_GO(12, true, false) else LRQ_GO(12, false, false) break;
+            case 8: return LRQ_GO(8, false, false);
+            case 9: return LRQ_GO(9, false, false);
+            case 10: return LRQ_GO(10, false, false);
+            case 11: return LRQ_GO(11, false, false);
+            default: return one ? LRQ_GO(12, true, true) : (persist ? LRQ_GO(12, true, false) : LRQ_GO(12, false, false));
         }
 #undef LRQ_GO
-        return hipGetLastError();
+#undef LRQ_FORM
     }
     const int nt = threads_for_row(K);
     const size_t lds = (size_t)(K + 16) * sizeof(double);
@@ -1179,8 +1200,8 @@ hipError_t launch_hadamard_quant(hipStream_t st, const uint16_t* X, int M, int K
 }
 
 hipError_t launch_plain_quant(hipStream_t st, const uint16_t* X, int M, int K, int act_bits, int8_t* q,
-                              float* scale, int32_t* zero, const float* prescale) {
-    return launch_hadamard_quant(st, X, M, K, 1, act_bits, q, scale, zero, prescale);
+                              float* scale, int32_t* zero, const float* prescale, const DecodeJob* decode) {
+    return launch_hadamard_quant(st, X, M, K, 1, act_bits, q, scale, zero, prescale, false, false, decode);
 }
 
 hipError_t launch_dense_rotate_quant(hipStream_t st, const uint16_t* X, const uint16_t* R, int M, int K,

@@ -893,15 +893,16 @@ def test_qlinear_few_tokens_in_one_launch(lrq, M, K, h, N, w_bits, a_bits, form)
 
 
 @pytest.mark.parametrize("M,N,K,w_bits,asym", [
-    (14009, 1672, 448, 4, False),      # 192 rows, two tiles to some workgroups, odd number of K blocks, cut both ways
-    (9734, 1232, 1152, 4, True),       # 192 rows, zero-points, one round, N no multiple of a channel group
-    (8708, 3224, 320, 4, False),       # 224 rows, five K blocks: the next tile's loads start in the third
+    (17120, 1416, 960, 4, False),      # 224 rows, odd number of K blocks, cut both ways; the weights decoded by a launch of their own
+    (17797, 2720, 832, 4, True),       # 192 rows, odd number of K blocks, several tiles to a workgroup, zero-points
+    (9734, 1232, 1152, 4, True),       # 192 rows, decoded beside the rotation; N no multiple of a channel group
     (16484, 656, 1536, 4, True),       # 224 rows, zero-points
-    (19991, 2216, 320, 4, False),      # 256 rows, three rounds
+    (14393, 824, 1536, 4, False),      # 256 rows
     (19174, 1288, 3072, 4, True),      # 256 rows, zero-points
+    (5000, 2048, 4096, 4, False),      # K past what the decoding of four blocks a wave covers in one workgroup
 ])
 def test_qlinear_with_weights_decoded_once(lrq, M, N, K, w_bits, asym):
-    """The wide GEMM of lrq_qlinear (256-column tiles on decoded weights in the workspace): the integer sums are exact in fp64 and the
+    """The wide GEMM of lrq_qlinear (256-column tiles on weights decoded, beside the rotation, into the workspace): the integer sums are exact in fp64 and the
     rescale is three fp32 operations in a stated order, so outputs are compared bit for bit; a workspace without room for
     the weights gives the same outputs through the other kernels."""
     import torch
