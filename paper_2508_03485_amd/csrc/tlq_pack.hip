@@ -58,7 +58,7 @@ __device__ __forceinline__ double clampd(double v, double lo, double hi) { retur
 //     instead of one after the other in every lane;
 //   * a thread's weights and their logarithms stay in registers (K <= 6144), longer rows keep the logarithms in LDS.
 // Measured at 4608 x 1152 with 21 candidates per sign: 1490 us with a pass per sign, an exp2 and a division per weight and
-// candidate and one ordered sum after the other; 177 us in this form
+// candidate and one ordered sum after the other; 177 us in this form with selects by sign, 169 us with masks
 // (about 65 us of them the logarithms, the encoding and the packing, 5 us each candidate).
 constexpr int PSTRIDE = NT + 1;          // one double of padding: the lanes that sum in parallel read distinct banks
 constexpr double kMagic = 6755399441055744.0;   // 1.5 * 2^52: adding it rounds to an integer, ties to even
@@ -66,7 +66,7 @@ constexpr double kMagic = 6755399441055744.0;   // 1.5 * 2^52: adding it rounds 
 struct Candidate {
     double s, inv, z;
     int zlow;                            // z + lowest level index of the sign
-    int mode;                            // 0: skipped, 1: 1 / s settles the rounding (see above), 2: always divide
+    int mode;                            // 0: skipped, 1: 1 / s settles the rounding (see above) and levels have finite squares, 2: always divide
 };
 
 // NC candidates per pass: 8 (NC * 2 * 257 doubles of partial sums are 33 KB: four workgroups per CU), 4 where a row of
@@ -103,6 +103,23 @@ __device__ void search_clip(const float* __restrict__ w, const double* __restric
         S.best_c[t] = 1.0f;
         S.best_g[t] = 1.0f;
     }
+    // MASKS: 1.0 where the weight has the sign, 0.0 elsewhere.  A fused multiply-add by it adds the square or + 0.0 exactly as a
+    // select and an addition do, in one instruction instead of three (the loop is bound by issue).  It needs finite squares:
+    // threads with an infinity or a NaN always take the general form, and so do candidates with huge levels (mode 2).
+    // Not at 24 weights a thread, where the masks spill (1500 x 6144: 245 us with the selects, 277 us with masks); 4000 x 2304:
+    // 248 -> 233 us, 9216 x 3072: 670 -> 643 us, 1000 x 4608: 134 -> 126 us.
+    constexpr bool MASKS = REGS && NE <= 18;
+    double is_pos[MASKS ? NE : 1], is_neg[MASKS ? NE : 1];
+    bool not_finite = false;
+    if constexpr (MASKS) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            is_pos[e] = wv[e] > 0.0f ? 1.0 : 0.0;
+            is_neg[e] = wv[e] < 0.0f ? 1.0 : 0.0;
+            not_finite |= !(fabsf(wv[e]) < INFINITY);
+            asm volatile("" : "+v"(is_pos[e]), "+v"(is_neg[e]));              // kept, not derived again
+        }
+    }
     for (int c0 = 0; c0 < total; c0 += NC) {
         const int nc = total - c0 < NC ? total - c0 : NC;
         if (t < NC * 2) {
@@ -115,7 +132,8 @@ __device__ void search_clip(const float* __restrict__ w, const double* __restric
                     c.s = (T - B) / (double)(side ? half : half - 1);
                     c.z = rint(B / c.s);
                     c.inv = 1.0 / c.s;
-                    c.mode = fmax(fmax(fabs(wmax[side]), fabs(wmin[side])) * c.inv, fabs(c.z)) <= 1048576.0 ? 1 : 2;
+                    c.mode = fmax(fmax(fabs(wmax[side]), fabs(wmin[side])) * c.inv, fabs(c.z)) <= 1048576.0 &&
+                                     fmax(fabs(T), fabs(B)) <= 240.0 ? 1 : 2;        // levels below 2^480: finite squares
                     c.zlow = c.mode == 1 ? (int)c.z + side : 0;
                 }
             }
@@ -125,7 +143,7 @@ __device__ void search_clip(const float* __restrict__ w, const double* __restric
         if (t < NC * 16) {
             const int j = t / 16, side = (t / 8) % 2, i = t % 8;
             const Candidate c = S.cand[j][side];
-            if (i < half && c.mode) S.level[j][side][i] = exp2(c.s * ((double)(i + side) + c.z));
+            if (i < half) S.level[j][side][i] = c.mode ? exp2(c.s * ((double)(i + side) + c.z)) : 0.0;   // skipped: finite all the same
         }
         __syncthreads();
         for (int base = 0; base < K; base += NT * NE) {
@@ -141,7 +159,7 @@ __device__ void search_clip(const float* __restrict__ w, const double* __restric
                 const Candidate cp = S.cand[j][0], cn = S.cand[j][1];
                 double ep = base ? S.part[j][0][t] : 0.0, en = base ? S.part[j][1][t] : 0.0;
                 const double ep0 = ep, en0 = en;
-                bool unsettled = cp.mode == 2 || cn.mode == 2;
+                bool unsettled = cp.mode == 2 || cn.mode == 2 || not_finite;
                 // what is derived from a weight (sign, double) is derived again for every candidate, not kept in registers
 #pragma unroll
                 for (int e = 0; e < NE; ++e) asm volatile("" : "+v"(wv[e]));
@@ -154,8 +172,13 @@ __device__ void search_clip(const float* __restrict__ w, const double* __restric
                     const int i = min(max(__double2loint(m) - (neg ? cn.zlow : cp.zlow), 0), half - 1);
                     const double d = S.level[j][neg ? 1 : 0][i] - fabs((double)wv[e]);
                     const double d2 = d * d;
-                    ep = ep + (wv[e] > 0.0f ? d2 : 0.0);          // + 0.0 leaves the other sign's sum as it is
-                    en = en + (neg ? d2 : 0.0);
+                    if constexpr (MASKS) {                        // d2 or + 0.0, which leaves the other sign's sum as it is
+                        ep = fma(d2, is_pos[e], ep);
+                        en = fma(d2, is_neg[e], en);
+                    } else {
+                        ep = ep + (wv[e] > 0.0f ? d2 : 0.0);
+                        en = en + (neg ? d2 : 0.0);
+                    }
                     if (e % 3 == 2) __builtin_amdgcn_sched_barrier(0);   // three in flight
                 }
                 if (unsettled) {                                  // rare: this thread's terms again, with the quotient itself

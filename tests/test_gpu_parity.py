@@ -679,6 +679,25 @@ def test_tlq_search_with_quotients_past_the_reciprocal_range(lrq):
     assert np.array_equal(w.codes.cpu().numpy(), oracle.pack_codes(want, 4))
 
 
+@pytest.mark.parametrize("K,bits", [(320, 4), (1152, 4), (1536, 3), (4608, 4), (6144, 4)])
+def test_tlq_search_with_skipped_sides_and_huge_levels(lrq, K, bits):
+    """The sums of the two signs share one pass over a row: a candidate that is skipped on one side (all its magnitudes equal,
+    no weight of the sign, a factor that turns the range over, a shorter grid) and one whose levels or their squares pass
+    what fp64 holds (factors of 200 and 300 on log2|w| = 2) leave the other side's sum as it is."""
+    print(f"case tlq skipped sides K={K} b={bits}", flush=True)
+    W = synth.make_weights(6, K, (948, K, bits))
+    W[0] = np.where(W[0] > 0, np.float32(0.25), W[0])
+    W[1] = np.where(W[1] < 0, np.float32(-2.0), W[1])
+    W[2] = np.abs(W[2])
+    W[3] = -np.abs(W[3])
+    W[4, 0], W[4, 1] = 4.0, -3.0
+    alpha = np.array([1.0, 200.0, 0.9, 300.0, -1.0], np.float32)
+    beta = np.array([300.0, 0.95, 200.0], np.float32)
+    with np.errstate(all="ignore"):
+        _check_weight(lrq, W, bits, 7, alpha, beta)
+        _check_weight(lrq, W, bits, 7, beta, alpha)
+
+
 @pytest.mark.parametrize("N,K,bits", [(70, 192, 4), (48, 128, 3), (33, 64, 4)])
 def test_gemm_code_tiling_matches_its_description(lrq, N, K, bits):
     """The GEMM's private copy of the weight codes: units of (32 channels x 64 k) stored [channel tile][K block], 64 slots
