@@ -380,6 +380,11 @@ def main():
                     traffic=None, note="multiply-accumulates counted as 2 ops; averaged over the "
                     "workload's layers, %d launches each" % ksteps,
                     avg_launch_ms=round(gemm_total_ms / len(layers), 4))
+    if not (args.levels or fp8 or packed or args.graph) and ms_per_step > sum(rot_ms):
+        # the product as the timed step runs it: lrq_qlinear, unlike lrq_qgemm, has room to decode the weights of large 4-bit layers once
+        # (qgemm_wide_kernel), so its share is the step less the rotate + quantize calls
+        step_tops = total_ops / ((ms_per_step - sum(rot_ms)) * 1e-3) / 1e12
+        roofline.update(in_step_achieved=round(step_tops, 2), in_step_frac=round(step_tops / mfma_peak, 4))
     # Hadamard rotate+quantize: algorithmic bytes = 2 (bf16 in) + 1 (code out) per element + 4 per token
     had = [(li, l) for li, l in enumerate(layers) if l["spec"].rotation == "hadamard"]
     roofline_rq = None
