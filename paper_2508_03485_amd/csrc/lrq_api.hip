@@ -311,10 +311,17 @@ size_t lrq_workspace_bytes_asym(int M, int N, int K, const lrq_rotation* rot, in
 
 enum class Gemm { kInt8, kInt8Zero, kLevels };
 
-// Whether the int8 layer runs as one kernel: a few tokens, and a rotation that every workgroup can repeat.
-static bool one_launch(int M, int N, int K, const lrq_rotation* rot) {
-    return (rot->kind == LRQ_ROT_NONE && lrq::qlinear_few_applies(M, N, K, 1)) ||
-           (rot->kind == LRQ_ROT_HADAMARD && lrq::qlinear_few_applies(M, N, K, rot->had_block));
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    return reinterpret_cast<uintptr_t>(a) < reinterpret_cast<uintptr_t>(b) + nb && reinterpret_cast<uintptr_t>(b) < reinterpret_cast<uintptr_t>(a) + na;
+}
+
+// Whether the int8 layer runs as one kernel: a few tokens, and a rotation that every workgroup can repeat.  An output that overlaps what
+// the rotation reads (a layer in place) needs the two launches, where the rotation has ended before the output is written.
+static bool one_launch(const void* X, int M, int K, const lrq_rotation* rot, int N, int out_dtype, const void* Y) {
+    const size_t out = (size_t)M * N * (out_dtype == LRQ_OUT_FP32 ? 4 : 2);
+    return ((rot->kind == LRQ_ROT_NONE && lrq::qlinear_few_applies(M, N, K, 1)) ||
+            (rot->kind == LRQ_ROT_HADAMARD && lrq::qlinear_few_applies(M, N, K, rot->had_block))) &&
+           !overlap(Y, out, X, (size_t)M * K * 2) && !(rot->prescale && overlap(Y, out, rot->prescale, (size_t)K * 4));
 }
 static int run_one_launch(hipStream_t st, const void* X, int M, int K, const lrq_rotation* rot, int act_bits, bool asym,
                           const lrq_tlq_weight* w, const float* bias, int out_dtype, void* Y) {
@@ -399,7 +406,7 @@ static int qlinear_impl(void* stream, const void* X, int M, int K, const lrq_rot
     void* rot_ws = base + round256((size_t)M * K) + round256((size_t)M * sizeof(float));
     int32_t* zero = asym ? reinterpret_cast<int32_t*>(static_cast<char*>(rot_ws) + ars_layout(M, K, rot).total) : nullptr;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (kind != Gemm::kLevels && one_launch(M, w->N, K, rot)) return run_one_launch(s, X, M, K, rot, act_bits, asym, w, bias, out_dtype, Y);
+    if (kind != Gemm::kLevels && one_launch(X, M, K, rot, w->N, out_dtype, Y)) return run_one_launch(s, X, M, K, rot, act_bits, asym, w, bias, out_dtype, Y);
     void* wide = nullptr;
     const size_t bytes = lrq::qgemm_wide_bytes(w->N, K);
     if (kind != Gemm::kLevels) {
@@ -510,7 +517,7 @@ int lrq_qlinear_packed4(void* stream, const void* X, int M, int K, const lrq_rot
     float* scale = reinterpret_cast<float*>(base + round256((size_t)M * K / 2));
     void* rot_ws = base + round256((size_t)M * K / 2) + round256((size_t)M * sizeof(float));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (one_launch(M, w->N, K, rot)) return run_one_launch(s, X, M, K, rot, 4, false, w, bias, out_dtype, Y);
+    if (one_launch(X, M, K, rot, w->N, out_dtype, Y)) return run_one_launch(s, X, M, K, rot, 4, false, w, bias, out_dtype, Y);
     st = rotate_quant_packed4(s, X, M, K, rot, q4, scale, rot_ws);
     if (st != LRQ_OK) return st;
     return lrq::launch_qgemm(s, reinterpret_cast<const int8_t*>(q4), scale, nullptr, M, K, *w, bias, out_dtype, Y, true) == hipSuccess

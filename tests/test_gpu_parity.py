@@ -911,6 +911,26 @@ def test_qlinear_few_tokens_in_one_launch(lrq, M, K, h, N, w_bits, a_bits, form)
         assert torch.equal(y, ref)
 
 
+@pytest.mark.parametrize("form,shift", [("symmetric", 0), ("packed", 0), ("zero_point", 64), ("symmetric", -64)])
+def test_qlinear_few_tokens_over_its_own_input(lrq, form, shift):
+    """Y over X, in place or `shift` bytes beside it: every workgroup of the one-launch form reads all of X, so these calls take the
+    two launches, whose rotation has ended before the first output is written."""
+    import torch
+    M, K = 6, 1152
+    print(f"case few in place {form} {shift}", flush=True)
+    gd = to_dev(np.array([1.0, 1.5], np.float32))
+    w = lrq.tlq_quantize_pack(to_dev(synth.make_weights(K, K, (913, K, K))), 4, 7, gd, gd)
+    X = bf16_to_dev(_acts(M, K, 76))
+    rot = lrq.Rotation("hadamard", 128)
+    call = (lambda x, y: lrq.qlinear_packed4(x, rot, w, out=y)) if form == "packed" else (
+        lambda x, y: lrq.qlinear(x, rot, 4, w, out=y, asym=form == "zero_point"))
+    ref = call(X, torch.empty_like(X))
+    buf = torch.zeros(M * K + 64, dtype=X.dtype, device="cuda")
+    x, y = (buf[32 + s // 2:][:M * K].view(M, K) for s in (0, shift))
+    x.copy_(X)
+    assert torch.equal(call(x, y), ref)
+
+
 @pytest.mark.parametrize("M,N,K,w_bits,asym", [
     (17120, 1416, 960, 4, False),      # 224 rows, odd number of K blocks, cut both ways; the weights decoded by a launch of their own
     (17797, 2720, 832, 4, True),       # 192 rows, odd number of K blocks, several tiles to a workgroup, zero-points
