@@ -263,8 +263,8 @@ int lrq_qlinear(void* stream, const void* X, int M, int K, const lrq_rotation* r
  * and the rotation scratch live in a buffer of lrq_static_scratch_bytes() = 64 MiB that is part of the library's
  * code object (every device the library runs on holds one copy until the process ends).  The call allocates and
  * frees nothing.
- *   - A layer whose lrq_workspace_bytes(M, N, K, rot, act_bits) exceeds the buffer is refused with LRQ_ESCRATCH and
- *     nothing is launched (Hadamard layers fit up to M * K of about 6.7e7: all layers of the 8192- and 4608-token
+ *   - A layer whose codes, scales and rotation scratch (lrq_workspace_bytes for N = 0) exceed the buffer is refused with
+ *     LRQ_ESCRATCH and nothing is launched; one that only leaves no room for decoded weights decodes them inside the GEMM (Hadamard layers fit up to M * K of about 6.7e7: all layers of the 8192- and 4608-token
  *     workloads; dense rotations up to M * K of about 7e6).
  *   - Every call on a device uses that device's one buffer: calls that may overlap on one device (different
  *     streams, or several host threads) race on it and must be ordered by the caller.  The buffer keeps the previous
