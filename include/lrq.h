@@ -264,8 +264,9 @@ int lrq_qlinear(void* stream, const void* X, int M, int K, const lrq_rotation* r
  * code object (every device the library runs on holds one copy until the process ends).  The call allocates and
  * frees nothing.
  *   - A layer whose codes, scales and rotation scratch (lrq_workspace_bytes for N = 0) exceed the buffer is refused with
- *     LRQ_ESCRATCH and nothing is launched; one that only leaves no room for decoded weights decodes them inside the GEMM (Hadamard layers fit up to M * K of about 6.7e7: all layers of the 8192- and 4608-token
- *     workloads; dense rotations up to M * K of about 7e6).
+ *     LRQ_ESCRATCH and nothing is launched (Hadamard layers fit up to M * K of about 6.7e7: all layers of the 8192- and
+ *     4608-token workloads; dense rotations up to M * K of about 7e6).  One that leaves no room for the decoded weights
+ *     decodes them inside the GEMM.
  *   - Every call on a device uses that device's one buffer: calls that may overlap on one device (different
  *     streams, or several host threads) race on it and must be ordered by the caller.  The buffer keeps the previous
  *     call's contents; the kernels overwrite what they read, nothing relies on its state.
