@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void decode_weights_kernel(DecodeJob job) { de
 // 64 lanes x 16 bytes from global memory into LDS: lane l's bytes land at lds + 16 l.  In assembly, with no register written, because
 // the compiler would wait for every load of this kind before any later LDS read; the waits are the WAIT_LOADS below.
 __device__ __forceinline__ void load_to_lds(unsigned lds, unsigned voff, const void* base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
 // all but the wave's latest n vector-memory operations have finished
 #define LRQ_WAIT_LOADS(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")

@@ -296,3 +296,16 @@ def test_qgemm_diagnostics(L):
     assert seen == built
     # output rows that are not aligned keep the tall shape where other tiles hide their stores
     assert lrq.qgemm_tile(35100, 12001, 3072, 4) == (128, 256) and lrq.qgemm_tile(20000, 9001, 3072, 4) == (128, 256)
+
+
+def test_inline_assembly_names_m0_where_it_writes_it():
+    """m0 is an ordinary register to the compiler: an asm statement that sets it has to say so, or a value that the compiler keeps
+    there is lost."""
+    csrc = os.path.join(ROOT, "paper_2508_03485_amd", "csrc")
+    seen = 0
+    for name in os.listdir(csrc):
+        for stmt in re.findall(r"asm(?:\s+volatile)?\s*\((.*?)\);", open(os.path.join(csrc, name)).read(), re.S):
+            if re.search(r"\bs_\w+\s+m0\b", stmt):
+                seen += 1
+                assert re.search(r'"m0"', stmt.rsplit(":", 1)[1]), f"{name}: {stmt}"
+    assert seen
