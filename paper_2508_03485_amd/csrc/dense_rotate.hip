@@ -26,6 +26,7 @@
 //   S <= rho * sqrt(sum_{|x_k| < theta} x_k^2)  +  sum_{|x_k| >= theta} |x_k| * max_j |R_kj|
 // (Cauchy-Schwarz on the many small entries, rho = max_j ||R[:, j]||_2; the few large ones - salient channels - term by
 // term), theta = 4 * mean |x|.  u~ is stored as fp32: one more rounding, 2^-24 |u~| <= 2^-24 S.
+// What fp32 cannot hold to full precision - squares, products and sums below 2^-126 - is bounded absolutely and added to the bound.
 #include "lrq_internal.h"
 
 namespace lrq {
@@ -537,9 +538,12 @@ __global__ __launch_bounds__(256) void dense_row_candidates_kernel(const uint16_
     }
     small2 = wave_sumf(small2);
     big = wave_sumf(big);
-    const float rho = sqrtf(__uint_as_float(*rho2_bits)) * kBoundSlack;
-    const float S = (rho * sqrtf(small2) * kBoundSlack + big) * kBoundSlack;       // >= sum_k |x_k| |R_kj| for every j
-    const double e = (double)S * (double)err_factor;
+    // squares below 2^-126 lose bits or vanish: at most K 2^-126 of either sum; products and sums below it cost at most K 2^-126 absolutely, and
+    // so do subnormal factors times the other operand's magnitude
+    const float lost = sqrtf((float)K) * 0x1p-62f;
+    const float rho = (sqrtf(__uint_as_float(*rho2_bits)) + lost) * kBoundSlack;
+    const float S = (rho * (sqrtf(small2) + lost) * kBoundSlack + big) * kBoundSlack;      // >= sum_k |x_k| |R_kj| for every j
+    const double e = (double)S * (double)err_factor + (double)K * 0x1p-125 * (1.0 + (double)rho + (double)s1);
     // row maximum of |u~| (zero-point form: maximum and minimum of u~) and the elements within 2 eps of it
     int whole = 0, cnt[2] = {0, 0};
     const float* ur = Ut + (size_t)row * K;
@@ -550,7 +554,7 @@ __global__ __launch_bounds__(256) void dense_row_candidates_kernel(const uint16_
         for (int c = lane; c < nseg; c += kWave) mx = fmaxf(mx, sm[c]);
         mx = wave_maxf(mx);
         int n = 0;
-        if (S > 0.0f && !whole) {                // otherwise x is all zero (or not finite) and there is nothing to decide
+        if (s1 > 0.0f && S > 0.0f && !whole) {   // otherwise x is all zero (or not finite) and there is nothing to decide
             const float lf = (float)((double)mx - 2.0 * e);
             const float lim = lf - fabsf(lf) * 1e-6f;                                  // rounded down: never misses a candidate
             for (int base = 0; base < nseg && !whole; base += kWave) {
@@ -578,7 +582,7 @@ __global__ __launch_bounds__(256) void dense_row_candidates_kernel(const uint16_
     if (lane == 0) {
         eps[row] = e;
         // no search (all-zero row): u is 0 everywhere
-        const bool zero_row = !(S > 0.0f);
+        const bool zero_row = !(s1 > 0.0f);
         amax_bits[2 * (size_t)row] = ASYM && zero_row ? okey(0.0) : 0ull;
         amax_bits[2 * (size_t)row + 1] = ASYM && zero_row ? okey(0.0) : 0ull;
         ccount[2 * (size_t)row] = cnt[0];

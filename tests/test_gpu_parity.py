@@ -270,6 +270,31 @@ def test_dense_rotation_random_shapes(lrq, seed):
         assert np.array_equal(a.cpu().numpy(), b)
 
 
+@pytest.mark.parametrize("r_exp", [0, -70, 60])
+@pytest.mark.parametrize("asym", [False, True])
+def test_dense_rotation_rows_of_any_magnitude(lrq, r_exp, asym):
+    """Rows from the subnormal bf16 values up to 2^110 (and R scaled as well): squares, products and sums leave the range in which fp32
+    holds them to full precision, and the codes must still be those of the all-fp64 evaluation."""
+    import torch
+    M, K = 140, 256
+    print(f"case dense magnitudes r_exp={r_exp} asym={asym}", flush=True)
+    g = synth.rng_for(946, r_exp + 100)
+    exps = np.array([-132, -126, -110, -90, -76, -74, -72, -70, -68, -66, -63, -60, -40, 0, 0, 40, 62, 66, 90, 110])
+    x = g.standard_normal((M, K)) * np.exp2(exps[np.arange(M) % len(exps)])[:, None]
+    x[13] = 0.0
+    x[35, 1:] = 0.0                                      # one value
+    R = np.linalg.qr(g.standard_normal((K, K)))[0] * 2.0 ** r_exp
+    X, Rd = (bf16_to_dev(synth.f32_to_bf16_bits(a.astype(np.float32))) for a in (x, R))
+    ref = lrq.ars_rotate_quant(X, lrq.Rotation("dense_f64", 0, Rd), 8, asym=asym)
+    for prepared in (False, True):
+        rot = lrq.Rotation("dense", 0, Rd)
+        rot.prepared = lrq.ars_dense_prepare(Rd) if prepared else None
+        got = lrq.ars_rotate_quant(X, rot, 8, asym=asym)
+        for a, b in zip(got, ref):
+            bad = (a != b).reshape(M, -1).any(dim=1).nonzero().flatten().tolist()
+            assert not bad, f"rows of 2^{sorted(set(exps[np.array(bad) % len(exps)].tolist()))} differ"
+
+
 @pytest.mark.parametrize("M,K", [(70, 128), (66, 2048), (130, 3200), (4200, 2176), (6200, 128)])
 @pytest.mark.parametrize("asym", [False, True])
 def test_dense_rotation_exact_ties(lrq, M, K, asym):
