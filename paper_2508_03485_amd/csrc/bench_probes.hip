@@ -73,6 +73,23 @@ __global__ __launch_bounds__(256) void copy_probe_kernel(const v4u* __restrict__
     if (i < n16) __builtin_nontemporal_store(__builtin_nontemporal_load(&src[i]), &dst[i]);
 }
 
+// One v_mfma_f32_32x32x16_bf16 per workgroup (one wave), operands and addend as given: D = C + A.B^T, A and B [32][16] bf16, C and D
+// [32][32] fp32.  For the rounding of the instruction itself, on which the dense rotation's error bound rests.
+typedef short v8s __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+__global__ __launch_bounds__(64) void mfma_bf16_once_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
+                                                            const float* __restrict__ C, float* __restrict__ D) {
+    const int lane = threadIdx.x, at = (lane % 32) * 16 + (lane / 32) * 8;          // row lane % 32, k = 8 (lane / 32) + [0, 8)
+    const v8s a = *reinterpret_cast<const v8s*>(A + (size_t)blockIdx.x * 512 + at);
+    const v8s b = *reinterpret_cast<const v8s*>(B + (size_t)blockIdx.x * 512 + at);
+    v16f c;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) c[r] = C[(size_t)blockIdx.x * 1024 + (8 * (r / 4) + 4 * (lane / 32) + r % 4) * 32 + lane % 32];
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) D[(size_t)blockIdx.x * 1024 + (8 * (r / 4) + 4 * (lane / 32) + r % 4) * 32 + lane % 32] = c[r];
+}
+
 }  // namespace
 
 extern "C" {
@@ -98,6 +115,15 @@ __attribute__((visibility("default"))) int bench_probe_copy(void* stream, const 
     const size_t n16 = bytes / 16;
     hipLaunchKernelGGL(copy_probe_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, static_cast<hipStream_t>(stream),
                        static_cast<const v4u*>(src), static_cast<v4u*>(dst), n16);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// n independent matrix instructions D[i] = C[i] + A[i].B[i]^T: A, B bf16 [n, 32, 16], C, D float [n, 32, 32].  Returns 0 or -1.
+__attribute__((visibility("default"))) int bench_probe_mfma_bf16(void* stream, int n, const void* A, const void* B, const float* C,
+                                                                 float* D) {
+    if (n <= 0 || !A || !B || !C || !D) return -1;
+    hipLaunchKernelGGL(mfma_bf16_once_kernel, dim3(n), dim3(64), 0, static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(A),
+                       static_cast<const uint16_t*>(B), C, D);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

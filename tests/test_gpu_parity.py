@@ -270,6 +270,65 @@ def test_dense_rotation_random_shapes(lrq, seed):
         assert np.array_equal(a.cpu().numpy(), b)
 
 
+@pytest.mark.parametrize("kind", ["mixed", "small", "cut", "halves"])
+def test_rounding_of_the_bf16_matrix_instruction(lrq, kind):
+    """The dense rotation's bound rests on how v_mfma_f32_32x32x16_bf16 rounds: single instructions against the steps that
+    oracle.matrix_core describes, bit for bit, and runs of two against the run's bound.  One instruction errs by up to
+    9.9 2^-24 (|C| + sum |a b|) on these operands ("cut")."""
+    import ctypes
+    import torch
+    from oracle import matrix_core
+    from paper_2508_03485_amd.build import PROBES
+    probe = ctypes.CDLL(PROBES).bench_probe_mfma_bf16
+    probe.argtypes = [ctypes.c_void_p, ctypes.c_int] + [ctypes.c_void_p] * 4
+    n = 48
+    print(f"case matrix instruction {kind}", flush=True)
+    g = synth.rng_for(947, len(kind))
+
+    def run(a, b, c):
+        d = torch.empty((n, 32, 32), dtype=torch.float32, device="cuda")
+        da, db = (bf16_to_dev(synth.f32_to_bf16_bits(v.astype(np.float32))) for v in (a, b))
+        dc = to_dev(c.astype(np.float32))
+        assert probe(torch.cuda.current_stream().cuda_stream, n, da.data_ptr(), db.data_ptr(), dc.data_ptr(), d.data_ptr()) == 0
+        return d.cpu().numpy().astype(np.float64)
+
+    def pairs(a, b):
+        return np.broadcast_arrays(a[:, :, None, :], b[:, None, :, :])
+    a, b, c = matrix_core.adversarial_operands(g, n, kind)
+    assert np.array_equal(run(a, b, c), matrix_core.mfma_bf16(*pairs(a, b), c))
+    a2, b2, _ = matrix_core.adversarial_operands(g, n, kind)
+    if kind in ("cut", "halves"):
+        a2 = np.abs(a2) * np.sign(a[:, :1, :1])              # both instructions lose on the same side
+    first = run(a, b, np.zeros_like(c))
+    second = run(a2, b2, first)
+    assert np.array_equal(second, matrix_core.mfma_bf16(*pairs(a2, b2), first))
+    exact = a @ b.transpose(0, 2, 1) + a2 @ b2.transpose(0, 2, 1)            # 53 bits: far below the error looked at
+    size = np.abs(a) @ np.abs(b).transpose(0, 2, 1) + np.abs(a2) @ np.abs(b2).transpose(0, 2, 1)
+    err = np.abs(second - exact)
+    print(f"  {kind}: run error at most {np.max(err / size) * 2 ** 24:.2f} 2^-24 S", flush=True)
+    assert np.all(err <= matrix_core.RUN_ERROR * size + 2.0 ** -147)         # four roundings among the subnormal values
+
+
+def test_dense_rotation_uses_the_bound_of_a_run(lrq):
+    """A row with a single 1: S is the largest |R_kj| of its channel (times the 0.4 % with which S is evaluated), and the bound has to
+    hold a run's error and eight further roundings of 2^-24 S."""
+    import torch
+    from oracle import matrix_core
+    assert matrix_core.RUN_ERROR <= matrix_core.RUN_ERROR_USED
+    M, K = 70, 256
+    g = synth.rng_for(949, K)
+    R = synth.f32_to_bf16_bits(np.linalg.qr(g.standard_normal((K, K)))[0].astype(np.float32))
+    x = np.zeros((M, K), np.float32)
+    x[np.arange(M), 3 * np.arange(M)] = 1.0
+    rot = lrq.Rotation("dense", 0, bf16_to_dev(R))
+    ws = torch.zeros(lrq.ars_workspace_bytes(M, K, rot, 8), dtype=torch.uint8, device="cuda")
+    lrq.ars_rotate_quant(bf16_to_dev(synth.f32_to_bf16_bits(x)), rot, 8, workspace=ws)
+    eps = lrq.ars_dense_diagnostics(ws, M, K)[1].cpu().numpy()
+    factor = eps / np.abs(oracle.bf16_bits_to_f64(R)).max(axis=1)[3 * np.arange(M)]
+    want = matrix_core.RUN_ERROR_USED + 8 * 2.0 ** -24
+    assert np.all(factor >= want) and np.all(factor <= 1.02 * want)
+
+
 @pytest.mark.parametrize("r_exp", [0, -70, 60])
 @pytest.mark.parametrize("asym", [False, True])
 def test_dense_rotation_rows_of_any_magnitude(lrq, r_exp, asym):
