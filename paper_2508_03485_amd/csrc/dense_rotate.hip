@@ -116,6 +116,9 @@ __device__ __forceinline__ float wave_maxf(float v) {
     return v;
 }
 
+// a value that all lanes hold, in a scalar register
+__device__ __forceinline__ float uniform(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
+
 // ---- statistics of a K x K bf16 matrix A, one workgroup per row: maxabs[row] = max_j |A[row, j]| (if maxabs) and
 // *sumsq_max = max over rows of sum_j A[row, j]^2 (if sumsq_max; float bits, atomic max - zero it first).  Run on R it
 // gives max_j |R_kj| per k; run on R transposed it gives rho^2.  zero_words: the launch on R also clears the scalars.
@@ -521,8 +524,8 @@ __global__ __launch_bounds__(256) void dense_row_candidates_kernel(const uint16_
             for (int d = 0; d < 4; ++d) s1 += fabsf(bf16_lo(w[d])) + fabsf(bf16_hi(w[d]));
         }
     }
-    s1 = wave_sumf(s1);
-    const float theta = 4.0f * s1 / (float)K;
+    s1 = uniform(wave_sumf(s1));
+    const float theta = uniform(4.0f * s1 / (float)K);
     float small2 = 0.0f, big = 0.0f;
 #pragma unroll
     for (int i = 0; i < xiters; ++i) {
@@ -546,8 +549,8 @@ __global__ __launch_bounds__(256) void dense_row_candidates_kernel(const uint16_
     // so do subnormal factors times the other operand's magnitude
     const float lost = sqrtf((float)K) * 0x1p-62f;
     const float rho = (sqrtf(__uint_as_float(*rho2_bits)) + lost) * kBoundSlack;
-    const float S = (rho * (sqrtf(small2) + lost) * kBoundSlack + big) * kBoundSlack;      // >= sum_k |x_k| |R_kj| for every j
-    const double e = (double)S * (double)err_factor + (double)K * 0x1p-125 * (1.0 + (double)rho + (double)s1);
+    const float S = uniform((rho * (sqrtf(small2) + lost) * kBoundSlack + big) * kBoundSlack);      // >= sum_k |x_k| |R_kj| for every j
+    const double e = (double)S * (double)err_factor + (double)uniform((1.0f + rho + s1) * ((float)K * 0x1p-124f));
     // row maximum of |u~| (zero-point form: maximum and minimum of u~) and the elements within 2 eps of it
     int whole = 0, cnt[2] = {0, 0};
     const float* ur = Ut + (size_t)row * K;
@@ -622,7 +625,7 @@ __global__ __launch_bounds__(256) void dense_exact_amax_kernel(const uint16_t* X
     constexpr int PP = 8 / LPA, DEPTH = XA_DEPTH / PP;       // pieces of a lane, lines in flight
     const int p = threadIdx.x % LPA;
     const long i = ((long)blockIdx.x * 256 + threadIdx.x) / LPA;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *nwhole = 0;                // for dense_quant_kernel
+    if (blockIdx.x == 0 && threadIdx.x < 2) nwhole[threadIdx.x] = 0;     // rows to recompute as a whole, and how many of them are taken
     int row = 0, col = 0, side = 0;
     bool have = false;
     if (i < (long)M * CAPC * (ASYM ? 2 : 1)) {
@@ -684,28 +687,33 @@ __global__ __launch_bounds__(256) void dense_exact_amax_kernel(const uint16_t* X
 // ---- codes from u~ with the exact amax (zero-point form: the exact maximum and minimum), one wave per row.  The elements that the
 // bound leaves undecided are listed in LDS and settled right away: 16 lanes sum the products of one element in fp64, each every
 // sixteenth piece of 8 k.  That sum is not the definition's (its additions round in another order), but both lie within
-// K 2^-53 S of the real number, and that bound settles the code unless u inv comes within some 1e-11 of a half-integer; what is
-// left then (exact ties) runs the definition's chain, an element to a lane.  Rows with more undecided elements than capf go to a list
-// and are recomputed as a whole.  While some waves wait for operands (an element reads its R column, 2 K bytes, mostly from the
+// K 2^-53 S of the real number, and that bound settles the code unless u inv comes within some 1e-11 of a half-integer.  What is
+// left then (exact ties) goes to the row's list of late elements, for which the next kernel runs the definition's chain, an element to a
+// lane.  Such elements come in numbers (an R that permutes, x on a coarse grid): where most of what a wave has summed is left over, it
+// lists the rest of its row unseen, and so do rows with many undecided elements, whose chains fill a wave better than sixteen lanes an
+// element do.  Rows with more than capf are recomputed as a whole.
+// While some waves wait for operands (an element reads its R column, 2 K bytes, mostly from the
 // Infinity Cache), others stream u~: flagging, a prefix sum over the rows' counts and the chains for all undecided elements take 11.5 +
 // 4.7 + 25.8 us at 8192 x 1152 as kernels of their own (below), this one 15.2 us; where it is used: quant_in_one.
 template <bool ASYM>
-__global__ __launch_bounds__(256) void dense_quant_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Rt,
+__global__ __launch_bounds__(256, ASYM ? 7 : 8) void dense_quant_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ Rt,
                                                           const float* __restrict__ Ut, int M, int K, double qmax, double err_factor,
                                                           const double* __restrict__ eps,
                                                           const unsigned long long* __restrict__ amax_bits, int8_t* __restrict__ q,
                                                           float* __restrict__ scale, int32_t* __restrict__ zero,
-                                                          int* __restrict__ fcount, int capf, int* __restrict__ mode,
-                                                          int* __restrict__ nwhole, int* __restrict__ whole) {
-    extern __shared__ uint16_t lds_idx[];       // per wave: capf undecided elements, capf ties
-    __shared__ int lds_cnt[4][2];
+                                                          int* __restrict__ fcount, uint16_t* __restrict__ fidx, int capf,
+                                                          int* __restrict__ mode, int* __restrict__ nwhole, int* __restrict__ whole,
+                                                          int* __restrict__ nlate) {
+    extern __shared__ uint16_t lds_idx[];       // per wave: capf undecided elements, capf / 2 late ones
+    __shared__ int lds_cnt[4];
     const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave, row = blockIdx.x * 4 + wv;
-    if (lane < 2) lds_cnt[wv][lane] = 0;
+    if (lane == 0) lds_cnt[wv] = 0;
     wave_sync();
     if (row >= M) return;
     if (mode[row]) {                            // recomputed as a whole later
         if (lane == 0) {
             fcount[row] = 0;
+            nlate[row] = 0;
             whole[atomicAdd(nwhole, 1)] = row;
         }
         return;
@@ -714,7 +722,7 @@ __global__ __launch_bounds__(256) void dense_quant_kernel(const uint16_t* __rest
     const double inv = rq.inv, e = eps[row];
     const double keep = 0.5 - (e * inv * (1.0 + 1e-6) + 1e-12);            // |p - rint(p)| below this: the code is settled
     const float4* us = reinterpret_cast<const float4*>(Ut + (size_t)row * K);
-    uint16_t* myidx = lds_idx + (size_t)wv * 2 * capf;
+    uint16_t* myidx = lds_idx + (size_t)wv * (capf + capf / 2);
     for (int c = lane; c < K / 8; c += kWave) {
         const float4 v0 = us[2 * c], v1 = us[2 * c + 1];
         const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
@@ -724,7 +732,7 @@ __global__ __launch_bounds__(256) void dense_quant_kernel(const uint16_t* __rest
             const double p = (double)v[i] * inv;
             double r = (p + kMagic) - kMagic;
             if (!(fabs(p - r) < keep)) {
-                const int slot = atomicAdd(&lds_cnt[wv][0], 1);
+                const int slot = atomicAdd(&lds_cnt[wv], 1);
                 if (slot < capf) myidx[slot] = (uint16_t)(c * 8 + i);
             }
             r = ASYM ? fmin(fmax(r - rq.zsub, -(qmax + 1.0)), qmax) : fmin(fmax(r, -qmax), qmax);
@@ -734,11 +742,12 @@ __global__ __launch_bounds__(256) void dense_quant_kernel(const uint16_t* __rest
             make_uint2(b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24), b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24));
     }
     wave_sync();
-    const int n = lds_cnt[wv][0];
+    const int n = lds_cnt[wv];
     if (lane == 0) {
         scale[row] = rq.scale;
         if (ASYM) zero[row] = rq.izero;
         fcount[row] = n > capf ? 0 : n;
+        nlate[row] = 0;
         if (n > capf) {
             mode[row] = 1;
             whole[atomicAdd(nwhole, 1)] = row;
@@ -752,8 +761,10 @@ __global__ __launch_bounds__(256) void dense_quant_kernel(const uint16_t* __rest
     constexpr int LPE = 16;                     // lanes that share an element
     const int l = lane % LPE;
     const uint4* xs = reinterpret_cast<const uint4*>(X + (size_t)row * K) + l;
-    for (int i0 = 0; i0 < n; i0 += 64 / LPE) {
-        const int i = i0 + lane / LPE;
+    const bool crowded = n > capf / 2;
+    int done = 0, late = 0;                     // elements that have been summed, and how many of them that left over
+    for (; !crowded && done < n && 2 * late <= done; done += 64 / LPE) {
+        const int i = done + lane / LPE;
         const int col = (int)myidx[i < n ? i : n - 1];
         const uint4* rs = reinterpret_cast<const uint4*>(Rt + (size_t)col * K) + l;
         double u = 0.0;
@@ -781,29 +792,18 @@ __global__ __launch_bounds__(256) void dense_quant_kernel(const uint16_t* __rest
 #pragma unroll
         for (int o = LPE / 2; o > 0; o >>= 1) u += __shfl_xor(u, o, kWave);
         const double p = u * inv, r = (p + kMagic) - kMagic;
-        if (l == 0 && i < n) {
-            if (fabs(p - r) < keep2) q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
-            else myidx[capf + atomicAdd(&lds_cnt[wv][1], 1)] = (uint16_t)col;
-        }
+        const bool settled = fabs(p - r) < keep2, mine = l == 0 && i < n;
+        if (mine && settled) q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
+        const unsigned long long left = __ballot(mine && !settled);
+        if (mine && !settled) myidx[capf + late + __popcll(left & ((1ull << lane) - 1ull))] = (uint16_t)col;
+        late += __popcll(left);
     }
+    if (done > n) done = n;
+    const int m = late + n - done;
+    if (m == 0) return;
+    if (lane == 0) nlate[row] = m;
     wave_sync();
-    const int ties = lds_cnt[wv][1];
-    for (int i = lane; i < ties; i += kWave) {
-        const int col = (int)myidx[capf + i];
-        const uint4* xr = reinterpret_cast<const uint4*>(X + (size_t)row * K);
-        const uint4* rr = reinterpret_cast<const uint4*>(Rt + (size_t)col * K);
-        double u = 0.0;
-        for (int c = 0; c < K / 8; ++c) {
-            const uint4 xv = xr[c], rv = rr[c];
-            const unsigned xw[4] = {xv.x, xv.y, xv.z, xv.w}, rw[4] = {rv.x, rv.y, rv.z, rv.w};
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                u = fma((double)bf16_lo(xw[d]), (double)bf16_lo(rw[d]), u);
-                u = fma((double)bf16_hi(xw[d]), (double)bf16_hi(rw[d]), u);
-            }
-        }
-        q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
-    }
+    for (int i = lane; i < m; i += kWave) fidx[(size_t)row * capf + i] = i < late ? myidx[capf + i] : myidx[done + i - late];
 }
 
 // ---- the same with a list: codes from u~ with the exact amax (zero-point form: the exact maximum and minimum); the elements the bound leaves
@@ -1011,6 +1011,18 @@ __device__ __forceinline__ double exact_element_wave(const uint16_t* X, const ui
     return u;
 }
 
+// Exact values and codes of a wave's elements, one to a lane (have: the lane has one).
+template <bool ASYM>
+__device__ __forceinline__ void exact_codes_wave(const uint16_t* X, const uint16_t* Rt, int K, double qmax, bool have, int row, int col,
+                                                 const unsigned long long* __restrict__ amax_bits, int8_t* __restrict__ q,
+                                                 unsigned char* lds) {
+    const double u = exact_element_wave(X, Rt, K, row, col, lds);
+    if (have) {
+        const RowQuant rq = row_quant<ASYM>(amax_bits[2 * (size_t)row], amax_bits[2 * (size_t)row + 1], qmax);
+        q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
+    }
+}
+
 // ---- undecided elements: exact value, exact code.  Thread i takes list entry i (row found by bisection of offs).
 template <bool ASYM>
 __global__ __launch_bounds__(256, 3) void dense_exact_codes_kernel(const uint16_t* X, const uint16_t* Rt, int M, int K, double qmax,
@@ -1033,11 +1045,7 @@ __global__ __launch_bounds__(256, 3) void dense_exact_codes_kernel(const uint16_
             row = lo;
             col = (int)fidx[(size_t)row * capf + (i - offs[row])];
         }
-        const double u = exact_element_wave(X, Rt, K, row, col, stage + (threadIdx.x / kWave) * XE_BUF);
-        if (have) {
-            const RowQuant rq = row_quant<ASYM>(amax_bits[2 * (size_t)row], amax_bits[2 * (size_t)row + 1], qmax);
-            q[(size_t)row * K + col] = (int8_t)exact_code<ASYM>(u, rq, qmax);
-        }
+        exact_codes_wave<ASYM>(X, Rt, K, qmax, have, row, col, amax_bits, q, stage + (threadIdx.x / kWave) * XE_BUF);
     }
 }
 
@@ -1047,16 +1055,58 @@ __global__ __launch_bounds__(256, 3) void dense_exact_codes_kernel(const uint16_
 // any (the grid walks the list of marked rows, whose order does not matter) and a thread keeps 32 loads in flight.  Rotate and
 // quantize, us, one row marked / 512 neighbours / all, 8192 x 1024: 211 / 282 / 2420 (95 with none; eight neighbouring rows to a
 // workgroup and one load after the other 1410 / 7120 / 7230; a workgroup per row of X, a column a thread 513 / 550 / 2990).
-template <bool ASYM>
-__global__ __launch_bounds__(256) void dense_exact_rows_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ R,
-                                                               int K, double qmax, const int* __restrict__ nwhole,
-                                                               const int* __restrict__ whole, int8_t* __restrict__ q,
+// LATE: after dense_quant_kernel; the late elements come first (4 XE_BUF bytes of LDS).  A workgroup takes the rows of a chunk together, its
+// waves 64 of the chunk's late elements each: the chains of neighbouring rows fill a wave, and nothing is counted by atomics (a
+// list of rows with one counter took 10 ns a row).  Rotate and quantize, us, one tie in every row / as many as a row's list holds:
+// 8192 x 1152 98 / 178, 35100 x 2048 565 / 1258 (a lane per tie in dense_quant_kernel, one load after the other: 194 / 280, 1253 / 2517;
+// a sorted list of all undecided elements: 112 / 183, 560 / 1261).  Without ties it costs 1 us of registers and LDS.
+template <bool ASYM, bool LATE>
+__global__ __launch_bounds__(256, LATE ? 3 : 1) void dense_exact_rows_kernel(const uint16_t* X, const uint16_t* __restrict__ R,
+                                                               const uint16_t* Rt, int M, int K, double qmax, int* nwhole,
+                                                               const int* __restrict__ whole,
+                                                               const int* __restrict__ nlate, const uint16_t* __restrict__ fidx, int capf,
+                                                               const unsigned long long* __restrict__ amax_bits, int8_t* __restrict__ q,
                                                                float* __restrict__ scale, int32_t* __restrict__ zero) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    const int t = threadIdx.x, n = *nwhole;
-    for (int w = blockIdx.x; w < n; w += gridDim.x) {
-        const int row = whole[w];
+    const int n = *nwhole;
+    if constexpr (LATE) {
+        const int lane = threadIdx.x % kWave, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+        const int share = (M + (int)gridDim.x - 1) / (int)gridDim.x, chunk = share < kWave ? share : kWave;        // rows, at most a lane each
+        for (int r0 = blockIdx.x * chunk; r0 < M; r0 += gridDim.x * chunk) {
+            int offs = lane < chunk && r0 + lane < M ? nlate[r0 + lane] : 0;    // then: where the row's elements end
+            if (__ballot(offs != 0) == 0ull) continue;
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const int before = __shfl_up(offs, o, kWave);
+                if (lane >= o) offs += before;
+            }
+            const int total = __builtin_amdgcn_readlane(offs, kWave - 1);
+            for (int base = wv * kWave; base < total; base += 256) {             // wave-uniform
+                const int i = base + lane;
+                int r = 0;                                                       // rows that end at i or before
+#pragma unroll
+                for (int o = kWave / 2; o > 0; o >>= 1)
+                    if (__shfl(offs, r + o - 1, kWave) <= i) r += o;
+                const int begin = __shfl(offs, r > 0 ? r - 1 : 0, kWave);
+                const bool have = i < total;
+                const int row = have ? r0 + r : 0;
+                const int col = have ? (int)fidx[(size_t)row * capf + (i - (r > 0 ? begin : 0))] : 0;
+                exact_codes_wave<ASYM>(X, Rt, K, qmax, have, row, col, amax_bits, q, lds_raw + wv * XE_BUF);
+            }
+        }
+    }
+    __shared__ int taken;
+    const int t = threadIdx.x;
+    if (n == 0) return;
+    for (int w = blockIdx.x;; w += gridDim.x) {
         __syncthreads();                                     // the previous row's x and maxima have been read
+        if constexpr (LATE) {                                // few workgroups: each takes the next row when it is done with one
+            if (t == 0) taken = atomicAdd(nwhole + 1, 1);
+            __syncthreads();
+            w = taken;
+        }
+        if (w >= n) break;
+        const int row = whole[w];
         uint16_t* xr = reinterpret_cast<uint16_t*>(lds_raw);
         double* red = reinterpret_cast<double*>(lds_raw + (((size_t)K * 2 + 15) & ~(size_t)15));
         for (int k = t; k < K; k += 256) xr[k] = X[(size_t)row * K + k];
@@ -1225,18 +1275,22 @@ hipError_t launch_dense_fast(hipStream_t st, const uint16_t* X, const uint16_t* 
     else
         hipLaunchKernelGGL((dense_exact_amax_kernel<ASYM, 4>), dim3((unsigned)((candidates + 63) / 64)), dim3(256), 0, st, X, Rt, M, K,
                            ccount, cidx, amax, nwhole);
+    const size_t rows_lds = (((size_t)K * 2 + 15) & ~(size_t)15) + 8 * sizeof(double);
+    const int most = quant_in_one(M, K) ? 768 : 2048;           // 768: as many as are resident with the chains' registers
+    const dim3 rows_grid(M < most ? M : most);
     if (quant_in_one(M, K)) {
-        hipLaunchKernelGGL(dense_quant_kernel<ASYM>, dim3((M + 3) / 4), dim3(256), 4 * 2 * L.capf * sizeof(uint16_t), st, X, Rt, Ut, M, K,
-                           qmax, (double)err_factor, eps, amax, q, scale, zero, fcount, L.capf, mode, nwhole, whole);
+        hipLaunchKernelGGL(dense_quant_kernel<ASYM>, dim3((M + 3) / 4), dim3(256), 4 * (L.capf + L.capf / 2) * sizeof(uint16_t), st, X, Rt, Ut,
+                           M, K, qmax, (double)err_factor, eps, amax, q, scale, zero, fcount, fidx, L.capf, mode, nwhole, whole, foffs);
+        hipLaunchKernelGGL((dense_exact_rows_kernel<ASYM, true>), rows_grid, dim3(256), rows_lds > 4 * XE_BUF ? rows_lds : 4 * XE_BUF, st, X, R,
+                           Rt, M, K, qmax, nwhole, whole, foffs, fidx, L.capf, amax, q, scale, zero);
     } else {
         hipLaunchKernelGGL(dense_quant_flag_kernel<ASYM>, dim3((M + 3) / 4), dim3(256), 4 * sizeof(int), st, Ut, M, K, qmax, eps, amax, q,
                            scale, zero, fcount, fidx, L.capf, mode, nwhole, whole);
         hipLaunchKernelGGL(dense_scan_counts_kernel, dim3(1), dim3(1024), 0, st, fcount, M, foffs);
         hipLaunchKernelGGL(dense_exact_codes_kernel<ASYM>, dim3(2048), dim3(256), 0, st, X, Rt, M, K, qmax, foffs, fidx, L.capf, amax, q);
+        hipLaunchKernelGGL((dense_exact_rows_kernel<ASYM, false>), rows_grid, dim3(256), rows_lds, st, X, R, Rt, M, K, qmax, nwhole, whole, foffs,
+                           fidx, L.capf, amax, q, scale, zero);
     }
-    const size_t rows_lds = (((size_t)K * 2 + 15) & ~(size_t)15) + 8 * sizeof(double);
-    hipLaunchKernelGGL(dense_exact_rows_kernel<ASYM>, dim3(M < 2048 ? M : 2048), dim3(256), rows_lds, st, X, R, K, qmax, nwhole, whole,
-                       q, scale, zero);
     return hipGetLastError();
 }
 }  // namespace

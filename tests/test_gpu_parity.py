@@ -382,6 +382,46 @@ def test_dense_rotation_exact_ties(lrq, M, K, asym):
     assert np.array_equal(q, np.rint(half))              # the step is 1; zero-points: x_q - 128 with z = -128
 
 
+@pytest.mark.parametrize("M,K", [(66, 128), (300, 1152), (2100, 2304), (600, 3200)])
+@pytest.mark.parametrize("asym", [False, True])
+def test_dense_rotation_few_and_many_undecided_elements(lrq, M, K, asym):
+    """Rows with no, one, a handful and as many ties as the row's list holds, beside rows whose bound leaves up to that many ordinary
+    elements undecided (the largest column norm belongs to a column on which x cancels): elements that are settled in place, listed
+    for the chains one by one, or listed unseen, in one launch."""
+    import torch
+    print(f"case dense undecided M={M} K={K} asym={asym}", flush=True)
+    g = synth.rng_for(952, M, K)
+    capf = ((32 + K // 64) + 7) & ~7
+    half = K // 2
+    R = np.zeros((K, K))
+    R[half + np.arange(half), half + g.permutation(half)] = 1.0              # lower half: a permutation
+    R[:half, :half] = np.linalg.qr(g.standard_normal((half, half)))[0]
+    R[:2] = 0.0
+    R[0, 0], R[1, 0] = 4.0, -4.0                                             # x_0 = x_1: nothing but the bound grows
+    x = np.zeros((M, K), np.float32)
+    ties = np.array([0, 1, 3, 5, capf // 2 - 1, capf // 2 + 3, capf - 4])[np.arange(M) % 7]
+    for i in range(M):
+        if i % 2:
+            x[i, :half] = g.standard_normal(half)
+            x[i, 0] = x[i, 1] = (0, 1, 3, 8)[i // 2 % 4]
+        else:                                                                # step 1 in either form of the quantizer
+            x[i, half:] = np.rint(g.standard_normal(half) * 20.0)
+            x[i, half], x[i, half + 1] = 127.0, (-128.0 if asym else -100.0)
+            n = min(int(ties[i]), half - 2)
+            x[i, half + 2:half + 2 + n] = g.integers(-60, 60, size=n) + 0.5
+    X, Rd = (bf16_to_dev(synth.f32_to_bf16_bits(a.astype(np.float32))) for a in (x, R))
+    rot = lrq.Rotation("dense", 0, Rd)
+    ws = torch.full((lrq.ars_workspace_bytes(M, K, rot, 8),), 90, dtype=torch.uint8, device="cuda")
+    got = lrq.ars_rotate_quant(X, rot, 8, asym=asym, workspace=ws)
+    cnt, whole = (a.cpu().numpy() for a in lrq.ars_dense_diagnostics(ws, M, K)[2:])
+    kept = cnt[whole == 0]
+    print(f"  undecided a row: {np.bincount(kept).nonzero()[0].tolist()}, whole rows {int(whole.sum())}", flush=True)
+    assert (kept == 0).any() and ((kept > 0) & (kept <= capf // 2)).any() and (kept > capf // 2).any()
+    ref = lrq.ars_rotate_quant(X, lrq.Rotation("dense_f64", 0, Rd), 8, asym=asym)
+    for a, b in zip(got, ref):
+        assert torch.equal(a, b)
+
+
 def _equal_maxima_inputs(M, K, marked):
     """Sylvester Hadamard matrix as the rotation; the marked rows hold one spike, so that every |u| of theirs is a maximum."""
     R = synth.f32_to_bf16_bits((oracle.hadamard_matrix(K) / np.sqrt(K)).astype(np.float32))
