@@ -88,7 +88,7 @@ __device__ __forceinline__ double level_index(double ell, double s, double z, do
 
 // Elements k = base + e NT + t of the row, e < NE: REGS: the row fits NT * NE elements and el / wv hold it all along; otherwise
 // they are read from ell (LDS) and w for every pass.
-template <int NE, bool REGS, int NC>
+template <int NE, bool REGS, int NC, bool MASKS>
 __device__ void search_clip(const float* __restrict__ w, const double* __restrict__ ell, double (&el)[NE], float (&wv)[NE], int K,
                             const bool (&has)[2], const double (&wmax)[2], const double (&wmin)[2],
                             const float* __restrict__ agrid, int na, const float* __restrict__ bgrid, int nb,
@@ -106,9 +106,8 @@ __device__ void search_clip(const float* __restrict__ w, const double* __restric
     // MASKS: 1.0 where the weight has the sign, 0.0 elsewhere.  A fused multiply-add by it adds the square or + 0.0 exactly as a
     // select and an addition do, in one instruction instead of three (the loop is bound by issue).  It needs finite squares:
     // threads with an infinity or a NaN always take the general form, and so do candidates with huge levels (mode 2).
-    // Not at 24 weights a thread, where the masks spill (1500 x 6144: 245 us with the selects, 277 us with masks); 4000 x 2304:
-    // 248 -> 233 us, 9216 x 3072: 670 -> 643 us, 1000 x 4608: 134 -> 126 us.
-    constexpr bool MASKS = REGS && NE <= 18;
+    // Which grids take them: masks_from.
+    static_assert(REGS || !MASKS, "the masks belong to weights in registers");
     double is_pos[MASKS ? NE : 1], is_neg[MASKS ? NE : 1];
     bool not_finite = false;
     if constexpr (MASKS) {
@@ -265,7 +264,7 @@ __device__ __forceinline__ uint8_t f64_to_e4m3_rne(double x) {
     return (uint8_t)(sgn | ((unsigned)(e + 7) << 3) | ((unsigned)n - 8u));
 }
 
-template <int NE, bool REGS, int NC>
+template <int NE, bool REGS, int NC, bool MASKS>
 __global__ __launch_bounds__(NT, !REGS || NE > 12 ? 2 : (NE > 6 ? 3 : 4)) void tlq_quantize_pack_kernel(
     const float* __restrict__ W, int N, int K, int bits, int I, const float* __restrict__ agrid, int na,
     const float* __restrict__ bgrid, int nb, uint8_t* __restrict__ codes_out, double* __restrict__ s_pos,
@@ -323,7 +322,7 @@ __global__ __launch_bounds__(NT, !REGS || NE > 12 ? 2 : (NE > 6 ? 3 : 4)) void t
 
     const bool has[2] = {has_p, has_n};
     const double wmax[2] = {pmax, nmax}, wmin[2] = {pmin, nmin};
-    search_clip<NE, REGS, NC>(w, ell, el, wv, K, has, wmax, wmin, agrid, na, bgrid, nb, ggrid, ngamma, half, S);
+    search_clip<NE, REGS, NC, MASKS>(w, ell, el, wv, K, has, wmax, wmin, agrid, na, bgrid, nb, ggrid, ngamma, half, S);
     const double sp = S.best_s[0], zp = S.best_z[0], ep = S.best_err[0], sn = S.best_s[1], zn = S.best_z[1], en = S.best_err[1];
     const float al = S.best_c[0], be = S.best_c[1], gp = S.best_g[0], gn = S.best_g[1];
 
@@ -450,6 +449,15 @@ __global__ __launch_bounds__(NT, !REGS || NE > 12 ? 2 : (NE > 6 ? 3 : 4)) void t
 
 }  // namespace
 
+// From how many candidates on a search with ne weights a thread adds through masks: they take 4 ne registers, to be set up and, at the
+// occupancy that the launch bounds ask for, spilled in part (3, 5, 6, 9, 12 weights: 2, 4, 11, 2, 25 registers), and save
+// instructions of every candidate.  us with selects / with masks for 1, 4, 8, 21 candidates: 4608 x 768 50.8 / 51.4, 60.8 / 60.7,
+// 74.8 / 73.8, 140.2 / 135.2; 4608 x 1152 57.9 / 59.0, 72.1 / 72.0, 91.9 / 89.7, 176.9 / 169.3; 4096 x 1536 57.8 / 59.8,
+// 71.9 / 72.8, 91.8 / 90.0, 175.3 / 168.6; 4000 x 2304 82.4 / 83.2, 104.3 / 102.7, 133.1 / 128.1, 248.5 / 232.8; 9216 x 3072
+// 201.9 / 221.9, 265.5 / 282.5, 345.4 / 355.7, 671.9 / 643.6 (16 candidates: 561.1 / 557.5); 1152 x 4608 54.0 / 54.8, 68.7 / 68.0,
+// 88.7 / 85.5, 166.6 / 155.0.  24 weights a thread lose at 21 candidates too (1500 x 6144: 245 / 277).
+static int masks_from(int ne) { return ne <= 5 ? 4 : (ne <= 6 ? 6 : (ne <= 9 ? 3 : (ne <= 12 ? 16 : 3))); }
+
 hipError_t launch_tlq_quantize_pack(hipStream_t st, const float* W, int N, int K, int bits, int I,
                                     const float* alpha_grid, int n_alpha, const float* beta_grid, int n_beta,
                                     const lrq_tlq_weight& out, const float* gamma_grid, int n_gamma, float* gamma_pos,
@@ -457,29 +465,26 @@ hipError_t launch_tlq_quantize_pack(hipStream_t st, const float* W, int N, int K
     // Weights per thread: the smallest count that holds the row (K = 1152 fills 4.5 of 5); above 6144 the row goes through the
     // registers in passes of 16.  There the row's logarithms leave room for few partial sums beside a second workgroup on the CU: a
     // grid of one or two candidates takes two at a time (6528 x 8328, one candidate: 860 us, eight at a time 1076).
-#define LRQ_GO(NE, REGS, NC)                                                                                                  \
-    {                                                                                                                         \
-        const size_t lds = sizeof(SearchLds<NC>) + (size_t)K * (REGS ? 1 : sizeof(double));                                   \
-        const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(tlq_quantize_pack_kernel<NE, REGS, NC>), 158 * 1024); \
-        if (e != hipSuccess) return e;                                                                                        \
-        hipLaunchKernelGGL((tlq_quantize_pack_kernel<NE, REGS, NC>), dim3(N), dim3(NT), lds, st, W, N, K, bits, I, alpha_grid, \
-                           n_alpha, beta_grid, n_beta, out.codes, out.s_pos, out.s_neg, out.z_pos, out.z_neg, out.alpha,      \
-                           out.beta, out.lut, out.wscale, out.gemm_codes, out.colsum, gamma_grid, n_gamma, gamma_pos,         \
-                           gamma_neg, out.levels, out.err_pos, out.err_neg, out.lut_fp8, out.wscale_fp8);                     \
-    }
+    auto go = [&](auto kernel, size_t lds) {
+        const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(kernel), 158 * 1024);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(N), dim3(NT), lds, st, W, N, K, bits, I, alpha_grid, n_alpha, beta_grid, n_beta, out.codes,
+                           out.s_pos, out.s_neg, out.z_pos, out.z_neg, out.alpha, out.beta, out.lut, out.wscale, out.gemm_codes,
+                           out.colsum, gamma_grid, n_gamma, gamma_pos, gamma_neg, out.levels, out.err_pos, out.err_neg,
+                           out.lut_fp8, out.wscale_fp8);
+        return hipGetLastError();
+    };
     const int ne = (K + NT - 1) / NT, candidates = (n_alpha > n_beta ? n_alpha : n_beta) * (n_gamma > 0 ? n_gamma : 1);
-    if (ne <= 3) LRQ_GO(3, true, 8)
-    else if (ne <= 5) LRQ_GO(5, true, 8)
-    else if (ne <= 6) LRQ_GO(6, true, 8)
-    else if (ne <= 9) LRQ_GO(9, true, 8)
-    else if (ne <= 12) LRQ_GO(12, true, 8)
-    else if (ne <= 18) LRQ_GO(18, true, 8)
-    else if (ne <= 24) LRQ_GO(24, true, 8)
-    else if (candidates <= 2) LRQ_GO(16, false, 2)
-    else if (K <= 12288) LRQ_GO(16, false, 8)
-    else LRQ_GO(16, false, 4)
-#undef LRQ_GO
-    return hipGetLastError();
+    const size_t lds = sizeof(SearchLds<8>) + (size_t)K;
+#define LRQ_REGS(NE) \
+    if (ne <= NE) return candidates >= masks_from(NE) ? go(tlq_quantize_pack_kernel<NE, true, 8, true>, lds) : go(tlq_quantize_pack_kernel<NE, true, 8, false>, lds);
+    LRQ_REGS(3) LRQ_REGS(5) LRQ_REGS(6) LRQ_REGS(9) LRQ_REGS(12) LRQ_REGS(18)
+#undef LRQ_REGS
+    if (ne <= 24) return go(tlq_quantize_pack_kernel<24, true, 8, false>, lds);
+    const size_t row = (size_t)K * sizeof(double);
+    if (candidates <= 2) return go(tlq_quantize_pack_kernel<16, false, 2, false>, sizeof(SearchLds<2>) + row);
+    if (K <= 12288) return go(tlq_quantize_pack_kernel<16, false, 8, false>, sizeof(SearchLds<8>) + row);
+    return go(tlq_quantize_pack_kernel<16, false, 4, false>, sizeof(SearchLds<4>) + row);
 }
 
 }  // namespace lrq

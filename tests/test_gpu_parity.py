@@ -822,6 +822,21 @@ def test_tlq_search_with_skipped_sides_and_huge_levels(lrq, K, bits):
         _check_weight(lrq, W, bits, 7, beta, alpha)
 
 
+@pytest.mark.parametrize("K,bits,n", [(640, 4, 3), (768, 3, 4), (1152, 4, 3), (1152, 4, 4), (1536, 4, 5), (1536, 3, 6), (2304, 4, 2), (2304, 4, 3),
+                                      (3072, 4, 15), (3072, 4, 16), (4608, 3, 2), (4608, 4, 3), (6144, 4, 16)])
+def test_tlq_search_on_either_side_of_the_masks(lrq, K, bits, n):
+    """Grids just short of and just long enough for sums through sign masks, per row length; a row of one sign, one with equal
+    magnitudes, one with an infinity beside ordinary ones."""
+    print(f"case tlq masks K={K} b={bits} n={n}", flush=True)
+    W = synth.make_weights(6, K, (953, K, n))
+    W[0] = np.abs(W[0])
+    W[1] = np.where(W[1] > 0, np.float32(0.25), W[1])
+    W[2, K // 2] = np.inf
+    with np.errstate(all="ignore"):
+        _check_weight(lrq, W, bits, 7, GRID[:n], GRID[:max(n - 1, 1)])
+        _check_weight(lrq, W, bits, 7, GRID[:max(n - 1, 1)], GRID[:n])
+
+
 @pytest.mark.parametrize("N,K,bits", [(70, 192, 4), (48, 128, 3), (33, 64, 4)])
 def test_gemm_code_tiling_matches_its_description(lrq, N, K, bits):
     """The GEMM's private copy of the weight codes: units of (32 channels x 64 k) stored [channel tile][K block], 64 slots
