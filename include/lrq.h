@@ -40,7 +40,7 @@ typedef enum {
     LRQ_OK = 0,
     LRQ_EINVAL = -1,       /* null pointer, non-positive size, misaligned pointer, inconsistent struct   */
     LRQ_EUNSUPPORTED = -2, /* bit-width, block size or shape outside what the kernels implement          */
-    LRQ_EWORKSPACE = -3,   /* workspace pointer null or smaller than the *_workspace_bytes() answer      */
+    LRQ_EWORKSPACE = -3,   /* workspace pointer null or smaller than the call needs                     */
     LRQ_EHIP = -4,         /* the HIP runtime reported an error while launching                           */
     LRQ_ESCRATCH = -5      /* lrq_qlinear_static: the layer does not fit the library's built-in scratch buffer */
 } lrq_status;
@@ -232,9 +232,11 @@ int lrq_ars_dense_diagnostics(int M, int K, size_t offsets[4]);
 size_t lrq_ars_dense_prepared_bytes(int K);
 int lrq_ars_dense_prepare(void* stream, const void* R, int K, void* prepared, size_t prepared_bytes);
 
-/* Workspace of lrq_qlinear (bytes): activation codes, scales and rotation scratch, and for large products with 4-bit weights room for
- * the decoded weights (about N * K bytes) unless the rotation scratch holds them.  A workspace without that room
- * (lrq_workspace_bytes for N = 0) is accepted: the call then decodes inside the GEMM, slower, with the same outputs. */
+/* Workspace of lrq_qlinear (bytes): activation codes, scales and rotation scratch, and for large products room for the decoded weights
+ * (about N * K bytes) unless the rotation scratch holds them.  An upper bound over bit-widths and output types: only calls with
+ * 4-bit weights and bf16 outputs use that room.  A workspace without it (lrq_workspace_bytes for N = 0) is accepted by every call, and
+ * is all that 3-bit weights, fp32 outputs, lrq_qlinear_levels and lrq_qlinear_fp8 use; the others then decode inside the GEMM, slower,
+ * with the same outputs. */
 size_t lrq_workspace_bytes(int M, int N, int K, const lrq_rotation* rot, int act_bits);
 
 /*

@@ -401,7 +401,7 @@ def qlinear_fp8(X, rot: Rotation, w: TLQWeight, bias=None, out_dtype=None, out=N
         out = torch.empty((M, w.N), dtype=out_dtype, device=X.device)
     r, cs = rot.c_struct(), w.c_struct()
     if workspace is None:
-        workspace = torch.empty(lib().lrq_workspace_bytes(M, w.N, K, ctypes.byref(r), 4), dtype=torch.uint8, device=X.device)
+        workspace = torch.empty(lib().lrq_workspace_bytes(M, 0, K, ctypes.byref(r), 4), dtype=torch.uint8, device=X.device)
     st = lib().lrq_qlinear_fp8(_stream(), _ptr(X), M, K, ctypes.byref(r), ctypes.byref(cs), _ptr(bias), _out_code(out_dtype),
                                _ptr(out), _ptr(workspace), workspace.numel())
     _check(st, "lrq_qlinear_fp8")
@@ -443,6 +443,12 @@ def _out_code(dtype) -> int:
     raise KeyError(dtype)
 
 
+def _workspace_n(w: TLQWeight, out_dtype, levels: bool = False) -> int:
+    """The N to ask lrq_workspace_bytes for: its room for decoded weights serves 4-bit weights with bf16 outputs on the int8 path only, every
+    other call is complete with the size for N = 0."""
+    return w.N if w.bits == 4 and _out_code(out_dtype) == LRQ_OUT_BF16 and not levels else 0
+
+
 def qlinear(X, rot: Rotation, act_bits: int, w: TLQWeight, bias=None, out_dtype=None, out=None, workspace=None,
             asym: bool = False, levels: bool = False):
     """lrq_qlinear (asym=True: lrq_qlinear_asym; levels=True: lrq_qlinear_levels): fused rotate, quantize, decode,
@@ -457,7 +463,7 @@ def qlinear(X, rot: Rotation, act_bits: int, w: TLQWeight, bias=None, out_dtype=
     L, r, cs = lib(), ctypes.byref(rot.c_struct()), ctypes.byref(w.c_struct())
     if workspace is None:
         size_fn = L.lrq_workspace_bytes_asym if asym else L.lrq_workspace_bytes
-        workspace = torch.empty(size_fn(M, w.N, K, r, act_bits), dtype=torch.uint8, device=X.device)
+        workspace = torch.empty(size_fn(M, _workspace_n(w, out_dtype, levels), K, r, act_bits), dtype=torch.uint8, device=X.device)
     call = L.lrq_qlinear_asym if asym else (L.lrq_qlinear_levels if levels else L.lrq_qlinear)
     st = call(_stream(), X.data_ptr(), M, K, r, act_bits, cs, None if bias is None else bias.data_ptr(), _out_code(out_dtype),
               out.data_ptr(), workspace.data_ptr(), workspace.numel())

@@ -298,6 +298,43 @@ def test_qgemm_diagnostics(L):
     assert lrq.qgemm_tile(35100, 12001, 3072, 4) == (128, 256) and lrq.qgemm_tile(20000, 9001, 3072, 4) == (128, 256)
 
 
+def test_the_binding_asks_for_decoded_weights_room_only_where_it_is_used(L, monkeypatch):
+    """12288 x 3072: 37.7 MB that 3-bit weights, fp32 outputs, levels and FP8 calls never touch."""
+    import types
+    import torch
+    rot = lrq.Rotation("hadamard", 1024)
+    M, N, K = 4608, 12288, 3072
+    sizes = []
+
+    class Sized(Exception):
+        pass
+
+    def empty(shape, **_):
+        if isinstance(shape, int):
+            sizes.append(shape)
+            raise Sized                                      # nothing is launched
+        return object()
+    monkeypatch.setattr(torch, "empty", empty)
+    X = types.SimpleNamespace(is_cuda=True, dtype=torch.bfloat16, is_contiguous=lambda: True, shape=(M, K), device="cuda")
+
+    def asked(call, bits, **kw):
+        w = types.SimpleNamespace(N=N, K=K, bits=bits, c_struct=lambda: lrq._TlqWeight())
+        with pytest.raises(Sized):
+            call(X, w, **kw)
+        return sizes[-1]
+    linear = lambda X, w, **kw: lrq.qlinear(X, rot, 8, w, **kw)
+    for asym in (False, True):
+        bare = lrq.workspace_bytes(M, 0, K, rot, 8, asym=asym)
+        full = lrq.workspace_bytes(M, N, K, rot, 8, asym=asym)
+        assert full >= bare + N * K
+        assert asked(linear, 4, asym=asym) == full
+        assert asked(linear, 3, asym=asym) == bare
+        assert asked(linear, 4, asym=asym, out_dtype=torch.float32) == bare
+    bare = lrq.workspace_bytes(M, 0, K, rot, 8)
+    assert asked(linear, 4, levels=True) == bare
+    assert asked(lambda X, w: lrq.qlinear_fp8(X, rot, w), 4) == bare
+
+
 def test_inline_assembly_names_m0_where_it_writes_it():
     """m0 is an ordinary register to the compiler: an asm statement that sets it has to say so, or a value that the compiler keeps
     there is lost."""
