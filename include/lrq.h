@@ -295,6 +295,12 @@ int lrq_qgemm(void* stream, const int8_t* q, const float* scale, int M, int K,
  * depend on the choice.  Errors: LRQ_EINVAL (null pointer, non-positive size, unknown form), LRQ_EUNSUPPORTED.
  */
 int lrq_qgemm_diagnostics(int M, int N, int K, int bits, int form, int out_dtype, int tile[2]);
+/*
+ * The same for lrq_qlinear (form 0), lrq_qlinear_asym (1) and lrq_qlinear_packed4 (2) under a rotation, given a workspace of
+ * lrq_workspace_bytes: 192, 224 or 256 rows and 256 columns where the weights are decoded once, 0 and 0 where the whole layer is one
+ * launch, otherwise lrq_qgemm_diagnostics' answer.
+ */
+int lrq_qlinear_diagnostics(int M, int N, int K, const lrq_rotation* rot, int bits, int form, int out_dtype, int tile[2]);
 
 /*
  * The same layer on the levels themselves (paper: "Hardware Implementation", exponent split f / r and the

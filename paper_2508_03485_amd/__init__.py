@@ -25,7 +25,7 @@ EXPORTS = ("lrq_status_string", "lrq_version", "lrq_tlq_codes_bytes", "lrq_tlq_g
            "lrq_qlinear_asym", "lrq_ars_build_workspace_bytes", "lrq_ars_build_rotation",
            "lrq_fluctuation_workspace_bytes", "lrq_fluctuation_metric", "lrq_ars_select",
            "lrq_smooth_workspace_bytes", "lrq_smooth_factor", "lrq_tlq_quantize_pack_clip", "lrq_qgemm_levels",
-           "lrq_qlinear_levels", "lrq_ars_dense_diagnostics", "lrq_qgemm_diagnostics", "lrq_ars_dense_prepared_bytes", "lrq_ars_dense_prepare", "lrq_ars_workspace_bytes_packed4",
+           "lrq_qlinear_levels", "lrq_ars_dense_diagnostics", "lrq_qgemm_diagnostics", "lrq_qlinear_diagnostics", "lrq_ars_dense_prepared_bytes", "lrq_ars_dense_prepare", "lrq_ars_workspace_bytes_packed4",
            "lrq_ars_rotate_quant_packed4", "lrq_qgemm_packed4", "lrq_workspace_bytes_packed4", "lrq_qlinear_packed4",
            "lrq_ars_rotate_quant_fp8", "lrq_qgemm_fp8", "lrq_qlinear_fp8", "lrq_init", "lrq_static_scratch_bytes", "lrq_qlinear_static")
 
@@ -81,6 +81,8 @@ def lib() -> ctypes.CDLL:
     L.lrq_ars_rotate_quant.argtypes = [vp, vp, ci, ci, ctypes.POINTER(_Rotation), ci, vp, vp, vp, sz]
     L.lrq_qgemm_diagnostics.restype = ci
     L.lrq_qgemm_diagnostics.argtypes = [ci, ci, ci, ci, ci, ci, ctypes.POINTER(ci * 2)]
+    L.lrq_qlinear_diagnostics.restype = ci
+    L.lrq_qlinear_diagnostics.argtypes = [ci, ci, ci, ctypes.POINTER(_Rotation), ci, ci, ci, ctypes.POINTER(ci * 2)]
     L.lrq_ars_dense_diagnostics.restype = ci
     L.lrq_ars_dense_diagnostics.argtypes = [ci, ci, ctypes.POINTER(sz * 4)]
     L.lrq_ars_dense_prepared_bytes.restype = sz
@@ -493,6 +495,15 @@ def qgemm_tile(M: int, N: int, K: int, bits: int, form: str = "symmetric", out_d
     tile = (ctypes.c_int * 2)()
     _check(lib().lrq_qgemm_diagnostics(M, N, K, bits, ("symmetric", "zero_point", "packed").index(form),
                                        _out_code(out_dtype or torch.bfloat16), ctypes.byref(tile)), "lrq_qgemm_diagnostics")
+    return tuple(tile)
+
+
+def qlinear_tile(M: int, N: int, K: int, rot: Rotation, bits: int, form: str = "symmetric", out_dtype=None):
+    """lrq_qlinear_diagnostics: qgemm_tile of the kernel that a whole layer takes, given all of its workspace; (0, 0): one launch."""
+    import torch
+    tile = (ctypes.c_int * 2)()
+    _check(lib().lrq_qlinear_diagnostics(M, N, K, ctypes.byref(rot.c_struct()), bits, ("symmetric", "zero_point", "packed").index(form),
+                                         _out_code(out_dtype or torch.bfloat16), ctypes.byref(tile)), "lrq_qlinear_diagnostics")
     return tuple(tile)
 
 

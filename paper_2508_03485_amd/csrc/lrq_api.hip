@@ -317,10 +317,13 @@ static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 
 // Whether the int8 layer runs as one kernel: a few tokens, and a rotation that every workgroup can repeat.  An output that overlaps what
 // the rotation reads (a layer in place) needs the two launches, where the rotation has ended before the output is written.
+static bool few_tokens(int M, int K, const lrq_rotation* rot, int N) {
+    return (rot->kind == LRQ_ROT_NONE && lrq::qlinear_few_applies(M, N, K, 1)) ||
+           (rot->kind == LRQ_ROT_HADAMARD && lrq::qlinear_few_applies(M, N, K, rot->had_block));
+}
 static bool one_launch(const void* X, int M, int K, const lrq_rotation* rot, int N, int out_dtype, const void* Y) {
     const size_t out = (size_t)M * N * (out_dtype == LRQ_OUT_FP32 ? 4 : 2);
-    return ((rot->kind == LRQ_ROT_NONE && lrq::qlinear_few_applies(M, N, K, 1)) ||
-            (rot->kind == LRQ_ROT_HADAMARD && lrq::qlinear_few_applies(M, N, K, rot->had_block))) &&
+    return few_tokens(M, K, rot, N) &&
            !overlap(Y, out, X, (size_t)M * K * 2) && !(rot->prescale && overlap(Y, out, rot->prescale, (size_t)K * 4));
 }
 static int run_one_launch(hipStream_t st, const void* X, int M, int K, const lrq_rotation* rot, int act_bits, bool asym,
@@ -373,6 +376,22 @@ int lrq_qgemm_diagnostics(int M, int N, int K, int bits, int form, int out_dtype
     const lrq::GemmShape s = lrq::qgemm_shape(M, N, K, bits, form == 1, form == 2, out_dtype == LRQ_OUT_FP32);
     tile[0] = s.rows;
     tile[1] = s.cols;
+    return LRQ_OK;
+}
+
+int lrq_qlinear_diagnostics(int M, int N, int K, const lrq_rotation* rot, int bits, int form, int out_dtype, int tile[2]) {
+    if (!rot) return LRQ_EINVAL;
+    const int st = lrq_qgemm_diagnostics(M, N, K, bits, form, out_dtype, tile);
+    if (st != LRQ_OK) return st;
+    if (few_tokens(M, K, rot, N)) {
+        tile[0] = tile[1] = 0;
+        return LRQ_OK;
+    }
+    const int rows = form == 2 ? 0 : lrq::qgemm_wide_rows(M, N, K, bits, form == 1, out_dtype == LRQ_OUT_FP32, decodes_along(K, rot));
+    if (rows > 0) {
+        tile[0] = rows;
+        tile[1] = 256;
+    }
     return LRQ_OK;
 }
 

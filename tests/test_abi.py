@@ -298,6 +298,32 @@ def test_qgemm_diagnostics(L):
     assert lrq.qgemm_tile(35100, 12001, 3072, 4) == (128, 256) and lrq.qgemm_tile(20000, 9001, 3072, 4) == (128, 256)
 
 
+def test_qlinear_diagnostics(L):
+    """The whole layer's query: what the GEMM's rejects is rejected, decoded weights only where the layer has them, every height reached."""
+    t = (ctypes.c_int * 2)()
+    had = lrq.Rotation("hadamard", 128)
+    r = ctypes.byref(had.c_struct())
+    assert L.lrq_qlinear_diagnostics(4, 64, 128, None, 4, 0, lrq.LRQ_OUT_BF16, ctypes.byref(t)) == lrq.LRQ_EINVAL
+    assert L.lrq_qlinear_diagnostics(4, 64, 128, r, 4, 3, lrq.LRQ_OUT_BF16, ctypes.byref(t)) == lrq.LRQ_EINVAL
+    assert L.lrq_qlinear_diagnostics(4, 64, 128, r, 5, 0, lrq.LRQ_OUT_BF16, ctypes.byref(t)) == lrq.LRQ_EUNSUPPORTED
+    assert L.lrq_qlinear_diagnostics(4, 64, 128, r, 4, 0, lrq.LRQ_OUT_BF16, None) == lrq.LRQ_EINVAL
+    assert lrq.qlinear_tile(2, 6912, 1152, had, 3) == (0, 0) and lrq.qlinear_tile(2, 6912, 1152, had, 3, "packed") == (0, 0)
+    import torch
+    seen = set()
+    for M in (17, 256, 2333, 4500, 8192, 14000, 35100):
+        for N in (96, 1091, 2056, 4608, 12288):
+            for K in (1152, 3072, 4608):
+                for form in ("symmetric", "zero_point", "packed"):
+                    tile, bare = lrq.qlinear_tile(M, N, K, had, 4, form), lrq.qgemm_tile(M, N, K, 4, form)
+                    if tile != bare:
+                        seen.add(tile)
+                        assert form != "packed" and N % 8 == 0
+                        assert lrq.workspace_bytes(M, N, K, had, 8) >= lrq.workspace_bytes(M, 0, K, had, 8) + N * K
+                    assert lrq.qlinear_tile(M, N, K, had, 3, form) == lrq.qgemm_tile(M, N, K, 3, form)
+                    assert lrq.qlinear_tile(M, N, K, had, 4, form, torch.float32) == lrq.qgemm_tile(M, N, K, 4, form, torch.float32)
+    assert seen == {(192, 256), (224, 256), (256, 256)}
+
+
 def test_the_binding_asks_for_decoded_weights_room_only_where_it_is_used(L, monkeypatch):
     """12288 x 3072: 37.7 MB that 3-bit weights, fp32 outputs, levels and FP8 calls never touch."""
     import types

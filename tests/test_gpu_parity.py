@@ -1091,6 +1091,8 @@ def test_qlinear_with_weights_decoded_once(lrq, M, N, K, w_bits, asym):
     X = (torch.randn(M, K, generator=gen, device="cuda") + 0.5).to(torch.bfloat16)
     bias = torch.randn(N, generator=gen, device="cuda")
     rot = lrq.Rotation("none")
+    rows = {17120: 224, 17797: 192, 9734: 192, 16484: 224, 14393: 256, 19174: 256, 5000: 192}[M]
+    assert lrq.qlinear_tile(M, N, K, rot, w_bits, "zero_point" if asym else "symmetric") == (rows, 256)
     full = lrq.workspace_bytes(M, N, K, rot, 8, asym=asym)
     base = sum((v + 255) // 256 * 256 for v in (M * K, 4 * M, 4 * M if asym else 0))
     assert full >= base + N * K
@@ -1108,6 +1110,56 @@ def test_qlinear_with_weights_decoded_once(lrq, M, N, K, w_bits, asym):
         total += zero[0].double()[:, None] * to_dev(wv.sum(axis=1))[None, :]
     ref = total.to(torch.float32) * scale[:, None] * w.wscale[None, :] + bias[None, :]
     assert torch.equal(y, ref.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("kind,h,M,N,K,form,rows", [
+    ("hadamard", 128, 6000, 1288, 1152, "symmetric", 192),       # decoded beside blocks inside a quad
+    ("hadamard", 64, 9000, 1032, 1152, "zero_point", 192),
+    ("hadamard", 32, 6000, 2056, 2240, "symmetric", 224),        # K % 128: decoded by a launch of its own
+    ("hadamard", 256, 7001, 2056, 2304, "symmetric", 256),       # beside the two-pass kernel, other wave counts
+    ("hadamard", 512, 4500, 3080, 1536, "prescale", 256),
+    ("hadamard", 512, 6000, 2056, 1536, "zero_point", 224),
+    ("hadamard", 1024, 4096, 3080, 3072, "zero_point", 224),
+    ("hadamard", 2048, 7001, 1544, 4096, "prescale", 224),
+    ("hadamard", 4096, 6000, 1288, 4096, "symmetric", 192),      # beside persistent workgroups
+    ("hadamard", 4096, 4096, 3080, 12288, "zero_point", 224),
+    ("hadamard", 4096, 4096, 2056, 16384, "prescale", 192),      # the same, exchange in two rounds
+    ("hadamard", 8192, 4096, 3080, 8192, "zero_point", 224),     # the generic kernel: a launch of its own
+    ("none", 0, 9000, 3080, 1152, "prescale", 256),
+    ("dense", 0, 8192, 3080, 1024, "symmetric", 224),            # decoded into the rotation's scratch
+    ("prepared", 0, 5000, 2056, 2304, "zero_point", 192),
+    ("dense", 0, 6000, 2056, 2048, "prescale", 224),             # all in fp64
+    ("dense", 0, 900, 12296, 3072, "symmetric", 192),            # more weights than scratch: behind it
+    ("dense_f64", 0, 6000, 2056, 2048, "symmetric", 224),        # u stays in the scratch
+    ("blockperm", 128, 6000, 2056, 2048, "symmetric", 224),      # the structured rotation's scratch
+    ("blockperm", 256, 8192, 3080, 1024, "zero_point", 224),
+])
+def test_qlinear_with_weights_decoded_under_every_rotation(lrq, kind, h, M, N, K, form, rows):
+    """Weights decoded beside each rotation kernel, in a launch of their own, behind the rotation's scratch and over it: against the two
+    stages, bit for bit, from a workspace full of a pattern (a block that is not decoded shows)."""
+    import torch
+    print(f"case wide {kind} h={h} M={M} N={N} K={K} {form}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(K + M)
+    gd = to_dev(np.array([1.0, 1.5], np.float32))
+    w = lrq.tlq_quantize_pack(torch.randn(N, K, generator=g, device="cuda") * 0.05, 4, 7, gd, gd)
+    X = (torch.randn(M, K, generator=g, device="cuda") + 0.3).to(torch.bfloat16)
+    bias = torch.randn(N, generator=g, device="cuda")
+    if kind == "blockperm":
+        rot = _blockperm_inputs(lrq, K, h, 5)[1]
+    elif kind in ("none", "hadamard"):
+        rot = lrq.Rotation(kind, h)
+    else:
+        R = (torch.randn(K, K, generator=g, device="cuda") / K ** 0.5).to(torch.bfloat16)
+        rot = lrq.Rotation("dense" if kind == "prepared" else kind, 0, R)
+        rot.prepared = lrq.ars_dense_prepare(R) if kind == "prepared" else None
+    if form == "prescale":
+        rot.prescale = torch.exp2(torch.rand(K, generator=g, device="cuda") * 4 - 2)
+    asym = form == "zero_point"
+    assert lrq.qlinear_tile(M, N, K, rot, 4, "zero_point" if asym else "symmetric") == (rows, 256)
+    ws = torch.full((lrq.workspace_bytes(M, N, K, rot, 8, asym=asym),), 90, dtype=torch.uint8, device="cuda")
+    y = lrq.qlinear(X, rot, 8, w, bias=bias, workspace=ws, asym=asym)
+    q, scale, *zero = lrq.ars_rotate_quant(X, rot, 8, asym=asym)
+    assert torch.equal(y, lrq.qgemm(q, scale, w, bias=bias, zero=zero[0] if asym else None))
 
 
 @pytest.mark.parametrize("M,N,K,w_bits,a_bits,I", [
