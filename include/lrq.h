@@ -210,12 +210,12 @@ int lrq_ars_rotate_quant(void* stream, const void* X, int M, int K, const lrq_ro
 /*
  * Diagnostics of the LRQ_ROT_DENSE evaluation (host only, launches nothing): byte offsets, inside the workspace that
  * lrq_ars_rotate_quant was given, of what its matrix-core evaluation leaves behind -
- *   offsets[0]  float  [M, K]  the approximation u~ of u = x . R (bf16 matrix cores, fp64 accumulation of 64-k runs)
+ *   offsets[0]  float  [M, K]  the approximation u~ of u = x . R (bf16 matrix cores in runs of 32 k, fp32 sums of eight runs, fp64 totals)
  *   offsets[1]  double [M]     the bound eps_t on |u~ - u| that holds for every element of token t
  *   offsets[2]  int32  [M]     how many elements of token t the bound left undecided and were recomputed in fp64
  *   offsets[3]  int32  [M]     1 for a token that was recomputed as a whole (0 otherwise)
  * Returns LRQ_OK, or LRQ_EUNSUPPORTED when that evaluation does not serve the shape (then the fp64 evaluation runs:
- * M <= 64, K % 128 != 0, K > 16384, M * K >= 2^31; also whenever a pre-scale or the zero-point form is used).
+ * M <= 64, K % 128 != 0, K > 16384, M * K >= 2^31; also whenever a pre-scale is used).
  */
 int lrq_ars_dense_diagnostics(int M, int K, size_t offsets[4]);
 
@@ -250,8 +250,10 @@ size_t lrq_workspace_bytes(int M, int N, int K, const lrq_rotation* rot, int act
  *   bias       float [N] or NULL.
  *   out_dtype  LRQ_OUT_BF16 (round-to-nearest-even) | LRQ_OUT_FP32.       Y: [M, N] out.
  *   ws         device workspace of at least lrq_workspace_bytes(M, N, K, rot, act_bits) bytes.
- * Runs as the rotate+quantize kernel(s) followed by the decode+MFMA GEMM kernel (large products: a decoding kernel and an int8
- * GEMM) on the same stream.
+ * Runs as the rotate+quantize kernel(s) followed by the decode+MFMA GEMM kernel on the same stream.  Large products with 4-bit weights
+ * and bf16 outputs decode the weights once (extra workgroups of the Hadamard kernel, or a kernel of their own) for an int8 GEMM;
+ * up to 16 tokens without a rotation or with a Hadamard rotation run as one kernel, unless Y overlaps X, and leave ws as it was.  Results do not depend
+ * on the choice, which lrq_qlinear_diagnostics tells.
  * Requires K % 64 == 0.
  */
 int lrq_qlinear(void* stream, const void* X, int M, int K, const lrq_rotation* rot, int act_bits,
@@ -260,9 +262,9 @@ int lrq_qlinear(void* stream, const void* X, int M, int K, const lrq_rotation* r
 
 /*
  * lrq_qlinear_static - lrq_qlinear for callers that cannot allocate device memory or carry a workspace around:
- * code running under HIP stream capture, tight serving loops, harnesses that forbid allocation.  Same arguments,
- * same kernels and bit-identical results as lrq_qlinear, minus the workspace: the activation codes, the token scales
- * and the rotation scratch live in a buffer of lrq_static_scratch_bytes() = 64 MiB that is part of the library's
+ * code running under HIP stream capture, tight serving loops, harnesses that forbid allocation.  Same arguments
+ * and bit-identical results as lrq_qlinear, minus the workspace: the activation codes, the token scales, the decoded
+ * weights and the rotation scratch live in a buffer of lrq_static_scratch_bytes() = 64 MiB that is part of the library's
  * code object (every device the library runs on holds one copy until the process ends).  The call allocates and
  * frees nothing.
  *   - A layer whose codes, scales and rotation scratch (lrq_workspace_bytes for N = 0) exceed the buffer is refused with

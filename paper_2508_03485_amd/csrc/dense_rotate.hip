@@ -29,26 +29,15 @@
 // (Cauchy-Schwarz on the many small entries, rho = max_j ||R[:, j]||_2; the few large ones - salient channels - term by
 // term), theta = 4 * mean |x|.  u~ is stored as fp32: one more rounding, 2^-24 |u~| <= 2^-24 S.
 // What fp32 cannot hold to full precision - squares, products and sums below 2^-126 - is bounded absolutely and added to the bound.
-#include "lrq_internal.h"
+#include "rotate_common.h"
 
 namespace lrq {
 namespace {
 
-constexpr int kWave = 64;
-constexpr double kMagic = 6755399441055744.0;   // 1.5 * 2^52: adding it rounds to an integer, ties to even
 constexpr int CAPC = 4;                          // amax candidates kept per row
 constexpr float kBoundSlack = 1.004f;            // covers the fp32 arithmetic in which the bound itself is evaluated
 
-// Monotone map double -> uint64 (unsigned order = numeric order), so that an unsigned atomic maximum is a maximum of doubles.
-// The zero-point form keeps, per row, the key of max u and the key of max (-u); the symmetric form the bits of max |u|.
-__device__ __forceinline__ unsigned long long okey(double v) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    return (b >> 63) ? ~b : b | 0x8000000000000000ull;
-}
-__device__ __forceinline__ double okey_value(unsigned long long k) {
-    return __longlong_as_double((long long)((k >> 63) ? k & 0x7fffffffffffffffull : ~k));
-}
-
+// The zero-point form keeps, per row, the key (okey) of max u and that of max (-u); the symmetric form the bits of max |u|.
 // The per-token quantizer of a row (Preliminaries, Eq. 1).  Symmetric form: inv = qmax / amax, code = rint(u inv).  Zero-point
 // form: range = max - min, L = 2^b - 1, inv = L / range, z = rint(min inv), x_q = clamp(rint(u inv) - z, 0, L), s = range / L,
 // stored as q = x_q - 2^(b-1) and zero = z + 2^(b-1); a constant row takes x_q = 0 and (s, z) = (|c|, sign c), (1, 0) for c = 0.
@@ -68,7 +57,7 @@ __device__ __forceinline__ RowQuant row_quant(unsigned long long kmax, unsigned 
         r.izero = 0;
     } else {
         const double L = 2.0 * qmax + 1.0, half = qmax + 1.0;       // qmax = 2^(b-1) - 1
-        const double vmax = okey_value(kmax), vmin = -okey_value(kmin), rng = vmax - vmin;
+        const double vmax = okey_inv(kmax), vmin = -okey_inv(kmin), rng = vmax - vmin;
         double sc, z;
         if (rng > 0.0) {
             r.inv = L / rng;
@@ -604,8 +593,9 @@ __global__ __launch_bounds__(256) void dense_row_candidates_kernel(const uint16_
 // R column (Rt holds R's columns contiguously; the eight pieces are one cache line) and forms its products (exact in fp64), then
 // the sum goes from lane to lane, each adding its own products; the other lanes' sums mean nothing meanwhile.  A k costs two vector
 // instructions that way instead of five and no trip through LDS; XA_DEPTH lines of an element are in flight.  A lane per element, the
-// operands handed out through LDS, took 67.3 us at 35100 x 3072 (432 MB at 6.4 TB/s) and 23.8 us at 8192 x 1152; this takes 71 and
-// 12.3 us.  (Products through LDS to a wave that only adds: 107 and 14.7 us.)
+// operands handed out through LDS, took 67.3 us at 35100 x 3072 (432 MB at 6.4 TB/s) and 23.8 us at 8192 x 1152; eight lanes take 71 and
+// 12.3 us, four lanes, two pieces each, which both of these sizes run (amax_eight_lanes), 58 and 10.0.  (Products through LDS to a
+// wave that only adds: 107 and 14.7 us.)
 constexpr int XA_DEPTH = 6;
 
 // DPP move of a double within rows of 16 lanes (0x111: from the lane below, 0x100 + n: from n lanes above)

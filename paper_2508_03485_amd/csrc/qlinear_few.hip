@@ -234,9 +234,12 @@ hipError_t launch_block(hipStream_t st, const uint16_t* X, int M, int K, int h, 
 
 }  // namespace
 
-// Every workgroup repeats the rotation and has a CU to itself (registers), so they have to fit one round.  us per call, one launch / two:
-// 2 x 1152 -> 6912 5.6 / 8.8, 14 x 1152 -> 6912 6.0 / 8.7, 5 x 3072 -> 8192 7.2 / 9.2, 16 x 1024 -> 8192 6.4 / 9.1, 3 x 4608 -> 4608 7.8 / 9.9;
-// in two rounds 14 x 1152 -> 12288 would take 9.5 / 9.0, 5 x 3072 -> 12288 12.7 / 10.3.
+// Every workgroup repeats the rotation, so there must not be more of them than CUs.  us per call, one launch / two: 2 x 1152 -> 6912 5.6 / 8.8,
+// 14 x 1152 -> 6912 6.0 / 8.7, 5 x 3072 -> 8192 7.2 / 9.2, 16 x 1024 -> 8192 6.4 / 9.1, 3 x 4608 -> 4608 7.8 / 9.9.  Past 256 workgroups, in device
+// time (a graph of calls; called one by one the host's rate hides up to 2 us of it), -> 10240: 2 x 1152 with h = 32, 64, 128 7.3 / 6.2, 6.9 / 6.5,
+// 8.4 / 6.6, 4 x 1024 with h = 256, 1024 8.4 / 7.2, 7.5 / 7.5, 8 x 2048 with h = 512 11.9 / 8.6, 5 x 3072 with h = 64, 1024 8.9 / 8.2, 12.6 / 9.3;
+// -> 24576 all lose more.  Registers let two workgroups share a CU in 19 of the 24 forms (all but h = 128 and the symmetric h = 256),
+// LDS does not for long exchanges; sharing one, two rotations take nearly twice as long.
 bool qlinear_few_applies(int M, int N, int K, int had_block) {
     return M <= 16 && K % 128 == 0 && (long)M * K <= kFewElements && had_block <= 1024 && (N + 31) / 32 <= 256;
 }
