@@ -136,6 +136,14 @@ def parse():
     return args
 
 
+def product_stage(ops, layer_ms, rot_ms, staged):
+    """Rate (TOPS), time (ms) and operations of the products inside lrq_qlinear calls: whole calls less their rotate + quantize calls, over
+    the layers that are such a pair of stages."""
+    ms = sum(whole - rot for whole, rot, on in zip(layer_ms, rot_ms, staged) if on)
+    n = sum(o for o, on in zip(ops, staged) if on)
+    return n / (ms * 1e-3) / 1e12, ms, n
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -311,7 +319,11 @@ def main():
 
     # ---------------------------------------------------------------- per-kernel durations (HIP events on the launch stream)
     ksteps = int(min(300, max(3, min(args.steps, round(0.25 / (ms_per_step * 1e-3))))))
-    ev = []
+    ev, whole = [], []
+    # the layers whose timed call is a rotate + quantize stage and a product (not the one-launch form of a few tokens)
+    form = "zero_point" if args.asym else "symmetric"
+    tiles = [lrq.qlinear_tile(l["spec"].M, l["spec"].N, l["spec"].K, l["rot"], l["spec"].w_bits, form) for l in layers]
+    staged = [t != (0, 0) and not (args.levels or fp8 or packed) for t in tiles]
     lead = torch.zeros(1, dtype=torch.int32, device=dev)
     for i in range(ksteps):
         # a ~0.5 ms lead-in kernel keeps the host ahead of the device, so that an interval between two events holds
@@ -340,12 +352,25 @@ def main():
                           levels=args.levels)
             d.record()
             ev.append((li, a, b, d))
+        # whole calls in a pass of their own: a layer's inputs are as cold as they were for its stages
+        if any(staged):
+            probes.launch_mfma(2048, 512, 1, lead)
+        for li, l in enumerate(layers):
+            if staged[li]:
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                lrq.qlinear(l["X"][c], l["rot"], l["spec"].a_bits, l["w"], out=l["Y"][c], workspace=l["ws"][c], asym=args.asym)
+                b.record()
+                whole.append((li, a, b))
     torch.cuda.synchronize()
     rot_ms = [0.0] * len(layers)
     gemm_ms = [0.0] * len(layers)
+    layer_ms = [0.0] * len(layers)
     for li, a, b, d in ev:
         rot_ms[li] += a.elapsed_time(b) / ksteps
         gemm_ms[li] += b.elapsed_time(d) / ksteps
+    for li, a, b in whole:
+        layer_ms[li] += a.elapsed_time(b) / ksteps
 
     per_layer = []
     agg = {}
@@ -380,11 +405,22 @@ def main():
                     traffic=None, note="multiply-accumulates counted as 2 ops; averaged over the "
                     "workload's layers, %d launches each" % ksteps,
                     avg_launch_ms=round(gemm_total_ms / len(layers), 4))
-    if not (args.levels or fp8 or packed or args.graph) and ms_per_step > sum(rot_ms):
+    if any(staged):
         # the product as the timed step runs it: lrq_qlinear, unlike lrq_qgemm, has room to decode the weights of large 4-bit layers once
-        # (qgemm_wide_kernel), so its share is the step less the rotate + quantize calls
-        step_tops = total_ops / ((ms_per_step - sum(rot_ms)) * 1e-3) / 1e12
-        roofline.update(in_step_achieved=round(step_tops, 2), in_step_frac=round(step_tops / mfma_peak, 4))
+        # (qgemm_wide_kernel).  Whole call less rotate + quantize call, each between two events of its own, so what bracketing adds (some
+        # 2 us) cancels; decoding beside the rotation and the gap between the stages count as the product's.  lrq_qgemm is given
+        # for the same layers, with what bracketing adds
+        stage_tops, product_ms, product_ops = product_stage([l["spec"].ops for l in layers], layer_ms, rot_ms, staged)
+        alone_ms = sum(gemm_ms[i] for i, on in enumerate(staged) if on)
+        wide = sum(1 for t, on in zip(tiles, staged) if on and t[1] == 256 and t[0] in (192, 224, 256))
+        alone = dict(kernel=roofline["kernel"], achieved=round(product_ops / (alone_ms * 1e-3) / 1e12, 2), avg_launch_ms=round(alone_ms / sum(staged), 4),
+                     note="lrq_qgemm, which decodes in its operand loader at every size, on the same layers")
+        alone["frac"] = round(alone["achieved"] / mfma_peak, 4)
+        roofline.update(kernel="product stage of lrq_qlinear: %s" % ("qgemm_wide_kernel (weights decoded once) on %d of %d layers" % (wide, sum(staged))
+                                                                      if wide else alone["kernel"]),
+                        achieved=round(stage_tops, 2), frac=round(stage_tops / mfma_peak, 4), avg_launch_ms=round(product_ms / sum(staged), 4),
+                        note="multiply-accumulates counted as 2 ops; whole call less its rotate + quantize call, %d of each per layer" % ksteps,
+                        qgemm_alone=alone)
     # Hadamard rotate+quantize: algorithmic bytes = 2 (bf16 in) + 1 (code out) per element + 4 per token
     had = [(li, l) for li, l in enumerate(layers) if l["spec"].rotation == "hadamard"]
     roofline_rq = None
@@ -409,7 +445,7 @@ def main():
                               "fp64 totals, error bound, exact recomputation of undecided elements)", achieved=round(tf, 2),
                               peak=BF16_MFMA_PEAK_TFLOPS, unit="TFLOP/s", frac=round(tf / BF16_MFMA_PEAK_TFLOPS, 4), traffic=None,
                               avg_launch_ms=round(t / len(dense), 4),
-                              note="time of the whole call (seven kernels with R prepared offline, ten without), flops of the product alone")
+                              note="time of the whole call, flops of the product alone")
         # what the error bound left undecided in the first such layer's last call, and how far the approximate product
         # really is from the fp64 evaluation (LRQ_ROT_DENSE_F64 leaves u in fp64 at the head of its workspace)
         l0 = dense[0][1]

@@ -42,3 +42,14 @@ def test_oracle_baseline_leg_on_a_tiny_sample():
     # (a few milliseconds of work at most a second long on any host)
     s = specs[0]
     assert out["value"] >= 2 * 32 * 48 * s.K / 1.0 / 1e12
+
+
+@pytest.mark.parametrize("bracket", [0.0, 0.002, 0.01])
+def test_product_rate_is_that_of_the_product(bracket):
+    """Two layers of 30 and 50 us of product behind 10 and 20 us of rotation, and one that is a single launch of 6 us; what two events
+    around a call add is in every interval and must not change the rate."""
+    ops, rot, product = [3.0e10, 5.0e10, 1.0e9], [0.010, 0.020, 0.003], [0.030, 0.050, 0.003]
+    rot_ms = [r + bracket for r in rot]
+    layer_ms = [0.0 if i == 2 else r + p + bracket for i, (r, p) in enumerate(zip(rot, product))]
+    tops, ms, n = bench.product_stage(ops, layer_ms, rot_ms, [True, True, False])
+    assert abs(ms - 0.080) < 1e-12 and n == 8.0e10 and abs(tops - 1000.0) < 1e-6
