@@ -400,6 +400,7 @@ def main():
     gemm_tops = total_ops / (gemm_total_ms * 1e-3) / 1e12
     mfma_peak = BF16_MFMA_PEAK_TFLOPS if args.levels else INT8_MFMA_PEAK_TOPS      # the FP8 peak equals the int8 one (5.0 PFLOP/s)
     roofline = dict(bound="mfma", kernel=("qgemm_levels_kernel (decode + bf16 MFMA + rescale)" if args.levels else
+                                          "qgemm_fp8_kernel (decode + FP8 MFMA + rescale)" if fp8 else
                                           "qgemm_kernel (decode + int8 MFMA + rescale)"), achieved=round(gemm_tops, 2),
                     peak=mfma_peak, unit="TFLOP/s", frac=round(gemm_tops / mfma_peak, 4),
                     traffic=None, note="multiply-accumulates counted as 2 ops; averaged over the "
