@@ -284,15 +284,20 @@ hipError_t launch_wide(hipStream_t st, const int8_t* q, const float* scale, cons
 
 // Times in us, decoding included, fitted (with 4 % between fit and measurement) to 600 measurements of each height over M = 200 ..
 // 35100, N = 96 .. 12288, K = 320 .. 12288.  A round of tiles, one per CU, takes k per K block + k_fill times the share of the CUs that
-// have a tile (the chip's clock falls with the work in flight) + its epilogue (1.5 us above the fit: the boards differ most in how fast
-// all CUs' stores drain, 8192 x 1152 -> 4608 with three rounds of them 60.2 us against 62.9 on one and 67.8 against 64.4 on another).  The
-// lower tiles are taken where they fill the last round better (us with 192 / 224 / 256 rows: 8192 x 1152 -> 4608 50.2 / 52.1 / 55.5,
-// 4608 x 3072 -> 9216 136 / 128 / 143, 35100 x 3072 -> 12288 1165 / 1138 / 1104).  Decoded along with the rotation, the weights cost
-// neither their launch nor most of their time (8192 x 1152 -> 4608: 3 us of 62).
-// Against qgemm.hip, whose predicted time has to be 3 % longer: 35100 x 3072 -> 12288 1340 us at 4 bits.  3-bit
-// weights, whose decoding takes a third of the instructions, stay there: 35100 x 3072 -> 9216 835 us against 846 here.  So do outputs other than
-// bf16 rows of whole 16-byte pieces: fp32 outputs (22488 x 6144 -> 4736 616 us against 678, but 30107 x 3072 -> 490 87 against 62: every tile's
-// 256 KB are written at once) and ragged rows (element by element: 20688 x 2304 -> 2389 212 us against 143) rarely gain.
+// have a tile (the chip's clock falls with the work in flight) + its epilogue.  The lower tiles are taken where they fill the last round
+// better (us with 192 / 224 / 256 rows: 8192 x 4608 -> 1152 50.2 / 52.1 / 55.5, 4608 x 3072 -> 9216 136 / 128 / 143, 35100 x 3072 -> 12288
+// 1165 / 1138 / 1104).  The zero-point form's epilogue needs more registers than there are at 224 and 256 rows: the compiler spills 2 and 16,
+// which is most of what zero_point adds there.  Decoded along with the rotation, the weights cost neither their launch nor most of their
+// time (8192 x 1152 -> 4608: 3 us of 62).
+// Against qgemm.hip, whose predicted time has to be 3 % longer than this one's with an epilogue 1.5 us longer than fitted: the boards differ in
+// how fast all CUs' stores drain once outputs no longer stay in the Infinity Cache.  75 shapes with K = 320 .. 4608, N % 8 == 0, both
+// kernels timed on five boards with the buffers rotated through 700 MB: none of the 54 that the rule takes loses 1 % on any board, and
+// all 75 gain 7.2 % on average.  The fit as it is, with a demand of 3 / 5 %, takes 70 / 67 for 7.9 / 8.0 %, but 6 / 4 lose on a board, up to
+// 12 / 8 % (and 8192 x 1152 -> 4608, not among the 75, -2 .. +7 % by board); + 0.5 / + 1 us with 3 % takes 67 / 63 for 8.1 / 7.8 %, 3 / 2 lose, up to 6 / 1.5 %.
+// 35100 x 3072 -> 12288: 1340 us at 4 bits in qgemm.hip.  3-bit weights, whose decoding takes a third of the instructions, stay there:
+// 35100 x 3072 -> 9216 835 us against 846 here.  So do outputs other than bf16 rows of whole 16-byte pieces: fp32 outputs (22488 x 6144 -> 4736
+// 616 us against 678, but 30107 x 3072 -> 490 87 against 62: every tile's 256 KB are written at once) and ragged rows (element by element:
+// 20688 x 2304 -> 2389 212 us against 143) rarely gain.
 struct WideCost { int rows; float k, k_fill, tile, zero_point, once; };
 constexpr WideCost kWideCost[3] = {{192, 0.315f, 0.288f, 6.06f, 0.3f, 6.9f},
                                    {224, 0.357f, 0.318f, 6.87f, 1.3f, 6.1f},

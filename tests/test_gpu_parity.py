@@ -1113,11 +1113,11 @@ def test_qlinear_with_weights_decoded_once(lrq, M, N, K, w_bits, asym):
 
 
 @pytest.mark.parametrize("kind,h,M,N,K,form,rows", [
-    ("hadamard", 128, 6000, 1288, 1152, "symmetric", 192),       # decoded beside blocks inside a quad
+    ("hadamard", 128, 9000, 1032, 1152, "symmetric", 192),       # decoded beside blocks inside a quad
     ("hadamard", 64, 9000, 1032, 1152, "zero_point", 192),
     ("hadamard", 32, 6000, 2056, 2240, "symmetric", 224),        # K % 128: decoded by a launch of its own
-    ("hadamard", 256, 7001, 2056, 2304, "symmetric", 256),       # beside the two-pass kernel, other wave counts
-    ("hadamard", 512, 4500, 3080, 1536, "prescale", 256),
+    ("hadamard", 256, 4500, 3080, 2304, "symmetric", 256),       # beside the two-pass kernel, other wave counts
+    ("hadamard", 512, 8192, 1544, 1536, "prescale", 256),
     ("hadamard", 512, 6000, 2056, 1536, "zero_point", 224),
     ("hadamard", 1024, 4096, 3080, 3072, "zero_point", 224),
     ("hadamard", 2048, 7001, 1544, 4096, "prescale", 224),
@@ -1127,12 +1127,12 @@ def test_qlinear_with_weights_decoded_once(lrq, M, N, K, w_bits, asym):
     ("hadamard", 8192, 4096, 3080, 8192, "zero_point", 224),     # the generic kernel: a launch of its own
     ("none", 0, 9000, 3080, 1152, "prescale", 256),
     ("dense", 0, 8192, 3080, 1024, "symmetric", 224),            # decoded into the rotation's scratch
-    ("prepared", 0, 5000, 2056, 2304, "zero_point", 192),
+    ("prepared", 0, 5000, 2056, 3072, "zero_point", 192),
     ("dense", 0, 6000, 2056, 2048, "prescale", 224),             # all in fp64
     ("dense", 0, 900, 12296, 3072, "symmetric", 192),            # more weights than scratch: behind it
     ("dense_f64", 0, 6000, 2056, 2048, "symmetric", 224),        # u stays in the scratch
     ("blockperm", 128, 6000, 2056, 2048, "symmetric", 224),      # the structured rotation's scratch
-    ("blockperm", 256, 8192, 3080, 1024, "zero_point", 224),
+    ("blockperm", 256, 8192, 3080, 2048, "zero_point", 224),
 ])
 def test_qlinear_with_weights_decoded_under_every_rotation(lrq, kind, h, M, N, K, form, rows):
     """Weights decoded beside each rotation kernel, in a launch of their own, behind the rotation's scratch and over it: against the two
