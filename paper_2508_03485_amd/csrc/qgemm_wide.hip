@@ -293,7 +293,8 @@ hipError_t launch_wide(hipStream_t st, const int8_t* q, const float* scale, cons
 // how fast all CUs' stores drain once outputs no longer stay in the Infinity Cache.  75 shapes with K = 320 .. 4608, N % 8 == 0, both
 // kernels timed on five boards with the buffers rotated through 700 MB: none of the 54 that the rule takes loses 1 % on any board, and
 // all 75 gain 7.2 % on average.  The fit as it is, with a demand of 3 / 5 %, takes 70 / 67 for 7.9 / 8.0 %, but 6 / 4 lose on a board, up to
-// 12 / 8 % (and 8192 x 1152 -> 4608, not among the 75, -2 .. +7 % by board); + 0.5 / + 1 us with 3 % takes 67 / 63 for 8.1 / 7.8 %, 3 / 2 lose, up to 6 / 1.5 %.
+// 12 / 8 % (8192 x 1152 -> 4608, not among the 75, loses on some boards and gains on others, by up to 7 %); + 0.5 / + 1 us with 3 % takes
+// 67 / 63 for 8.1 / 7.8 %, 3 / 2 lose, up to 6 / 1.5 %.
 // 35100 x 3072 -> 12288: 1340 us at 4 bits in qgemm.hip.  3-bit weights, whose decoding takes a third of the instructions, stay there:
 // 35100 x 3072 -> 9216 835 us against 846 here.  So do outputs other than bf16 rows of whole 16-byte pieces: fp32 outputs (22488 x 6144 -> 4736
 // 616 us against 678, but 30107 x 3072 -> 490 87 against 62: every tile's 256 KB are written at once) and ragged rows (element by element:
